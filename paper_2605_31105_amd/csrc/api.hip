@@ -121,7 +121,6 @@ static void layout_plan(Plan* p, size_t slots, size_t splits2, size_t splits3, s
   p->colsum = take(U * (P > 0 ? P : 1) * sizeof(float));
   p->pooled = take(U * (P > 0 ? P : 1) * sizeof(float));
   p->fixed = take(slots);
-  p->redo = take(U * p->S1 * sizeof(int32_t));
   // the compact V0 copy serves the generic retained passes only; the fast
   // path reads V0 rows through idx
   const bool fast_path = stream_supported(*p) && merge_fast_supported(*p);
@@ -270,7 +269,6 @@ int run_compress(const Plan& p, const void* q_obs, const void* K, const void* V,
   // (with caller-supplied selection scores the window's column sums are not formed)
   full.ypart = F(p.ypart); full.colsum = p.prefix > 0 && !ext_scores ? F(p.colsum) : nullptr;
   full.prefix = p.prefix; full.xout = nullptr; full.split_p = true;
-  full.redo = (int*)(ws + p.redo);
   const bool fast = stream_supported(p);
   auto pass_a = [&](const AttnPass& a) { return fast ? launch_stream(p, a, 0, s) : launch_lse_pass(p, a, s); };
   auto pass_b = [&](const AttnPass& a) { return fast ? launch_stream(p, a, 1, s) : launch_prob_pass(p, a, s); };

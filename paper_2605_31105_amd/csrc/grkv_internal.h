@@ -66,7 +66,7 @@ struct Plan {
   const int32_t* rag_upd_order;    // [rag_upd_blocks] update block run by each block
   int rag_splits, rag_upd_blocks, upd_spb;
   // workspace offsets (bytes)
-  size_t pmax1, psum1, lse1, lse1_log2, ypart, y, colsum, pooled, fixed, v0c, redo;
+  size_t pmax1, psum1, lse1, lse1_log2, ypart, y, colsum, pooled, fixed, v0c;
   size_t pmax2, psum2, lse2, lse2_log2, xvpart, x, resid, npart, mpart, gram, z, zhi, zlo, stats_ws;
   // [U][kZParts] double (csplit > 1): ||Z||^2 of each solve block's columns,
   // and ||Y||^2 in the last entry
@@ -115,9 +115,6 @@ struct AttnPass {
   // the full-cache LSE, with its row sums in mpart [U][S][mp]
   float lse_bias;
   float* mpart;
-  // full-cache pass B (bf16 streaming): per-split flags [U][S] of the fp16
-  // P.V pass; flagged splits are recomputed exactly
-  int* redo;
 };
 
 hipError_t launch_lse_pass(const Plan& p, const AttnPass& a, hipStream_t s);

@@ -12,9 +12,11 @@
 //    row-major with the 16-byte chunks of row r XOR-swizzled by r, which keeps
 //    the MFMA operand reads of K free of bank conflicts.
 //  * Pass B's P.V takes fp16 P times the V tile converted to fp16 in LDS (one
-//    MFMA); a split whose V leaves the fp16 range is flagged and recomputed
-//    by the exact mode with P as a bf16 hi+lo pair (two MFMAs, about 16 bits
-//    of P), which the retained pass also uses.
+//    MFMA); a block whose V leaves the fp16 range streams its split again
+//    with P as a bf16 hi+lo pair (two MFMAs, about 16 bits of P), which the
+//    retained pass also uses.  Done in the same launch: a second launch whose
+//    blocks only read a flag and exit cost every call 2 to 3 us (one layer of
+//    32k tokens: 165.7 against 163.0 us).
 //  * The P.V B-operand (four consecutive keys of one d column per lane) is
 //    read from the row-major V tile with the LDS transpose read
 //    ds_read_b64_tr_b16: within a 16-lane group, lane 4e+q supplies the
@@ -64,7 +66,6 @@ struct StreamK {
   float* npart;           // retained pass: Gram partials [U][S][mp][mp]
   float* mpart;           // retained pass: row sums of P [U][S][mp]
   float lse_bias;         // pass B: P = 2^(t - (lse_log2 - lse_bias))
-  int* redo;              // full-cache pass B: per-split flag [U][S] (see the modes)
   // retained passes: rows of K (gather_k) and/or V (gather_v) are read
   // through kpos [U][nk] from tensors of src_rows rows per unit
   const int32_t* kpos;
@@ -226,15 +227,14 @@ __device__ __forceinline__ void load_tile_rows(const u16* base, int tile0, int k
 // Kernel modes: pass A (log-sum-exp partials), pass B over the full cache
 // (P.V partials and SnapKV column sums), pass B over the retained set (P.V
 // partials and the Gram matrix X_G X_G^T of the fixed-masked probabilities).
-//  * kModeFull: P.V in fp16 (fp16 P times the fp16-converted V tile); a split
-//    whose P.V comes out non-finite (a V element beyond the fp16 range) sets
-//    its redo flag;
-//  * kModeFullExact: P as a bf16 hi+lo pair times the bf16 V tile, run on the
-//    splits whose redo flag is set (the other blocks exit at once).
-enum { kModeLse = 0, kModeFull = 1, kModeRetained = 2, kModeFullExact = 3 };
+// Pass B over the full cache forms P.V in fp16 (fp16 P times the fp16-converted
+// V tile); a block whose P.V comes out non-finite (a V element beyond the fp16
+// range) runs its split again with P as a bf16 hi+lo pair times the bf16 V
+// tile.
+enum { kModeLse = 0, kModeFull = 1, kModeRetained = 2 };
 
 template <int MODE>
-constexpr bool is_full() { return MODE == kModeFull || MODE == kModeFullExact; }
+constexpr bool is_full() { return MODE == kModeFull; }
 
 template <bool B>
 struct BoolTag {
@@ -746,13 +746,13 @@ __attribute__((amdgpu_waves_per_eu(MODE == kModeLse ? 4 : 2))) void stream_kerne
   // pass B 4 x 16 KB (one stage holds the tile whose V is being converted);
   // retained pass 5 x 16 KB (one block of twice the waves per CU, so its
   // ring is deeper)
-  constexpr int NSTAGE = MODE == kModeFull ? 4 : MODE == kModeFullExact ? 3 : 5;
-  static_assert(NSTAGE >= 3 && NSTAGE <= 5, "ring depths with an unrolled loop below");
+  constexpr int NSTAGE = MODE == kModeFull ? 4 : 5;
+  static_assert(NSTAGE == 4 || NSTAGE == 5, "ring depths with an unrolled loop below");
   constexpr int STAGE_BYTES = kTileBytes * (PASS_B ? 2 : 1);
   __shared__ __attribute__((aligned(16))) char stg0[STAGE_BYTES];
   __shared__ __attribute__((aligned(16))) char stg1[STAGE_BYTES];
   __shared__ __attribute__((aligned(16))) char stg2[STAGE_BYTES];
-  __shared__ __attribute__((aligned(16))) char stg3[NSTAGE > 3 ? STAGE_BYTES : 16];
+  __shared__ __attribute__((aligned(16))) char stg3[STAGE_BYTES];
   __shared__ __attribute__((aligned(16))) char stg4[NSTAGE > 4 ? STAGE_BYTES : 16];
   __shared__ float colpart[2][WAVES][TK];
   // retained pass only: X_G fragment exchange [NT][2][64], fixed flags and
@@ -763,7 +763,6 @@ __attribute__((amdgpu_waves_per_eu(MODE == kModeLse ? 4 : 2))) void stream_kerne
   __shared__ uint8_t fixl[RET ? kRetMaxSlots : 1];
   __shared__ int32_t posl[RET ? kRetMaxSlots : 1];
 
-  if (MODE == kModeFullExact && !a.redo[(size_t)blockIdx.y * a.S + blockIdx.x]) return;
   Stream<D, WAVES, MODE, NSTAGE> sm{a};
   // unit, split, key count and partial index of this block
   int s = blockIdx.x, nk = a.nk;
@@ -927,14 +926,10 @@ __attribute__((amdgpu_waves_per_eu(MODE == kModeLse ? 4 : 2))) void stream_kerne
     } else {
       sm.issue(0, stg0);
       sm.issue(1, stg1);
-      if constexpr (NSTAGE >= 4) sm.issue(2, stg2);
+      sm.issue(2, stg2);
       if constexpr (NSTAGE == 5) sm.issue(3, stg3);
       for (int t = 0; t < sm.ntiles; t += NSTAGE) {
-        if constexpr (NSTAGE == 3) {
-          sm.template step<F16>(t + 0, stg0, stg2, S);
-          sm.template step<F16>(t + 1, stg1, stg0, S);
-          sm.template step<F16>(t + 2, stg2, stg1, S);
-        } else if constexpr (NSTAGE == 4) {
+        if constexpr (NSTAGE == 4) {
           sm.template step<F16>(t + 0, stg0, stg3, S);
           sm.template step<F16>(t + 1, stg1, stg0, S);
           sm.template step<F16>(t + 2, stg2, stg1, S);
@@ -957,7 +952,7 @@ __attribute__((amdgpu_waves_per_eu(MODE == kModeLse ? 4 : 2))) void stream_kerne
   if constexpr (MODE == kModeFull) {
     run(BoolTag<true>{});
     // A V element beyond the fp16 range (|v| > 65504) makes this split's P.V
-    // non-finite: flag the split for the exact pass.
+    // non-finite: the whole block runs the split again in the exact form.
     bool bad = false;
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
@@ -965,9 +960,13 @@ __attribute__((amdgpu_waves_per_eu(MODE == kModeLse ? 4 : 2))) void stream_kerne
       for (int dt = 0; dt < D / 16; ++dt)
 #pragma unroll
         for (int i = 0; i < 4; ++i) bad |= !__builtin_isfinite(S.y[rt][dt][i]);
-    bad = __syncthreads_or(bad);
-    if (threadIdx.x == 0) a.redo[pidx] = bad ? 1 : 0;
-    if (bad) return;
+    if (__syncthreads_or(bad)) {   // (also ends the first run's use of the ring)
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int dt = 0; dt < D / 16; ++dt) S.y[rt][dt] = zero4();
+      run(BoolTag<false>{});
+    }
   } else {
     run(BoolTag<false>{});
   }
@@ -1041,7 +1040,6 @@ hipError_t launch_stream_t(const Plan& p, const AttnPass& a, hipStream_t s) {
   k.lse_ready = a.lse_ready ? 1 : 0;
   k.ypart = a.ypart; k.colsum = a.colsum; k.prefix = a.prefix;
   k.fixed = a.fixed; k.npart = a.npart; k.mpart = a.mpart; k.lse_bias = a.lse_bias;
-  k.redo = a.redo;
   k.kpos = a.kpos; k.src_rows = a.src_rows;
   k.gather_k = a.gather_k ? 1 : 0; k.gather_v = a.gather_v ? 1 : 0;
   k.kcopy = (u16*)a.kcopy;
@@ -1084,13 +1082,7 @@ hipError_t launch_stream_w(const Plan& p, const AttnPass& a, hipStream_t s) {
 template <int D>
 hipError_t launch_stream_d(const Plan& p, const AttnPass& a, int mode, hipStream_t s) {
   if (mode == kModeLse) return launch_stream_w<D, kModeLse>(p, a, s);
-  if (mode == kModeFull) {
-    // fp16 pass, then the exact pass on the splits it flagged
-    if (!a.redo) return hipErrorInvalidValue;
-    hipError_t e = launch_stream_w<D, kModeFull>(p, a, s);
-    if (e != hipSuccess) return e;
-    return launch_stream_w<D, kModeFullExact>(p, a, s);
-  }
+  if (mode == kModeFull) return launch_stream_w<D, kModeFull>(p, a, s);
   return launch_stream_w<D, kModeRetained>(p, a, s);
 }
 
