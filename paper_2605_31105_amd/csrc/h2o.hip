@@ -6,24 +6,34 @@
 // 0..i:
 //   s_j = sum_g sum_{i >= j} 2^(t_{g,i,j} - LSE2_{g,i}),  t = q . k log2(e) / sqrt(d).
 // This is the work of a prefill attention without P.V (O(n^2 d) per head),
-// done in two MFMA passes with no atomics, each with 8 waves, so that a tile
-// staged in LDS feeds many MFMAs per barrier:
-//  * h2o_lse_kernel: a block takes 512 / G prompt positions of all G query
-//    heads (512 rows, head-major; wave w owns rows 64w .. 64w + 63, four
-//    16-row tiles as MFMA B operands in registers) and streams the key tiles
-//    (64 keys) up to its last position through LDS, keeping per row and lane
-//    an integer reference exponent and an fp64 sum of 2^(t - ref) (as the
-//    window's pass A does); the four lanes of a row merge at the end into
-//    LSE2 (log2 domain).  Blocks run latest positions first (most keys);
-//  * h2o_colsum_kernel: a block takes 128 prefix keys (wave w: keys
-//    16w .. 16w + 15 as A operands in registers; more keys per block re-read
-//    the queries less but balance the causal triangle worse, measured slower)
-//    and streams the query tiles
-//    (256 / G positions of all heads) at or after its first key, with their
-//    LSE2, through LDS; P = 2^(t - LSE2) under the causal rule is summed per
-//    key, in fp32 within a query tile and in fp64 across tiles; a 16-lane
-//    reduction at the end gives the key's score.
-// Causal masks are applied only on tiles that straddle the diagonal.
+// done in two MFMA passes with no atomics, each with 8 waves per block:
+//  * h2o_lse_kernel: a block takes 128 RT / G prompt positions of all G query
+//    heads (head-major rows; a wave owns RT 16-row tiles as MFMA B operands in
+//    registers) and streams the keys up to its last position through LDS in
+//    tiles of 64, keeping per row and lane an integer reference exponent and an
+//    fp64 sum of 2^(t - ref) (as the window's pass A does); the four lanes of
+//    a row merge at the end into LSE2 (log2 domain).  Blocks run latest
+//    positions first (most keys);
+//  * h2o_colsum_kernel: a block takes 128 KT prefix keys (a wave: KT 16-key
+//    tiles as A operands in registers) and streams the query tiles (128 / G
+//    positions of all heads) at or after its first key, with their LSE2,
+//    through LDS; P = 2^(t - LSE2) under the causal rule is summed per key, in
+//    fp32 within a query tile and in fp64 across tiles; a 16-lane reduction at
+//    the end gives the key's score.
+// What bounds them: per 64 logits the VALU takes fma + exp + add (16 cycles of
+// a SIMD, the exponential at half rate) and the MFMAs 16 more, so both passes
+// are written to run the two side by side: the products of the next 16-wide
+// tile are issued among the exponentials of the current one (the accumulators
+// are double-buffered), one barrier per staged tile, and four stationary tiles
+// per wave, so that one fragment read from LDS feeds four MFMAs (with one, as
+// the column sums had it, the LDS reads took longer than the MFMAs).  Blocks
+// are ordered tile-major over the units, longest first: unit-major, the last
+// unit's long blocks started late and the column sums took 1.6 times the
+// row pass for the same work.  Eight units of 32k tokens with 4 heads each,
+// both passes: 13.1 -> 8.6 ms (two tiles per wave 10.0 ms).
+// Calls with few blocks take fewer stationary tiles per wave (h2o_tiles).
+// Causal masks are applied only on tiles that straddle the diagonal, and a
+// wave skips the tiles that it sees nothing of.
 // The scores then drive grkv_compress_scored (selection with pool width 1).
 #include "grkv_device.h"
 #include "grkv_internal.h"
@@ -35,263 +45,314 @@ namespace {
 
 constexpr int kH2oWaves = 8;
 constexpr int kH2oTh = kH2oWaves * 64;
-constexpr int kH2oRows = 512;       // rows (positions x heads) of an LSE block
 constexpr int kH2oKT = 64;          // keys per streamed key tile (LSE pass)
-constexpr int kH2oColKT = 1;       // 16-key tiles per wave (column sums)
-constexpr int kH2oColKeys = 16 * kH2oColKT * kH2oWaves;   // keys per column-sum block
-constexpr int kH2oQRows = 256;      // rows (positions x heads) of a streamed query tile
+constexpr int kH2oQRows = 128;      // rows (positions x heads) of a streamed query tile
 
 // ------------------------------------------------------------ row LSE ----
-template <int D, int G>
+template <int D, int G, int RT>
 __global__ __launch_bounds__(kH2oTh) void h2o_lse_kernel(const u16* __restrict__ q_all,
-                                                         const u16* __restrict__ K, int n,
+                                                         const u16* __restrict__ K, int U, int n,
                                                          float scale_log2, float* __restrict__ lse2) {
-  constexpr int TQ = kH2oRows / G;          // prompt positions per block
+  constexpr int WR = 16 * RT;               // rows per wave
+  constexpr int TQ = WR * kH2oWaves / G;    // prompt positions per block
   constexpr int KS = D + 8;                 // LDS row stride (bf16)
   constexpr int CH = kH2oKT * D / 8;        // 16-byte chunks of a key tile
-  constexpr int PER = (CH + kH2oTh - 1) / kH2oTh;
-  constexpr int RT = 4;                     // 16-row tiles per wave
+  constexpr int PER = CH / kH2oTh;
   constexpr int KT = kH2oKT / 16;           // 16-key tiles per key tile
+  constexpr int DS = D / 32;
   constexpr float NINF = -__builtin_huge_valf();
+  static_assert(CH % kH2oTh == 0 && TQ >= WR && TQ % WR == 0, "whole tiles");
   __shared__ __attribute__((aligned(16))) u16 kt_s[2][kH2oKT * KS];
   const int nb = (n + TQ - 1) / TQ;
-  const int u = blockIdx.y, p0 = (nb - 1 - (int)blockIdx.x) * TQ, tid = threadIdx.x;
+  const int u = blockIdx.x % U, p0 = (nb - 1 - (int)(blockIdx.x / U)) * TQ, tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, gq = lane >> 4;
-  const int head = (64 * wave) / TQ, pw0 = p0 + (64 * wave) % TQ;   // the wave's head, first position
+  const int head = (WR * wave) / TQ, pw0 = p0 + (WR * wave) % TQ;   // the wave's head, first position
   const u16* ku = K + (size_t)u * n * D;
   const u16* qh = q_all + ((size_t)u * G + head) * n * D;
 
   // the wave's rows: positions pw0 + 16 rt + l16 (B operand layout)
-  bf16x8 qb[RT][D / 32];
+  bf16x8 qb[RT][DS];
   int pos[RT];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
     pos[rt] = pw0 + 16 * rt + l16;
     const int pr = min(pos[rt], n - 1);
 #pragma unroll
-    for (int ks = 0; ks < D / 32; ++ks)
+    for (int ks = 0; ks < DS; ++ks)
       qb[rt][ks] = *reinterpret_cast<const bf16x8*>(qh + (size_t)pr * D + ks * 32 + 8 * gq);
   }
-  // keys 0 .. min(n, p0 + TQ) - 1 in tiles of kH2oKT; a tile needs the
-  // causal test only where it reaches past the block's first position
+  // keys 0 .. min(n, p0 + TQ) - 1 in tiles of kH2oKT
   const int kend = min(n, p0 + TQ);
   const int ntiles = (kend + kH2oKT - 1) / kH2oKT;
-  static_assert(CH % kH2oTh == 0, "whole key tiles per block");
   bf16x8 kr[PER];
-#define H2O_LOAD_K(T)                                                                     \
-  _Pragma("unroll") for (int k = 0; k < PER; ++k) {                                       \
-    const int e = tid + k * kH2oTh;                                                       \
-    const int key = min((T) * kH2oKT + e / (D / 8), n - 1), ch = e % (D / 8);           \
-    kr[k] = *reinterpret_cast<const bf16x8*>(ku + (size_t)key * D + ch * 8);              \
-  }
-  float mref[RT];
-  double srun[RT];
-#pragma unroll
-  for (int rt = 0; rt < RT; ++rt) {
-    mref[rt] = NINF;
-    srun[rt] = 0.0;
-  }
-  H2O_LOAD_K(0)
-  for (int t = 0; t < ntiles; ++t) {
-    u16* cur = kt_s[t & 1];
+  auto load_k = [&](int t) {   // (past the last tile: clamped rows, never used)
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
       const int e = tid + k * kH2oTh;
-      *reinterpret_cast<bf16x8*>(cur + (e / (D / 8)) * KS + (e % (D / 8)) * 8) = kr[k];
+      const int key = min(t * kH2oKT + e / (D / 8), n - 1), ch = e % (D / 8);
+      kr[k] = *reinterpret_cast<const bf16x8*>(ku + (size_t)key * D + ch * 8);
     }
-    __syncthreads();
-    H2O_LOAD_K(t + 1)   // (past the last tile: clamped rows, never stored)
-    const bool edge = (t + 1) * kH2oKT - 1 > pw0 || (t + 1) * kH2oKT > n;   // wave-uniform
-    // tv[rt][kt][i]: key 64t + 16kt + 4gq + i, row 16rt + l16
-    float tv[RT][KT][4];
+  };
+  auto store_k = [&](u16* dst) {
 #pragma unroll
-    for (int kt = 0; kt < KT; ++kt) {
-      bf16x8 kf[D / 32];
+    for (int k = 0; k < PER; ++k) {
+      const int e = tid + k * kH2oTh;
+      *reinterpret_cast<bf16x8*>(dst + (e / (D / 8)) * KS + (e % (D / 8)) * 8) = kr[k];
+    }
+  };
+  float nref[RT];   // minus the reference exponent (+inf before the first visible key)
+  double srun[RT];
 #pragma unroll
-      for (int ks = 0; ks < D / 32; ++ks)
+  for (int rt = 0; rt < RT; ++rt) {
+    nref[rt] = -NINF;
+    srun[rt] = 0.0;
+  }
+  load_k(0);
+  store_k(kt_s[0]);
+  load_k(1);
+  for (int t = 0; t < ntiles; ++t) {
+    const u16* cur = kt_s[t & 1];
+    __syncthreads();   // tile t is in LDS, and every wave is done with tile t - 1
+    store_k(kt_s[(t + 1) & 1]);
+    load_k(t + 2);
+    const int kt0 = t * kH2oKT;
+    if (kt0 > pw0 + WR - 1) continue;   // no visible key for this wave (wave-uniform)
+    // the causal test matters only on tiles that reach past the wave's first row
+    const bool edge = kt0 + kH2oKT - 1 > pw0 || kt0 + kH2oKT > n;
+    // acc[rt]: keys 64t + 16kt + 4gq + i, row 16rt + l16
+    auto products = [&](int kt, f32x4 (&acc)[RT]) {
+      bf16x8 kf[DS];
+#pragma unroll
+      for (int ks = 0; ks < DS; ++ks)
         kf[ks] = *reinterpret_cast<const bf16x8*>(cur + (16 * kt + l16) * KS + ks * 32 + 8 * gq);
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        f32x4 acc = zero4();
+      for (int rt = 0; rt < RT; ++rt) acc[rt] = zero4();
 #pragma unroll
-        for (int ks = 0; ks < D / 32; ++ks) acc = mfma_bf16(kf[ks], qb[rt][ks], acc);
+      for (int ks = 0; ks < DS; ++ks)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) tv[rt][kt][i] = acc[i] * scale_log2;
-      }
-    }
-    if (edge) {
+        for (int rt = 0; rt < RT; ++rt) acc[rt] = mfma_bf16(kf[ks], qb[rt][ks], acc[rt]);
+    };
+    // sums of 2^(t - ref) over the tile, per row tile
+    auto tile_sums = [&](auto edge_tag, float (&a)[RT]) {
+      constexpr bool EDGE = decltype(edge_tag)::value;
+      f32x4 st[2][RT];
 #pragma unroll
-      for (int kt = 0; kt < KT; ++kt)
+      for (int rt = 0; rt < RT; ++rt) a[rt] = 0.f;
+      products(0, st[0]);
+#pragma unroll
+      for (int kt = 0; kt < KT; ++kt) {
+        if (kt + 1 < KT) products(kt + 1, st[(kt + 1) & 1]);
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const int key = t * kH2oKT + 16 * kt + 4 * gq + i;
-            if (!(key <= pos[rt] && key < n)) tv[rt][kt][i] = NINF;
-          }
-    }
-    // per row tile: the tile's sum against the running reference (masked keys
-    // add nothing and never meet a -inf reference; only edge tiles have any)
-    auto accumulate = [&](auto edge_tag) {
-      constexpr bool EDGE = decltype(edge_tag)::value;
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        auto tile_sum = [&](float ref) {
-          float a = 0.f;
-#pragma unroll
-          for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              if constexpr (EDGE)
-                a += tv[rt][kt][i] != NINF ? __builtin_amdgcn_exp2f(tv[rt][kt][i] - ref) : 0.f;
-              else
-                a += __builtin_amdgcn_exp2f(tv[rt][kt][i] - ref);
+            const float x = __builtin_amdgcn_exp2f(fmaf(st[kt & 1][rt][i], scale_log2, nref[rt]));
+            if constexpr (EDGE) {
+              const int key = kt0 + 16 * kt + 4 * gq + i;
+              a[rt] += (key <= pos[rt] && key < n) ? x : 0.f;
+            } else {
+              a[rt] += x;
             }
-          return a;
-        };
-        float a = tile_sum(mref[rt]);
-        // a new reference when the tile's sum leaves [0, 2^64] (also taken on
-        // the lane's first visible key, while the reference is still -inf)
-        if (!(a <= 0x1p64f)) {
-          float mx = NINF;
-#pragma unroll
-          for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) mx = fmaxf(mx, tv[rt][kt][i]);
-          const float ref = ceilf(mx);   // finite: a was not 0, so a key is visible
-          srun[rt] = mref[rt] == NINF ? 0.0 : ldexp(srun[rt], (int)(mref[rt] - ref));
-          mref[rt] = ref;
-          a = tile_sum(ref);
-        }
-        srun[rt] += (double)a;
+          }
       }
     };
-    if (edge)
-      accumulate(std::true_type{});
-    else
-      accumulate(std::false_type{});
-    __syncthreads();   // the next store overwrites the other buffer only; this
-                       // one is rewritten two tiles later
+    float a[RT];
+    if (edge) tile_sums(std::true_type{}, a);
+    else tile_sums(std::false_type{}, a);
+    bool moved = false;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) moved |= !(a[rt] <= 0x1p64f);
+    // a new reference when a tile's sum leaves [0, 2^64] (also taken on the
+    // lane's first visible key, while the reference is still -inf): rare, so
+    // the tile's products are formed again
+    if (__any(moved)) {
+      float mx[RT];
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) mx[rt] = NINF;
+#pragma unroll 1
+      for (int kt = 0; kt < KT; ++kt) {
+        f32x4 st[RT];
+        products(kt, st);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int key = kt0 + 16 * kt + 4 * gq + i;
+            if (key <= pos[rt] && key < n) mx[rt] = fmaxf(mx[rt], st[rt][i]);
+          }
+      }
+      float b[RT];
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        b[rt] = 0.f;
+        if (!(a[rt] <= 0x1p64f) && mx[rt] != NINF) {
+          const float ref = ceilf(mx[rt] * scale_log2);
+          srun[rt] = nref[rt] == -NINF ? 0.0 : ldexp(srun[rt], (int)(-nref[rt] - ref));
+          nref[rt] = -ref;
+        }
+      }
+#pragma unroll 1
+      for (int kt = 0; kt < KT; ++kt) {
+        f32x4 st[RT];
+        products(kt, st);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int key = kt0 + 16 * kt + 4 * gq + i;
+            const float x = __builtin_amdgcn_exp2f(fmaf(st[rt][i], scale_log2, nref[rt]));
+            b[rt] += (key <= pos[rt] && key < n) ? x : 0.f;
+          }
+      }
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+        if (!(a[rt] <= 0x1p64f)) a[rt] = b[rt];
+    }
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) srun[rt] += (double)a[rt];
   }
   // merge the four lanes of each row (exact power-of-two rescales)
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
-    const float M = max_over_groups(mref[rt]);
-    const double part = mref[rt] == NINF ? 0.0 : ldexp(srun[rt], (int)(mref[rt] - M));
+    const float mref = -nref[rt];
+    const float M = max_over_groups(mref);
+    const double part = mref == NINF ? 0.0 : ldexp(srun[rt], (int)(mref - M));
     const double tot = sum_over_groups(part);
     if (gq == 0 && pos[rt] < n)
       lse2[((size_t)u * G + head) * n + pos[rt]] = (float)((double)M + log2(tot));
   }
-#undef H2O_LOAD_K
 }
 
 // --------------------------------------------------------- column sums ----
-template <int D, int G>
+template <int D, int G, int KT>
 __global__ __launch_bounds__(kH2oTh) void h2o_colsum_kernel(
     const u16* __restrict__ q_all, const u16* __restrict__ K, const float* __restrict__ lse2,
-    int n, int P, float scale_log2, float* __restrict__ scores) {
+    int U, int n, int P, float scale_log2, float* __restrict__ scores) {
   constexpr int TQ = kH2oQRows / G;         // positions per query tile
   constexpr int QS = D + 8;                 // LDS row stride (bf16) of Q rows
   constexpr int NR = kH2oQRows;             // rows of a query tile (head-major)
+  constexpr int NRT = NR / 16;
   constexpr int CH = NR * D / 8;            // 16-byte chunks of a query tile
-  constexpr int PER = (CH + kH2oTh - 1) / kH2oTh;
+  constexpr int PER = CH / kH2oTh;
+  constexpr int DS = D / 32;
+  static_assert(CH % kH2oTh == 0 && NR <= kH2oTh && TQ % 16 == 0, "whole query tiles per block");
   __shared__ __attribute__((aligned(16))) u16 q_s[2][NR * QS];
   __shared__ float l_s[2][NR];
-  const int u = blockIdx.y, k0 = blockIdx.x * kH2oColKeys, tid = threadIdx.x;
+  const int u = blockIdx.x % U, k0 = blockIdx.x / U * 16 * KT * kH2oWaves, tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, gq = lane >> 4;
   const u16* ku = K + (size_t)u * n * D;
   const u16* qu = q_all + (size_t)u * G * n * D;
   const float* lu = lse2 + (size_t)u * G * n;
 
-  // this wave's keys (kH2oColKT 16-key tiles) as A operands
-  constexpr int KT = kH2oColKT;
+  // this wave's keys (KT 16-key tiles) as A operands
   const int kb = k0 + 16 * KT * wave;
-  bf16x8 kf[KT][D / 32];
+  bf16x8 kf[KT][DS];
 #pragma unroll
   for (int kt = 0; kt < KT; ++kt) {
     const int key = min(kb + 16 * kt + l16, n - 1);
 #pragma unroll
-    for (int ks = 0; ks < D / 32; ++ks)
+    for (int ks = 0; ks < DS; ++ks)
       kf[kt][ks] = *reinterpret_cast<const bf16x8*>(ku + (size_t)key * D + ks * 32 + 8 * gq);
   }
   // query tiles at or after the block's first key
   const int qt0 = k0 / TQ, qt1 = (n + TQ - 1) / TQ;
-  static_assert(CH % kH2oTh == 0 && NR <= kH2oTh, "whole query tiles per block");
   bf16x8 qr[PER];
   float lr = 0.f;
-#define H2O_LOAD_Q(QT)                                                                    \
-  {                                                                                       \
-    const int pl0 = (QT) * TQ;                                                            \
-    _Pragma("unroll") for (int k = 0; k < PER; ++k) {                                     \
-      const int e = tid + k * kH2oTh;                                                     \
-      const int row = e / (D / 8), ch = e % (D / 8);                                      \
-      const int hg = row / TQ, pos = min(pl0 + row % TQ, n - 1);                          \
-      qr[k] = *reinterpret_cast<const bf16x8*>(qu + ((size_t)hg * n + pos) * D + ch * 8);  \
-    }                                                                                     \
-    if (tid < NR) {                                                                       \
-      const int hg = tid / TQ, pos = pl0 + tid % TQ;                                      \
-      lr = pos < n ? lu[(size_t)hg * n + pos] : 0.f;                                      \
-    }                                                                                     \
-  }
-  double col[KT][4];
+  auto load_q = [&](int qt) {   // (past the last tile: clamped rows, never used)
+    const int pl0 = qt * TQ;
 #pragma unroll
-  for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) col[kt][i] = 0.0;
-  H2O_LOAD_Q(qt0)
-  for (int qt = qt0; qt < qt1; ++qt) {
-    const int b = (qt - qt0) & 1;
+    for (int k = 0; k < PER; ++k) {
+      const int e = tid + k * kH2oTh;
+      const int row = e / (D / 8), ch = e % (D / 8);
+      const int hg = row / TQ, pos = min(pl0 + row % TQ, n - 1);
+      qr[k] = *reinterpret_cast<const bf16x8*>(qu + ((size_t)hg * n + pos) * D + ch * 8);
+    }
+    if (tid < NR) lr = lu[(size_t)(tid / TQ) * n + min(pl0 + tid % TQ, n - 1)];
+  };
+  auto store_q = [&](int b) {
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
       const int e = tid + k * kH2oTh;
       *reinterpret_cast<bf16x8*>(&q_s[b][(e / (D / 8)) * QS + (e % (D / 8)) * 8]) = qr[k];
     }
     if (tid < NR) l_s[b][tid] = lr;
-    __syncthreads();
-    H2O_LOAD_Q(qt + 1)   // (past the last tile: clamped rows, never stored)
+  };
+  double col[KT][4];
+#pragma unroll
+  for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) col[kt][i] = 0.0;
+  load_q(qt0);
+  store_q(0);
+  load_q(qt0 + 1);
+  for (int qt = qt0; qt < qt1; ++qt) {
+    const int b = (qt - qt0) & 1;
+    __syncthreads();   // tile qt is in LDS, and every wave is done with tile qt - 1
+    store_q(b ^ 1);
+    load_q(qt + 2);
     const int p0 = qt * TQ;
+    if (p0 + TQ - 1 < kb) continue;   // before all of the wave's keys (wave-uniform)
     // the causal test and the end of the prompt matter only on tiles that
     // start before the wave's last key or run past n (wave-uniform)
     const bool edge = p0 < kb + 16 * KT - 1 || p0 + TQ > n;
+    // acc[kt]: keys kb + 16kt + 4gq + i, row 16rt + l16 (head 16rt / TQ)
+    auto products = [&](int rt, f32x4 (&acc)[KT], float& nl) {
+      bf16x8 qf[DS];
+#pragma unroll
+      for (int ks = 0; ks < DS; ++ks)
+        qf[ks] = *reinterpret_cast<const bf16x8*>(&q_s[b][(16 * rt + l16) * QS + ks * 32 + 8 * gq]);
+      nl = -l_s[b][16 * rt + l16];
+#pragma unroll
+      for (int kt = 0; kt < KT; ++kt) acc[kt] = zero4();
+#pragma unroll
+      for (int ks = 0; ks < DS; ++ks)
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt) acc[kt] = mfma_bf16(kf[kt][ks], qf[ks], acc[kt]);
+    };
     float part[KT][4];
 #pragma unroll
     for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
       for (int i = 0; i < 4; ++i) part[kt][i] = 0.f;
-#pragma unroll 4
-    for (int rt = 0; rt < NR / 16; ++rt) {
-      // rows 16 rt .. : head 16 rt / TQ, positions p0 + (16 rt) % TQ + l16
-      bf16x8 qf[D / 32];
+    auto tile = [&](auto edge_tag) {
+      constexpr bool EDGE = decltype(edge_tag)::value;
+      f32x4 st[2][KT];
+      float nl[2];
+      auto consume = [&](int rt, const f32x4 (&t4)[KT], float nlr) {
+        const int rpos = p0 + (16 * rt) % TQ + l16;
 #pragma unroll
-      for (int ks = 0; ks < D / 32; ++ks)
-        qf[ks] = *reinterpret_cast<const bf16x8*>(&q_s[b][(16 * rt + l16) * QS + ks * 32 + 8 * gq]);
-      const int rpos = p0 + (16 * rt) % TQ + l16;
-      const float nl = -l_s[b][16 * rt + l16];
+        for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-      for (int kt = 0; kt < KT; ++kt) {
-        f32x4 acc = zero4();
-#pragma unroll
-        for (int ks = 0; ks < D / 32; ++ks) acc = mfma_bf16(kf[kt][ks], qf[ks], acc);
-        // lane: key kb + 16 kt + 4 gq + i, row (head, position rpos)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float x = __builtin_amdgcn_exp2f(fmaf(acc[i], scale_log2, nl));
-          if (edge) {
-            const int key = kb + 16 * kt + 4 * gq + i;
-            part[kt][i] += (rpos < n && key <= rpos) ? x : 0.f;
-          } else {
-            part[kt][i] += x;
+          for (int i = 0; i < 4; ++i) {
+            const float x = __builtin_amdgcn_exp2f(fmaf(t4[kt][i], scale_log2, nlr));
+            if constexpr (EDGE) {
+              const int key = kb + 16 * kt + 4 * gq + i;
+              part[kt][i] += (rpos < n && key <= rpos) ? x : 0.f;
+            } else {
+              part[kt][i] += x;
+            }
           }
-        }
+      };
+      products(0, st[0], nl[0]);
+#pragma unroll 1
+      for (int rt = 0; rt < NRT - 2; rt += 2) {
+        products(rt + 1, st[1], nl[1]);
+        consume(rt, st[0], nl[0]);
+        products(rt + 2, st[0], nl[0]);
+        consume(rt + 1, st[1], nl[1]);
       }
-    }
+      products(NRT - 1, st[1], nl[1]);
+      consume(NRT - 2, st[0], nl[0]);
+      consume(NRT - 1, st[1], nl[1]);
+    };
+    if (edge) tile(std::true_type{});
+    else tile(std::false_type{});
 #pragma unroll
     for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
       for (int i = 0; i < 4; ++i) col[kt][i] += (double)part[kt][i];
-    __syncthreads();   // the tile in buffer b is read before it is rewritten
   }
   // sum over the 16 lanes (rows) sharing each key, in fp64
 #pragma unroll
@@ -306,20 +367,49 @@ __global__ __launch_bounds__(kH2oTh) void h2o_colsum_kernel(
       const int key = kb + 16 * kt + 4 * gq + i;
       if (l16 == 0 && key < P) scores[(size_t)u * P + key] = (float)v;
     }
-#undef H2O_LOAD_Q
+}
+
+// Stationary 16-wide tiles per wave of a pass with `items` rows (or keys) per
+// unit: four when that still gives two blocks per compute unit, else fewer
+// (shorter blocks over more compute units).
+int h2o_tiles(int U, int64_t items) {
+  for (int t = 4; t > 1; t /= 2)
+    if (U * ((items + 128 * t - 1) / (128 * t)) >= 512) return t;
+  return 1;
+}
+
+template <int D, int G, int T>
+void launch_h2o_lse(const u16* q_all, const u16* K, int U, int n, float scale_log2, float* lse2,
+                    hipStream_t s) {
+  constexpr int TQ = 16 * T * kH2oWaves / G;
+  hipLaunchKernelGGL((h2o_lse_kernel<D, G, T>), dim3((unsigned)((n + TQ - 1) / TQ) * U), dim3(kH2oTh), 0, s,
+                     q_all, K, U, n, scale_log2, lse2);
+}
+
+template <int D, int G, int T>
+void launch_h2o_colsum(const u16* q_all, const u16* K, const float* lse2, int U, int n, int P,
+                       float scale_log2, float* scores, hipStream_t s) {
+  constexpr int KB = 16 * T * kH2oWaves;
+  hipLaunchKernelGGL((h2o_colsum_kernel<D, G, T>), dim3((unsigned)((P + KB - 1) / KB) * U), dim3(kH2oTh), 0, s,
+                     q_all, K, lse2, U, n, P, scale_log2, scores);
 }
 
 template <int D, int G>
 hipError_t launch_h2o_t(const u16* q_all, const u16* K, int U, int n, int P, float* lse2,
                         float* scores, hipStream_t s) {
-  const float scale_log2 = (float)(1.4426950408889634 / __builtin_sqrt((double)D));
-  constexpr int TQ = kH2oRows / G;
-  hipLaunchKernelGGL((h2o_lse_kernel<D, G>), dim3((n + TQ - 1) / TQ, U), dim3(kH2oTh), 0, s, q_all,
-                     K, n, scale_log2, lse2);
+  const float sc = (float)(1.4426950408889634 / __builtin_sqrt((double)D));
+  switch (h2o_tiles(U, (int64_t)n * G)) {
+    case 4: launch_h2o_lse<D, G, 4>(q_all, K, U, n, sc, lse2, s); break;
+    case 2: launch_h2o_lse<D, G, 2>(q_all, K, U, n, sc, lse2, s); break;
+    default: launch_h2o_lse<D, G, 1>(q_all, K, U, n, sc, lse2, s); break;
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || P < 1) return e;
-  hipLaunchKernelGGL((h2o_colsum_kernel<D, G>), dim3((P + kH2oColKeys - 1) / kH2oColKeys, U),
-                     dim3(kH2oTh), 0, s, q_all, K, lse2, n, P, scale_log2, scores);
+  switch (h2o_tiles(U, P)) {
+    case 4: launch_h2o_colsum<D, G, 4>(q_all, K, lse2, U, n, P, sc, scores, s); break;
+    case 2: launch_h2o_colsum<D, G, 2>(q_all, K, lse2, U, n, P, sc, scores, s); break;
+    default: launch_h2o_colsum<D, G, 1>(q_all, K, lse2, U, n, P, sc, scores, s); break;
+  }
   return hipGetLastError();
 }
 

@@ -136,3 +136,33 @@ def test_compress_scored_long_prefix_sample_misses_the_top():
         kept = gpu["idx"][u][: cfg.budget - cfg.window]
         assert np.all(kept % stride != 0)   # no sampled (low) position is kept
         print(check_unit(cfg, q, K, V, gpu, u, scores=s[u].astype(np.float64)), flush=True)
+
+
+@pytest.mark.parametrize("units,group,d,n", [
+    (128, 4, 128, 1000),    # four row tiles per wave, two key tiles
+    (256, 2, 128, 1009),    # four and four
+    (256, 1, 64, 777),      # two and two, head dim 64
+    (64, 8, 64, 2050),      # four and four, eight heads
+])
+def test_h2o_scores_stationary_tiles(units, group, d, n):
+    # calls with many blocks keep two or four 16-wide tiles stationary per wave;
+    # a logit of up to about 2^5 carries 2^-19 absolute in fp32, which the
+    # exponential turns into 2e-6 relative per term
+    import paper_2605_31105_amd as G
+    g = torch.Generator(device="cuda")
+    g.manual_seed(units + n)
+    K = torch.randn((units, n, d), device="cuda", generator=g).to(torch.bfloat16)
+    q = torch.randn((units, group, n, d), device="cuda", generator=g).to(torch.bfloat16)
+    w = 16
+    print("case", units, group, d, n, flush=True)
+    s = G.h2o_scores(q, K, w)
+    torch.cuda.synchronize()
+    keep = torch.ones((n, n), dtype=torch.bool, device="cuda").tril()
+    for u in (0, units // 2, units - 1):
+        ref = torch.zeros(n, dtype=torch.float64, device="cuda")
+        for h in range(group):
+            L = (q[u, h].double() @ K[u].double().t().contiguous()) / d ** 0.5
+            ref += torch.softmax(L.masked_fill(~keep, float("-inf")), 1).sum(0)
+        err = ((s[u].double() - ref[: n - w]).abs() / ref[: n - w]).max().item()
+        print("unit", u, "rel err %.2e" % err, flush=True)
+        assert err <= 1e-5
