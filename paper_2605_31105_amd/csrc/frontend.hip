@@ -4,12 +4,27 @@
 // all heads of the layer (ties to the lower head, then the lower position),
 // and head h keeps w plus the number of its tokens taken.
 //
-// One block per layer.  Pooled scores are non-negative, so their fp32 bit
-// patterns order like the values: a radix select over the 31-bit keys (three
-// digits of 11, 11 and 9 bits, one LDS histogram pass over the layer's scores
-// per digit) finds the k-th largest key T; a last pass counts every head's
-// keys above T and equal to T, and the keys equal to T are shared out in
-// head order.
+// One block per layer (the entry point has no workspace, so blocks cannot
+// share a layer).  Pooled scores are non-negative, so their fp32 bit patterns
+// order like the values, and the k-th largest key T is found in one full
+// sweep over the layer's scores:
+//  * 8192 keys are sampled (in large layers four from each of 2048 cache
+//    lines, since every line fetched costs as much as in a full sweep) and two
+//    order statistics either side of rank k bisected in registers; they
+//    bracket T;
+//  * one sweep counts, per head, the keys at or above the bracket and appends
+//    the keys inside it (a few percent) to LDS with their head, one LDS
+//    atomic per wave and 32 keys per lane;
+//  * radix rounds on those candidates find T, and they complete the per-head
+//    counts of keys above T and equal to T (shared out in head order).
+// A layer is 1 MB at 8 heads of 32k and one compute unit reads it at about
+// 100 GB/s, so the sweeps are what it costs: four of them (a histogram sweep
+// per radix digit of the whole key, then the counts) took 95 us for 32 layers
+// of 8 x 32k scores, the sample and one sweep take 59 us.
+// The bracket is used only when the exact counts confirm that it holds T and
+// the candidates fit; otherwise (heavily tied scores, an unlucky sample) the
+// radix select over the full keys runs: three digits of 11, 11 and 9 bits, one
+// LDS histogram sweep per digit, then a counting sweep.
 #include "grkv_device.h"
 #include "grkv_internal.h"
 
@@ -48,10 +63,217 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
   return v;
 }
 
+// Sum over the 64 lanes of a wave (DPP within rows of 16, then the rows).
+__device__ __forceinline__ uint32_t wave_sum_dpp(uint32_t v) {
+  int x = (int)v;
+  x += __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x141, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x140, 0xF, 0xF, false);
+  return (uint32_t)(__builtin_amdgcn_readlane(x, 0) + __builtin_amdgcn_readlane(x, 16) +
+                    __builtin_amdgcn_readlane(x, 32) + __builtin_amdgcn_readlane(x, 48));
+}
+
+constexpr int kAdaWaves = kAdaThreads / 64;
+constexpr int kAdaSamplePer = 8;
+constexpr int kAdaSample = kAdaSamplePer * kAdaThreads;
+constexpr uint32_t kAdaCand = 12288;   // candidates held in LDS
+constexpr uint32_t kAdaTop = 0x7F800001u;
+constexpr uint32_t kAdaSlack = 32768u;
+constexpr int64_t kAdaSparse = 65536;  // four samples span at least 32 keys (one line) from here
+
+// LDS of the one-sweep search, over the histogram area of the full radix.
+struct AdaLds {
+  uint32_t key[kAdaCand];
+  uint8_t head[kAdaCand];
+  uint32_t part[2][2][kAdaWaves];   // alternating halves: one barrier per step
+  uint32_t hist[256];
+  uint32_t sh[4];
+  uint32_t n;
+};
+static_assert(sizeof(AdaLds) <= sizeof(uint32_t) * kAdaBins * kAdaCopies, "fits the histogram area");
+
+// T by the sampled bracket; gt and eq (zeroed) receive the per-head counts.
+// Returns false, with gt and eq unchanged, when the bracket does not hold.
+__device__ bool bracket_search(const uint32_t* __restrict__ key, int64_t N, int H, int P,
+                               uint32_t kk, AdaLds& w, uint32_t* gt, uint32_t* eq) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int parity = 0;
+  // block totals of two counts per thread
+  auto totals = [&](uint32_t c0, uint32_t c1, uint32_t& t0, uint32_t& t1) {
+    c0 = wave_sum_dpp(c0);
+    c1 = wave_sum_dpp(c1);
+    if (lane == 0) { w.part[parity][0][wave] = c0; w.part[parity][1][wave] = c1; }
+    __syncthreads();
+    t0 = t1 = 0;
+#pragma unroll
+    for (int q = 0; q < kAdaWaves; ++q) { t0 += w.part[parity][0][q]; t1 += w.part[parity][1][q]; }
+    t0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)t0);
+    t1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)t1);
+    parity ^= 1;
+  };
+  // 1. the bracket [lo, hi): the samples about 4 sqrt(r) + 16 ranks either
+  // side of rank r = k / stride, each bisected down to kAdaSlack units in the
+  // last place (2^-8 relative: far less than the ranks' width) and kept on its
+  // safe side
+  uint32_t lo = 0u, hi = kAdaTop;
+  if (N > (int64_t)kAdaCand) {
+    // sample i is key i * stride, or (layers of at least kAdaSparse keys) key
+    // (i / 4) * 4 stride + 8 (i % 4): of four neighbouring samples' span, the
+    // first 25 keys
+    const int64_t stride = (N + kAdaSample - 1) / kAdaSample;
+    const int ns = (int)((N + stride - 1) / stride);
+    const bool sparse = N >= kAdaSparse;
+    uint32_t sv[kAdaSamplePer];
+#pragma unroll
+    for (int m = 0; m < kAdaSamplePer; ++m) {
+      const int i = tid + m * kAdaThreads;
+      const int64_t j = sparse ? (int64_t)(i >> 2) * (4 * stride) + 8 * (i & 3) : (int64_t)i * stride;
+      const uint32_t x = key[j < N ? j : N - 1];
+      sv[m] = i < ns && j < N ? x : 0u;
+    }
+    const int r = (int)((int64_t)kk / stride), delta = 4 * (int)sqrtf((float)r) + 16;
+    const bool act[2] = {r - delta >= 0, r + delta < ns};
+    const uint32_t J[2] = {(uint32_t)(r - delta), (uint32_t)(r + delta)};
+    uint32_t L[2] = {0u, 0u}, U[2] = {kAdaTop, kAdaTop};
+#pragma unroll 1
+    for (int it = 0; it < 32; ++it) {
+      const bool go0 = act[0] && U[0] - L[0] > kAdaSlack, go1 = act[1] && U[1] - L[1] > kAdaSlack;
+      if (!go0 && !go1) break;
+      const uint32_t m0 = L[0] + (U[0] - L[0]) / 2, m1 = L[1] + (U[1] - L[1]) / 2;
+      uint32_t c0 = 0, c1 = 0, t0, t1;
+#pragma unroll
+      for (int m = 0; m < kAdaSamplePer; ++m) {
+        c0 += sv[m] >= m0;
+        c1 += sv[m] >= m1;
+      }
+      totals(c0, c1, t0, t1);
+      if (go0) { if (t0 > J[0]) L[0] = m0; else U[0] = m0; }
+      if (go1) { if (t1 > J[1]) L[1] = m1; else U[1] = m1; }
+    }
+    if (act[0]) hi = U[0];
+    if (act[1]) lo = L[1];
+    if (!(lo < hi)) return false;
+  }
+  // 2. one sweep, head by head: keys at or above hi counted, keys in [lo, hi)
+  // appended
+  __syncthreads();
+  if (tid == 0) w.n = 0u;
+  __syncthreads();
+  const uint32_t width = hi - lo;
+  uint32_t above = 0;
+  for (int h = 0; h < H; ++h) {
+    const uint32_t* kh = key + (size_t)h * P;
+    uint32_t ch = 0;
+    for (int e0 = 0; e0 < P; e0 += kAdaThreads * kAdaUnroll) {
+      uint32_t x[kAdaUnroll];
+#pragma unroll
+      for (int k = 0; k < kAdaUnroll; ++k) x[k] = kh[min(e0 + k * kAdaThreads + tid, P - 1)];
+      uint32_t in = 0;   // bit k: key k lies inside the bracket
+#pragma unroll
+      for (int k = 0; k < kAdaUnroll; ++k) {
+        const bool live = e0 + k * kAdaThreads + tid < P;
+        ch += live && x[k] >= hi;
+        in |= (uint32_t)(live && x[k] - lo < width) << k;
+      }
+      const uint32_t cnt = __builtin_popcount(in);
+      uint32_t incl = cnt;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t t = __shfl_up(incl, off);
+        if (lane >= off) incl += t;
+      }
+      const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+      uint32_t base = 0;
+      if (lane == 0 && tot) base = atomicAdd(&w.n, tot);
+      uint32_t o = (uint32_t)__builtin_amdgcn_readfirstlane((int)base) + incl - cnt;
+      // the few keys inside are read again (from cache): a test per key of
+      // the 32 in registers costs more
+      while (in) {
+        const int k = __builtin_ctz(in);
+        in &= in - 1;
+        const uint32_t y = kh[e0 + k * kAdaThreads + tid];
+        if (o < kAdaCand) { w.key[o] = y; w.head[o] = (uint8_t)h; }
+        ++o;
+      }
+    }
+    ch = wave_sum_dpp(ch);
+    if (lane == 0 && ch) atomicAdd(&gt[h], ch);
+    above += ch;   // (this wave's share)
+  }
+  uint32_t chi, unused;
+  totals(lane == 0 ? above : 0u, 0u, chi, unused);   // the barrier also publishes the candidates
+  const uint32_t L = w.n;
+  uint32_t clo = chi + L;
+  if (L > kAdaCand || chi >= kk || clo < kk) {   // (block-uniform)
+    __syncthreads();
+    for (int h = tid; h < H; h += kAdaThreads) gt[h] = 0u;
+    __syncthreads();
+    return false;
+  }
+  // 3. radix rounds on the candidates' offsets: clo >= k > chi throughout
+#pragma unroll 1
+  for (int it = 0; it < 5 && hi - lo > 1; ++it) {
+    const int bits = 32 - __builtin_clz(hi - lo - 1);   // hi - lo - 1 < 2^bits
+    const int shift = bits > 8 ? bits - 8 : 0;
+    if (tid < 256) w.hist[tid] = 0u;
+    __syncthreads();
+    for (uint32_t e = tid; e < L; e += kAdaThreads) {
+      const uint32_t x = w.key[e];
+      if (x - lo < hi - lo) atomicAdd(&w.hist[(x - lo) >> shift], 1u);
+    }
+    __syncthreads();
+    if (wave == 0) {
+      // lane l holds bins 4(63 - l) .. +3: a prefix sum over the lanes counts
+      // the keys at or above each lane's bins
+      const int b0 = 4 * (63 - lane);
+      uint32_t h4[4], suf = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { h4[i] = w.hist[b0 + i]; suf += h4[i]; }
+      uint32_t incl = suf;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t t = __shfl_up(incl, off);
+        if (lane >= off) incl += t;
+      }
+      uint32_t abv = chi + incl - suf, bc = 0, bh = 0;
+      int best = -1;
+#pragma unroll
+      for (int i = 3; i >= 0; --i) {
+        const uint32_t c = abv + h4[i];
+        if (best < 0 && c >= kk) { best = b0 + i; bc = c; bh = abv; }
+        abv = c;
+      }
+      const uint64_t hit = __ballot(best >= 0);   // not empty: clo >= k
+      if (hit && lane == __builtin_ctzll(hit)) {
+        const uint64_t nh = (uint64_t)lo + ((uint64_t)(best + 1) << shift);
+        w.sh[0] = lo + ((uint32_t)best << shift);
+        w.sh[1] = nh < hi ? (uint32_t)nh : hi;
+        w.sh[2] = bc;
+        w.sh[3] = bh;
+      }
+    }
+    __syncthreads();
+    lo = w.sh[0];
+    hi = w.sh[1];
+    clo = w.sh[2];
+    chi = w.sh[3];
+    __syncthreads();
+  }
+  const uint32_t T = lo;
+  for (uint32_t e = tid; e < L; e += kAdaThreads) {
+    const uint32_t x = w.key[e];
+    if (x > T) atomicAdd(&gt[w.head[e]], 1u);
+    if (x == T) atomicAdd(&eq[w.head[e]], 1u);
+  }
+  return true;
+}
+
 __global__ __launch_bounds__(kAdaThreads) void adaptive_kernel(const float* __restrict__ pooled,
                                                                int H, int P, int64_t kk, int w,
                                                                int32_t* __restrict__ budgets) {
-  __shared__ uint32_t hist[kAdaBins * kAdaCopies];
+  __shared__ __attribute__((aligned(16))) uint32_t hist[kAdaBins * kAdaCopies];
   __shared__ uint32_t scratch[kAdaThreads / 64];
   __shared__ uint32_t gt[kAdaMaxHeads], eq[kAdaMaxHeads];
   __shared__ uint32_t pick[2];
@@ -61,12 +283,17 @@ __global__ __launch_bounds__(kAdaThreads) void adaptive_kernel(const float* __re
   if (kk > N) kk = N;
   for (int h = tid; h < H; h += kAdaThreads) gt[h] = eq[h] = 0;
 
+  __syncthreads();
+  const bool done = kk > 0 && bracket_search(key, N, H, P, (uint32_t)kk,
+                                             *reinterpret_cast<AdaLds*>(hist), gt, eq);
+  __syncthreads();   // hist is the search's LDS
+
   // digits from the top: bits 30..20, 19..9, 8..0
   constexpr int kShift[3] = {20, 9, 0};
   constexpr int kBits[3] = {11, 11, 9};
   uint32_t prefix = 0;          // the digits of T found so far, in place
   uint32_t krem = (uint32_t)kk; // rank of T among the keys matching the prefix
-  if (kk > 0) {
+  if (kk > 0 && !done) {
 #pragma unroll
     for (int lev = 0; lev < 3; ++lev) {
       const int shift = kShift[lev], nb = 1 << kBits[lev], top = shift + kBits[lev];
@@ -116,7 +343,7 @@ __global__ __launch_bounds__(kAdaThreads) void adaptive_kernel(const float* __re
   const uint32_t T = prefix;
 
   // keys above T and equal to T, per head (one LDS add per wave and head)
-  if (kk > 0) {
+  if (kk > 0 && !done) {
     for (int h = 0; h < H; ++h) {
       uint32_t a = 0, e = 0;
       for_keys(key + (size_t)h * P, P, [&](uint32_t x) {

@@ -146,3 +146,37 @@ def test_ragged_generic_path(label, cfg_id, over, budgets):
     cfg = W.config(cfg_id, **over)
     q, K, V = W.make_batch(cfg)
     _ragged_check(cfg, q, K, V, budgets)
+
+
+@pytest.mark.parametrize("layers,heads,P,budget,dist", [
+    (3, 1, 500, 60, "normal"),          # every key fits the candidate area
+    (2, 3, 4096, 300, "normal"),        # 12288 keys: the most that fit
+    (2, 3, 4097, 300, "normal"),        # one head more than fits: sampled
+    (4, 8, 20011, 1500, "normal"),
+    (2, 8, 9000, 700, "two-values"),    # ties too many for the bracket: full radix
+    (2, 5, 8000, 700, "sampled-low"),   # samples miss the top: the bracket fails its check
+    (2, 8, 20000, 1500, "sampled-low"),  # the same with four samples per cache line
+    (2, 4, 6000, 6032, "normal"),       # every token of the layer taken
+    (2, 4, 6000, 32, "normal"),         # none taken
+])
+def test_adaptive_budgets_search_paths(layers, heads, P, budget, dist):
+    import paper_2605_31105_amd as G
+    rng = np.random.default_rng(layers * 1000 + P)
+    U = layers * heads
+    if dist == "two-values":
+        p = np.where(rng.random((U, P)) < 0.3, 1.0, 0.5).astype(np.float32)
+    else:
+        p = np.exp(1.5 * rng.standard_normal((U, P))).astype(np.float32)
+    if dist == "sampled-low":
+        flat = p.reshape(layers, -1)
+        stride = -(-flat.shape[1] // 8192)
+        assert stride > 1
+        flat += 1.0
+        flat[:, ::stride] *= np.float32(1e-3)
+        if flat.shape[1] >= 65536:
+            for k in range(4):
+                flat[:, 8 * k::4 * stride] *= np.float32(1e-3)
+    print("case", layers, heads, P, budget, dist, flush=True)
+    got = G.adaptive_budgets(torch.from_numpy(p).cuda(), layers, heads, budget, 32)
+    torch.cuda.synchronize()
+    assert np.array_equal(got.cpu().numpy(), FO.adaptive_budgets(p, layers, heads, budget, 32))
