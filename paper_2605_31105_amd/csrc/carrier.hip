@@ -4,18 +4,29 @@
 // cosine similarity with its own (the key-similarity matching of D2O/KVMerger),
 // and the loads a_i of the retained slots are summarised per unit.
 //
-// match_kernel: a block takes 256 consecutive cache positions of one unit (one
-// wave per 32 of them) and streams the unit's retained keys through LDS in
-// tiles of 64, gathered through idx; the inverse norm of each retained key is
-// formed while the tile is staged.  S = K_q K_ret^T runs on the bf16 MFMA
+// match_kernel: a block takes 256 consecutive cache positions of one unit (two
+// 16-row tiles per wave in registers) and streams the unit's retained keys
+// through LDS in tiles of 64, gathered through idx; the inverse norm of each
+// retained key is formed while the tile is staged (NaN past the last slot, so
+// that those never compare larger).  S = K_q K_ret^T runs on the bf16 MFMA
 // (exact products, fp32 sums); a lane keeps, for each of its 8 rows, the best
 // (S / ||k_i||, slot) over the keys it sees, in increasing slot order, and the
 // 16 lanes that share a row settle the row at the end (equal values go to the
 // lower slot).  Scaling by 1 / ||k_j|| is left out: it does not change the
 // argmax.  Retained positions get -1.
+// Bound by issue and latency: per 64 products the VALU takes a multiply, a
+// compare and two selects (16 cycles of a SIMD) and the MFMAs 16, and staging a
+// key costs every block the same.  The products of the next 16 keys are issued
+// among the compares of the current ones, with one barrier per tile; the norm
+// is the hardware estimate with a Newton step, and row addresses are looked up
+// a tile ahead.  64 units of 32k tokens and 2048 keys: 1606 -> 1345 us (four row
+// tiles per wave, at one block per compute unit, 1570 us).
 // stats_kernel: one block per unit; loads by LDS atomics, then b, b_eff, A_max,
-// the Gini coefficient (exact integer sum of |a_i - a_j| over all pairs), and
-// the boundary-carrier figures.
+// the Gini coefficient (exact integer sum of |a_i - a_j| over all pairs: with
+// F(v) the number of loads <= v it is 2 sum_v F(v) (c - F(v)), from a histogram
+// of the loads and one scan; over the pairs themselves when a load reaches the
+// histogram's size), and the boundary-carrier figures.  With 64 units of 32k
+// tokens and 2048 slots: 147 -> 14 us.
 #include <math.h>
 
 #include "grkv_device.h"
@@ -24,76 +35,103 @@
 namespace grkv {
 namespace {
 
+// Sum over N (8 or 16) consecutive lanes, in every one of them.
+template <int N>
+__device__ __forceinline__ float row_sum(float v) {
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false));
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, false));
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, false));
+  if (N == 16)
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xF, 0xF, false));
+  return v;
+}
+
+// 1 / sqrt(ss), 0 for ss = 0 or infinite (ss scaled by a power of four where
+// the estimate would leave its normal range).
+__device__ __forceinline__ float inv_norm(float ss) {
+  const bool tiny = ss < 0x1p-100f;
+  const float x = tiny ? ss * 0x1p48f : ss;
+  float r = __builtin_amdgcn_rsqf(x);
+  r = fmaf(fmaf(-x * r, r, 1.f), 0.5f * r, r);
+  if (tiny) r *= 0x1p24f;
+  return ss > 0.f && ss < __builtin_huge_valf() ? r : 0.f;
+}
+
 constexpr int kMatchWaves = 8;
-constexpr int kMatchRows = 32 * kMatchWaves;   // cache positions per block
 constexpr int kRetTile = 64;                   // retained keys per LDS tile
 
-template <int D>
+// RT: 16-row tiles per wave
+template <int D, int RT>
 __global__ __launch_bounds__(kMatchWaves * 64) void match_kernel(
     const u16* __restrict__ K, const int32_t* __restrict__ idx, int64_t n, int c,
     int32_t* __restrict__ assign) {
   constexpr int NTH = kMatchWaves * 64;
   constexpr int KS = D + 8;                      // LDS row stride (bf16)
   constexpr int CH = kRetTile * D / 8;           // 16-byte chunks of a tile
-  constexpr int PER = (CH + NTH - 1) / NTH;
+  constexpr int PER = CH / NTH;
   constexpr int CPR = D / 8;                     // chunks per key row
+  constexpr int DS = D / 32, KT = kRetTile / 16;
+  static_assert(CH % NTH == 0 && (CPR == 8 || CPR == 16), "whole tiles, rows of 8 or 16 lanes");
   __shared__ __attribute__((aligned(16))) u16 kt_s[2][kRetTile * KS];
   __shared__ float inv_s[2][kRetTile];
   const int u = blockIdx.y, tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6, l16 = lane & 15, g = lane >> 4;
+  const int lane = tid & 63, l16 = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const u16* Ku = K + (size_t)u * n * D;
   const int32_t* iu = idx + (size_t)u * c;
-  const int64_t r0 = (int64_t)blockIdx.x * kMatchRows + 32 * wave;   // this wave's first row
+  const int64_t r0 = ((int64_t)blockIdx.x * kMatchWaves + wave) * (16 * RT);   // this wave's first row
 
   // query rows of this wave: rows r0 + 16 rt + l16, k = 32 ks + 8 g ..
-  uint4 qa[2][D / 32];
+  uint4 qa[RT][DS];
 #pragma unroll
-  for (int rt = 0; rt < 2; ++rt) {
+  for (int rt = 0; rt < RT; ++rt) {
     const int64_t r = min(r0 + 16 * rt + l16, n - 1);
 #pragma unroll
-    for (int ks = 0; ks < D / 32; ++ks)
+    for (int ks = 0; ks < DS; ++ks)
       qa[rt][ks] = *reinterpret_cast<const uint4*>(Ku + (size_t)r * D + ks * 32 + 8 * g);
   }
 
-  // register-staged retained tiles; chunk e of tile t: key t*64 + e / CPR
+  // register-staged retained tiles; chunk e of tile t: key t*64 + e / CPR.
+  // The source rows of a tile are looked up one tile before its keys.
   uint4 reg[PER];
-  auto load = [&](int t) {
+  uint32_t src[PER];
+  auto rows = [&](int t) {   // (past the last slot: the last slot's row)
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int e = min(tid + k * NTH, CH - 1);
-      const int slot = min(t * kRetTile + e / CPR, c - 1);
-      reg[k] = *reinterpret_cast<const uint4*>(Ku + (size_t)iu[slot] * D + (e % CPR) * 8);
-    }
+    for (int k = 0; k < PER; ++k)
+      src[k] = (uint32_t)iu[min(t * kRetTile + (tid + k * NTH) / CPR, c - 1)];
   };
-  auto store = [&](int t, int buf) {
+  auto load = [&]() {
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+      reg[k] = reinterpret_cast<const uint4*>(Ku)[(size_t)src[k] * CPR + tid % CPR];
+  };
+  auto store = [&](int t) {
+    const int buf = t & 1;
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
       const int e = tid + k * NTH;
       const int key = e / CPR, ch = e % CPR;
+      *reinterpret_cast<uint4*>(&kt_s[buf][key * KS + ch * 8]) = reg[k];
+      const uint32_t w4[4] = {reg[k].x, reg[k].y, reg[k].z, reg[k].w};
       float ss = 0.f;
-      if (e < CH) {
-        *reinterpret_cast<uint4*>(&kt_s[buf][key * KS + ch * 8]) = reg[k];
-        const uint32_t w4[4] = {reg[k].x, reg[k].y, reg[k].z, reg[k].w};
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const float a = __uint_as_float(w4[q] << 16), b = __uint_as_float(w4[q] & 0xffff0000u);
-          ss = fmaf(a, a, fmaf(b, b, ss));
-        }
+      for (int q = 0; q < 4; ++q) {
+        const float a = __uint_as_float(w4[q] << 16), b = __uint_as_float(w4[q] & 0xffff0000u);
+        ss = fmaf(a, a, fmaf(b, b, ss));
       }
       // the CPR chunks of a key sit in CPR consecutive lanes
-#pragma unroll
-      for (int off = 1; off < CPR; off <<= 1) ss += __shfl_xor(ss, off);
-      if (e < CH && ch == 0) {
-        const bool live = t * kRetTile + key < c;
-        inv_s[buf][key] = (live && ss > 0.f) ? 1.f / sqrtf(ss) : 0.f;
-      }
+      ss = row_sum<CPR>(ss);
+      // 1 / ||k||: the hardware estimate and one Newton step (within an ulp,
+      // as a division by the square root is, at a tenth of its instructions)
+      if (ch == 0)
+        inv_s[buf][key] = t * kRetTile + key >= c ? __builtin_nanf("") : inv_norm(ss);
     }
   };
 
-  float best[2][4];
-  int bslot[2][4];
+  float best[RT][4];
+  int bslot[RT][4];
 #pragma unroll
-  for (int rt = 0; rt < 2; ++rt)
+  for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       best[rt][i] = -__builtin_huge_valf();
@@ -101,42 +139,59 @@ __global__ __launch_bounds__(kMatchWaves * 64) void match_kernel(
     }
 
   const int ntiles = (c + kRetTile - 1) / kRetTile;
-  load(0);
-  store(0, 0);
+  rows(0);
+  load();
+  rows(1);
+  store(0);
+  load();
+  rows(2);
   for (int t = 0; t < ntiles; ++t) {
     const int buf = t & 1;
-    if (t + 1 < ntiles) load(t + 1);
-    __syncthreads();   // tile t is in LDS; tile t-1's buffer is no longer read
-#pragma unroll
-    for (int kt = 0; kt < kRetTile / 16; ++kt) {
+    __syncthreads();   // tile t is in LDS, and every wave is done with tile t - 1
+    store(t + 1);      // (past the last tile: never read)
+    load();
+    rows(t + 3);
+    // acc[rt]: rows r0 + 16rt + 4g + i, key 16kt + l16
+    auto products = [&](int kt, f32x4 (&acc)[RT], float& inv) {
       const int key = 16 * kt + l16;
-      f32x4 acc[2] = {zero4(), zero4()};
+      uint4 kb[DS];
 #pragma unroll
-      for (int ks = 0; ks < D / 32; ++ks) {
-        const bf16x8 kb = as_bf16x8(*reinterpret_cast<const uint4*>(&kt_s[buf][key * KS + ks * 32 + 8 * g]));
-        acc[0] = mfma_bf16(as_bf16x8(qa[0][ks]), kb, acc[0]);
-        acc[1] = mfma_bf16(as_bf16x8(qa[1][ks]), kb, acc[1]);
-      }
-      const int slot = t * kRetTile + key;
-      const float inv = inv_s[buf][key];
-      const bool live = slot < c;
+      for (int ks = 0; ks < DS; ++ks)
+        kb[ks] = *reinterpret_cast<const uint4*>(&kt_s[buf][key * KS + ks * 32 + 8 * g]);
+      inv = inv_s[buf][key];
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt)
+      for (int rt = 0; rt < RT; ++rt) acc[rt] = zero4();
+#pragma unroll
+      for (int ks = 0; ks < DS; ++ks)
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+          acc[rt] = mfma_bf16(as_bf16x8(qa[rt][ks]), as_bf16x8(kb[ks]), acc[rt]);
+    };
+    auto compare = [&](int kt, const f32x4 (&acc)[RT], float inv) {
+      const int slot = t * kRetTile + 16 * kt + l16;
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const float v = acc[rt][i] * inv;
-          if (live && v > best[rt][i]) {   // slots rise within a lane: a tie keeps the lower
-            best[rt][i] = v;
-            bslot[rt][i] = slot;
-          }
+          const bool up = v > best[rt][i];   // slots rise within a lane: a tie keeps the lower
+          best[rt][i] = up ? v : best[rt][i];
+          bslot[rt][i] = up ? slot : bslot[rt][i];
         }
+    };
+    f32x4 acc[2][RT];
+    float inv[2];
+    products(0, acc[0], inv[0]);
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) {
+      if (kt + 1 < KT) products(kt + 1, acc[(kt + 1) & 1], inv[(kt + 1) & 1]);
+      compare(kt, acc[kt & 1], inv[kt & 1]);
     }
-    if (t + 1 < ntiles) store(t + 1, buf ^ 1);
   }
 
   // settle each row over the 16 lanes holding it: larger value, then lower slot
 #pragma unroll
-  for (int rt = 0; rt < 2; ++rt)
+  for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       float v = best[rt][i];
@@ -174,15 +229,24 @@ __global__ __launch_bounds__(kStatsThreads) void stats_kernel(
     const int32_t* __restrict__ assign, const int32_t* __restrict__ idx, int64_t n, int c,
     int32_t* __restrict__ counts, float* __restrict__ metrics) {
   __shared__ int cnt[kMaxCarrierSlots];
+  __shared__ uint32_t hist[kMaxCarrierSlots];
+  __shared__ uint32_t scratch[16];
+  __shared__ int large;
   __shared__ unsigned long long red[16][6];
   const int u = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int32_t* iu = idx + (size_t)u * c;
   for (int i = tid; i < c; i += kStatsThreads) cnt[i] = 0;
   __syncthreads();
-  for (int64_t j = tid; j < n; j += kStatsThreads) {
-    const int a = assign[(size_t)u * n + j];
-    if (a >= 0 && a < c) atomicAdd(&cnt[a], 1);
+  for (int64_t j0 = tid; j0 < n; j0 += 16 * kStatsThreads) {   // sixteen loads in flight
+    int a[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) a[k] = assign[(size_t)u * n + min(j0 + k * kStatsThreads, n - 1)];
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+      if (j0 + k * kStatsThreads < n && a[k] >= 0 && a[k] < c) atomicAdd(&cnt[a[k]], 1);
   }
+  for (int i = tid; i < kMaxCarrierSlots; i += kStatsThreads) hist[i] = 0u;
+  if (tid == 0) large = 0;
   __syncthreads();
   // per thread: sum a, sum a^2, max a, active, boundary slots, boundary load,
   // and the pair sum of |a_i - a_j| over its rows i
@@ -200,10 +264,30 @@ __global__ __launch_bounds__(kStatsThreads) void stats_kernel(
       sb += a;
     }
     if (counts) counts[(size_t)u * c + i] = (int32_t)a;
-    for (int j = 0; j < c; ++j) {
-      const int dlt = cnt[i] - cnt[j];
-      pair += (unsigned long long)(dlt < 0 ? -dlt : dlt);
+    if (a < (unsigned long long)kMaxCarrierSlots) atomicAdd(&hist[a], 1u);
+    else large = 1;
+  }
+  __syncthreads();
+  if (!large) {   // (block-uniform)
+    constexpr int PER = kMaxCarrierSlots / kStatsThreads;
+    uint32_t h[PER], sum = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      h[k] = hist[tid * PER + k];
+      sum += h[k];
     }
+    uint32_t total, F = block_exclusive_scan(sum, scratch, &total);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      F += h[k];
+      pair += 2ull * F * (uint32_t)(c - (int)F);
+    }
+  } else {
+    for (int i = tid; i < c; i += kStatsThreads)
+      for (int j = 0; j < c; ++j) {
+        const int dlt = cnt[i] - cnt[j];
+        pair += (unsigned long long)(dlt < 0 ? -dlt : dlt);
+      }
   }
   unsigned long long v[6] = {s1, s2, act, nb, sb, pair};
   for (int off = 32; off > 0; off >>= 1) {
@@ -287,13 +371,22 @@ bool carrier_supported(int dtype, int d, int c) {
 hipError_t launch_carrier(const void* K, const int32_t* idx, int U, int64_t n, int c, int d,
                           const float* stats, int32_t* assign, int32_t* counts, float* metrics,
                           float* l_common, hipStream_t s) {
-  const dim3 grid((unsigned)((n + kMatchRows - 1) / kMatchRows), U);
-  if (d == 128)
-    hipLaunchKernelGGL(match_kernel<128>, grid, dim3(kMatchWaves * 64), 0, s, (const u16*)K, idx,
-                       n, c, assign);
-  else
-    hipLaunchKernelGGL(match_kernel<64>, grid, dim3(kMatchWaves * 64), 0, s, (const u16*)K, idx,
-                       n, c, assign);
+  // two row tiles per wave when that still gives two blocks per compute unit
+  // (which run side by side at 109 registers), else one
+  auto blocks = [&](int tiles) { return (n + 16 * tiles * kMatchWaves - 1) / (16 * tiles * kMatchWaves); };
+  const int rt = U * blocks(2) >= 512 ? 2 : 1;
+  const dim3 grid((unsigned)blocks(rt), U);
+#define GRKV_MATCH(DV, RTV)                                                                  \
+  hipLaunchKernelGGL((match_kernel<DV, RTV>), grid, dim3(kMatchWaves * 64), 0, s,            \
+                     (const u16*)K, idx, n, c, assign)
+  if (d == 128) {
+    if (rt == 2) GRKV_MATCH(128, 2);
+    else GRKV_MATCH(128, 1);
+  } else {
+    if (rt == 2) GRKV_MATCH(64, 2);
+    else GRKV_MATCH(64, 1);
+  }
+#undef GRKV_MATCH
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(stats_kernel, dim3(U), dim3(kStatsThreads), 0, s, assign, idx, n, c, counts,

@@ -116,3 +116,39 @@ def test_carrier_config4_sampled():
     assert np.all(gpu["counts"].sum(axis=1) == cfg.n - c)
     met = gpu["metrics"]
     assert np.all(met[:, 0] <= c) and np.all(met[:, 1] <= met[:, 0] + 1e-3)
+
+
+@pytest.mark.parametrize("units,n,c,d,kind", [
+    (256, 1000, 200, 128, "normal"),    # two row tiles per wave, a part-filled last key tile
+    (128, 1030, 64, 64, "normal"),      # the same at head dim 64, one whole key tile
+    (2, 20000, 130, 64, "one-carrier"), # a load past the histogram of loads
+    (2, 3000, 100, 128, "duplicates"),  # equal cosines go to the lower slot
+])
+def test_carrier_tiles_and_loads(units, n, c, d, kind):
+    import paper_2605_31105_amd as G
+    rng = np.random.default_rng(units + n)
+    K = rng.standard_normal((units, n, d)).astype(np.float32)
+    idx = np.sort(np.stack([rng.choice(n, c, replace=False) for _ in range(units)]), axis=1)
+    for u in range(units):
+        if kind == "one-carrier":
+            x = rng.standard_normal(d).astype(np.float32)
+            K[u] = x + 0.01 * K[u]
+            K[u, idx[u, 1:]] *= -1.0
+        elif kind == "duplicates":
+            K[u] = K[u][rng.integers(0, 7, n)]
+            K[u, idx[u, 50:60]] = 0.0
+    bits = W.f32_to_bf16_bits(K)
+    print("case", units, n, c, d, kind, flush=True)
+    a, cnt, met, _ = G.carrier_stats(to_device(bits, "bf16"),
+                                     torch.from_numpy(idx.astype(np.int32)).cuda(), 4)
+    torch.cuda.synchronize()
+    gpu = dict(idx=idx, assign=a.cpu().numpy(), counts=cnt.cpu().numpy(), metrics=met.cpu().numpy())
+    cfg = W.config(2, head_dim=d)
+    for u in (0, 1, units - 1):
+        print(_check_unit(cfg, bits, gpu, u), flush=True)
+        if kind == "duplicates":   # products of equal keys are equal bit for bit
+            keep = gpu["assign"][u] >= 0
+            assert np.array_equal(gpu["assign"][u][keep], CO.carrier_assignment(
+                W.decode(bits[u], "bf16"), idx[u])[keep])
+        if kind == "one-carrier":
+            assert gpu["counts"][u].max() >= 8192
