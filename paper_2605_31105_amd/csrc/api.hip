@@ -172,6 +172,8 @@ static void make_key_plan(const Plan& p, int steps, KeyPlan* kp) {
   kp->opart = take(U * Smax * mp * d * sizeof(float));
   kp->hpart = take(U * Smax * mp * sizeof(float));
   kp->cg = take(U * 4 * sizeof(double));
+  kp->cgpart = take(U * kCgBlocks * sizeof(double));
+  kp->cgcount = take(U * sizeof(int));
   const size_t later = steps > 1 ? 1 : 0;
   kp->q32 = take(later * U * p.m * d * sizeof(float));
   kp->v0f = take(later * U * p.c * d * sizeof(float));
@@ -511,6 +513,8 @@ int grkv_compress_kv(const void* q_obs, const void* K, const void* V, int64_t n,
   a.opart = F(kp.opart);
   a.hpart = F(kp.hpart);
   a.cg = (double*)(ws + kp.cg);
+  a.cgpart = (double*)(ws + kp.cgpart);
+  a.cgcount = (int*)(ws + kp.cgcount);
   a.kstar = k_star;
   a.cg_info = cg_info;
   a.lam_k = ko.lambda_k;

@@ -210,11 +210,13 @@ hipError_t launch_update_add(const Plan& p, const float* x, const uint8_t* fixed
 // state values (cg[u][3], reported in cg_info[u][2] as the GRKV_KEY_* codes).
 enum { kKeyRunning = 0, kKeyConverged = 1, kKeyMaxIter = 2, kKeySkipped = 3, kKeyBreakdown = 4 };
 
+constexpr int kCgBlocks = 16;   // blocks per unit of a separate CG update
+
 struct KeyPlan {
   int S4, chunk4;           // splits of the retained keys per unit, later CG iterations
   int S4r, chunk4r;         // the same for the ring passes (at most S4)
   int S_full, chunk_full;   // the same for the first iterations and the final pass
-  size_t Fm, alpha, r, p, sdot, W, opart, hpart, cg;   // offsets after Plan::total
+  size_t Fm, alpha, r, p, sdot, W, opart, hpart, cg, cgpart, cgcount;   // offsets after Plan::total
   // later alternating steps (steps > 1): fp32 copies of Q and V0, the compact
   // bf16 V0, X [U][mp][c] of the fp32 value step, the current keys
   size_t q32, v0f, v0c, x, kcur;
@@ -242,6 +244,8 @@ struct KeyArgs {
   float *Fm, *alpha, *r, *p, *W, *opart, *hpart;
   float* sdot;              // [U][mp] rowdot(F, p) of the current direction
   double* cg;               // [U][4] {r.r, r0.r0, iterations, state}
+  double* cgpart;           // [U][kCgBlocks] shares of p.Ap
+  int* cgcount;             // [U] blocks of the running CG update that are done
   float* kstar;             // [U][c][d] out
   float* cg_info;           // [U][4] out or null
   float lam_k, tol;

@@ -17,7 +17,7 @@
 //
 // Kernels: key_init (one block per unit: F, E, W, CG state), key_pass (the
 // operator, or the final J_G^T a, over the retained keys in splits), key_cg
-// (one block per unit: combines the split partials, one CG update).  The
+// (combines the split partials, one CG update).  The
 // host enqueues max_iter pairs of key_pass + key_cg; a unit that has converged
 // makes both return at once.
 //
@@ -75,7 +75,8 @@ __global__ __launch_bounds__(256) void key_init_kernel(
     const u16* __restrict__ q, const float* __restrict__ y, const float* __restrict__ zt,
     const float* __restrict__ stats_ws, float lam_v, int m, float* __restrict__ Fm,
     float* __restrict__ alpha, float* __restrict__ r, float* __restrict__ p,
-    float* __restrict__ sdot, float* __restrict__ W, double* __restrict__ cg) {
+    float* __restrict__ sdot, float* __restrict__ W, double* __restrict__ cg,
+    int* __restrict__ cgcount) {
   __shared__ double red[4];
   // E = lam_v Z and F = Y - E of this unit, rows padded by one float
   constexpr int ES = D + 1;
@@ -156,6 +157,7 @@ __global__ __launch_bounds__(256) void key_init_kernel(
     cg[u * 4 + 1] = ee;
     cg[u * 4 + 2] = 0;
     cg[u * 4 + 3] = skip ? kKeySkipped : ee == 0 ? kKeyConverged : kKeyRunning;
+    cgcount[u] = 0;
   }
 }
 
@@ -680,102 +682,145 @@ __global__ __launch_bounds__(1024) void key_rhs_kernel(
 // One conjugate-gradient update per unit: Ap = sum_s opart - (sum_s hpart) o F
 // + lambda_k p; alpha += a p; r -= a Ap; p = r + beta p; and the row dots
 // s = rowdot(F, p) of the new direction for the next operator pass.
+// The split partials are what it reads most (S of them, 64 KB each at m = 128,
+// d = 128), and a single compute unit reads some 60 GB/s: summed by one block
+// per unit, 26 splits took about 36 us per iteration.  So kCgBlocks blocks per
+// unit each sum a range of rows, leave Ap in place of split 0's partial (their
+// own rows of it) and their share of p . Ap in cgpart; the block that finishes
+// last (cgcount, which it sets back to zero) makes the update.  No block waits
+// for another.  One layer of 8 units at 3277 retained keys, the whole call:
+// 1368 -> 1176 us.
+constexpr int kCgTh = 256;
+constexpr int kCgLoads = 16;   // split partials a thread loads together
 
 template <int MP, int D>
-__global__ __launch_bounds__(1024) void key_cg_kernel(
-    const float* __restrict__ opart, const float* __restrict__ hpart, int S,
-    const float* __restrict__ Fm, float* __restrict__ alpha, float* __restrict__ r,
-    float* __restrict__ p, float* __restrict__ sdot, double* __restrict__ cg, float lam_k,
-    float tol, int max_iter) {
-  constexpr int NTH = 1024, E4 = MP * D / 4, PER = (E4 + NTH - 1) / NTH, RW = D / 4;
-  __shared__ float hsum[MP];
-  __shared__ double red[16];
-  const int u = blockIdx.x, tid = threadIdx.x;
+__global__ __launch_bounds__(kCgTh) void key_cg_kernel(
+    float* opart, const float* __restrict__ hpart, int S, const float* __restrict__ Fm,
+    float* alpha, float* r, float* p, float* sdot, double* cg, double* cgpart, int* cgcount,
+    float lam_k, float tol, int max_iter) {
+  constexpr int E4 = MP * D / 4, RW = D / 4;
+  constexpr int EB = E4 / kCgBlocks;                    // elements (float4) of a block
+  constexpr int PB = (EB + kCgTh - 1) / kCgTh;          // of a thread of it
+  constexpr int RB = MP / kCgBlocks;                    // rows of a block
+  static_assert(E4 % kCgBlocks == 0 && MP % kCgBlocks == 0 && EB == RB * RW, "whole rows per block");
+  __shared__ float hsum[RB];
+  __shared__ double red[kCgTh / 64];
+  __shared__ int last;
+  const int u = blockIdx.y, blk = blockIdx.x, tid = threadIdx.x;
   if ((int)cg[u * 4 + 3] != kKeyRunning) return;
-  // the split partials are loaded kCgBatch splits at a time (indices past S
+  // the split partials are loaded kCgLoads splits at a time (indices past S
   // read split S - 1, in bounds, and are not summed) and summed in split
   // order: the loads of a batch are in flight together
-  for (int i = tid; i < MP; i += NTH) {
+  if (tid < RB) {
     float h = 0.f;
-    for (int k0 = 0; k0 < S; k0 += kCgBatch) {
-      float hv[kCgBatch];
+    for (int k0 = 0; k0 < S; k0 += kCgLoads) {
+      float hv[kCgLoads];
 #pragma unroll
-      for (int j = 0; j < kCgBatch; ++j) hv[j] = hpart[((size_t)u * S + min(k0 + j, S - 1)) * MP + i];
+      for (int j = 0; j < kCgLoads; ++j)
+        hv[j] = hpart[((size_t)u * S + min(k0 + j, S - 1)) * MP + blk * RB + tid];
 #pragma unroll
-      for (int j = 0; j < kCgBatch; ++j)
+      for (int j = 0; j < kCgLoads; ++j)
         if (k0 + j < S) h += hv[j];
     }
-    hsum[i] = h;
+    hsum[tid] = h;
   }
-  __syncthreads();
   const size_t base = (size_t)u * E4;
-  const float4* __restrict__ op4 = reinterpret_cast<const float4*>(opart) + (size_t)u * S * E4;
+  float4* op4 = reinterpret_cast<float4*>(opart) + (size_t)u * S * E4;
   const float4* __restrict__ F4 = reinterpret_cast<const float4*>(Fm) + base;
-  float4* __restrict__ a4 = reinterpret_cast<float4*>(alpha) + base;
-  float4* __restrict__ r4 = reinterpret_cast<float4*>(r) + base;
-  float4* __restrict__ p4 = reinterpret_cast<float4*>(p) + base;
+  float4* a4 = reinterpret_cast<float4*>(alpha) + base;
+  float4* r4 = reinterpret_cast<float4*>(r) + base;
+  float4* p4 = reinterpret_cast<float4*>(p) + base;
   const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
-  float4 osum[PER];
+  float4 osum[PB];
 #pragma unroll
-  for (int k = 0; k < PER; ++k) osum[k] = z4;
-  for (int s0 = 0; s0 < S; s0 += kCgBatch) {
-    float4 ov[kCgBatch][PER];
+  for (int k = 0; k < PB; ++k) osum[k] = z4;
+  for (int s0 = 0; s0 < S; s0 += kCgLoads) {
+    float4 ov[kCgLoads][PB];
 #pragma unroll
-    for (int j = 0; j < kCgBatch; ++j)
+    for (int j = 0; j < kCgLoads; ++j)
 #pragma unroll
-      for (int k = 0; k < PER; ++k)
-        ov[j][k] = op4[(size_t)min(s0 + j, S - 1) * E4 + min(tid + k * NTH, E4 - 1)];
+      for (int k = 0; k < PB; ++k)
+        ov[j][k] = op4[(size_t)min(s0 + j, S - 1) * E4 + blk * EB + min(tid + k * kCgTh, EB - 1)];
 #pragma unroll
-    for (int j = 0; j < kCgBatch; ++j)
+    for (int j = 0; j < kCgLoads; ++j)
       if (s0 + j < S)
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
+        for (int k = 0; k < PB; ++k) {
           osum[k].x += ov[j][k].x; osum[k].y += ov[j][k].y;
           osum[k].z += ov[j][k].z; osum[k].w += ov[j][k].w;
         }
   }
-  float4 ap[PER], pp[PER], fv[PER];
+  __syncthreads();   // hsum
   double pap = 0;
 #pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int e = tid + k * NTH;
-    ap[k] = pp[k] = fv[k] = z4;
-    if (e < E4) {
+  for (int k = 0; k < PB; ++k) {
+    const int eb = tid + k * kCgTh, e = blk * EB + eb;
+    if (eb < EB) {
       float4 v = osum[k];
       const float4 pe = p4[e], f = F4[e];
-      const float h = hsum[e / RW];
+      const float h = hsum[eb / RW];
       v.x += lam_k * pe.x - h * f.x;
       v.y += lam_k * pe.y - h * f.y;
       v.z += lam_k * pe.z - h * f.z;
       v.w += lam_k * pe.w - h * f.w;
-      ap[k] = v;
-      pp[k] = pe;
-      fv[k] = f;
+      op4[e] = v;   // Ap (split 0's partial of these rows has been read by this thread)
       pap += (double)dot4(pe, v);
     }
   }
   pap = block_sum(pap, red);
+  // publish Ap and the share of p . Ap, then count in; the last block sees
+  // every other block's
+  if (tid == 0) cgpart[(size_t)u * kCgBlocks + blk] = pap;
+  __threadfence();
+  __syncthreads();
+  if (tid == 0) last = atomicAdd(&cgcount[u], 1) == kCgBlocks - 1;
+  __syncthreads();
+  if (!last) return;
+  __threadfence();
+  if (tid == 0) cgcount[u] = 0;
+
+  constexpr int PER = (E4 + kCgTh - 1) / kCgTh;
+  pap = 0;
+#pragma unroll
+  for (int k = 0; k < kCgBlocks; ++k) pap += cgpart[(size_t)u * kCgBlocks + k];
   const double rr = cg[u * 4 + 0], rr0 = cg[u * 4 + 1];
   const int it = (int)cg[u * 4 + 2] + 1;
+  __syncthreads();   // every thread has read cg
   if (!(pap > 0)) {
     if (tid == 0) cg[u * 4 + 3] = kKeyBreakdown;
     return;
   }
   const float a = (float)(rr / pap);
-  float4 rv[PER];
-  double rn = 0;
+  float4 rv[PER], pp[PER];
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
-    const int e = tid + k * NTH;
-    rv[k] = z4;
-    if (e < E4) {
-      float4 al = a4[e], re = r4[e];
-      al.x += a * pp[k].x; al.y += a * pp[k].y; al.z += a * pp[k].z; al.w += a * pp[k].w;
-      re.x -= a * ap[k].x; re.y -= a * ap[k].y; re.z -= a * ap[k].z; re.w -= a * ap[k].w;
-      a4[e] = al;
-      r4[e] = re;
-      rv[k] = re;
-      rn += (double)dot4(re, re);
+    const int e = min(tid + k * kCgTh, E4 - 1);
+    rv[k] = r4[e];
+    pp[k] = p4[e];
+  }
+  double rn = 0;
+  constexpr int HB = PER < 8 ? PER : 8;   // elements whose Ap and alpha are in flight together
+#pragma unroll
+  for (int k0 = 0; k0 < PER; k0 += HB) {
+    float4 ap[HB], al[HB];
+#pragma unroll
+    for (int k = 0; k < HB; ++k) {
+      const int e = min(tid + (k0 + k) * kCgTh, E4 - 1);
+      ap[k] = op4[e];
+      al[k] = a4[e];
+    }
+#pragma unroll
+    for (int k = 0; k < HB; ++k) {
+      const int e = tid + (k0 + k) * kCgTh;
+      float4& re = rv[k0 + k];
+      const float4 pe = pp[k0 + k];
+      if (e < E4) {
+        al[k].x += a * pe.x; al[k].y += a * pe.y; al[k].z += a * pe.z; al[k].w += a * pe.w;
+        re.x -= a * ap[k].x; re.y -= a * ap[k].y; re.z -= a * ap[k].z; re.w -= a * ap[k].w;
+        a4[e] = al[k];
+        r4[e] = re;
+        rn += (double)dot4(re, re);
+      }
     }
   }
   rn = block_sum(rn, red);
@@ -785,19 +830,26 @@ __global__ __launch_bounds__(1024) void key_cg_kernel(
   if (st == kKeyRunning) {
     const float beta = (float)(rn / rr);
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int e = tid + k * NTH;
-      float4 pn = z4;
-      if (e < E4) {
-        pn = make_float4(rv[k].x + beta * pp[k].x, rv[k].y + beta * pp[k].y,
-                         rv[k].z + beta * pp[k].z, rv[k].w + beta * pp[k].w);
-        p4[e] = pn;
-      }
-      // row dot over the RW consecutive threads of a row (whole rows only)
-      float sd = dot4(fv[k], pn);
+    for (int k0 = 0; k0 < PER; k0 += HB) {
+      float4 fv[HB];
 #pragma unroll
-      for (int off = 1; off < RW; off <<= 1) sd += __shfl_xor(sd, off);
-      if (e < E4 && (e % RW) == 0) sdot[(size_t)u * MP + e / RW] = sd;
+      for (int k = 0; k < HB; ++k) fv[k] = F4[min(tid + (k0 + k) * kCgTh, E4 - 1)];
+#pragma unroll
+      for (int k = 0; k < HB; ++k) {
+        const int e = tid + (k0 + k) * kCgTh;
+        const float4 re = rv[k0 + k], pe = pp[k0 + k];
+        float4 pn = z4;
+        if (e < E4) {
+          pn = make_float4(re.x + beta * pe.x, re.y + beta * pe.y, re.z + beta * pe.z,
+                           re.w + beta * pe.w);
+          p4[e] = pn;
+        }
+        // row dot over the RW consecutive threads of a row (whole rows only)
+        float sd = dot4(fv[k], pn);
+#pragma unroll
+        for (int off = 1; off < RW; off <<= 1) sd += __shfl_xor(sd, off);
+        if (e < E4 && (e % RW) == 0) sdot[(size_t)u * MP + e / RW] = sd;
+      }
     }
   }
   if (tid == 0) {
@@ -805,6 +857,14 @@ __global__ __launch_bounds__(1024) void key_cg_kernel(
     cg[u * 4 + 2] = it;
     cg[u * 4 + 3] = st;
   }
+}
+
+template <int MP, int D>
+hipError_t launch_cg(const Plan& p, const KeyArgs& a, int S, hipStream_t s) {
+  hipLaunchKernelGGL((key_cg_kernel<MP, D>), dim3(kCgBlocks, p.U), dim3(kCgTh), 0, s, a.opart,
+                     a.hpart, S, a.Fm, a.alpha, a.r, a.p, a.sdot, a.cg, a.cgpart, a.cgcount,
+                     a.lam_k, a.tol, a.max_iter);
+  return hipGetLastError();
 }
 
 template <int MP, int D, int KM, bool KF>
@@ -827,7 +887,7 @@ hipError_t launch_pass(const Plan& p, const KeyArgs& a, int S, int chunk, const 
 template <int MP, int D, bool KF>
 hipError_t launch_key_t(const Plan& p, const KeyPlan& kp, const KeyArgs& a, hipStream_t s) {
   hipLaunchKernelGGL((key_init_kernel<MP, D>), dim3(p.U), dim3(256), 0, s, a.q, a.y, a.zt,
-                     a.stats_ws, p.lam, p.m, a.Fm, a.alpha, a.r, a.p, a.sdot, a.W, a.cg);
+                     a.stats_ws, p.lam, p.m, a.Fm, a.alpha, a.r, a.p, a.sdot, a.W, a.cg, a.cgcount);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (!KF && a.vh) {
@@ -842,10 +902,7 @@ hipError_t launch_key_t(const Plan& p, const KeyPlan& kp, const KeyArgs& a, hipS
       e = launch_key_ring(p, a, false, S, chunk, a.p, fuse, s);
       if (e != hipSuccess) return e;
       if (!fuse) {
-        hipLaunchKernelGGL((key_cg_kernel<MP, D>), dim3(p.U), dim3(1024), 0, s, a.opart,
-                           a.hpart, S, a.Fm, a.alpha, a.r, a.p, a.sdot, a.cg, a.lam_k, a.tol,
-                           a.max_iter);
-        e = hipGetLastError();
+        e = launch_cg<MP, D>(p, a, S, s);
         if (e != hipSuccess) return e;
       }
     }
@@ -868,9 +925,7 @@ hipError_t launch_key_t(const Plan& p, const KeyPlan& kp, const KeyArgs& a, hipS
     const int S = early ? kp.S_full : kp.S4, chunk = early ? kp.chunk_full : kp.chunk4;
     e = launch_pass<MP, D, kOp, KF>(p, a, S, chunk, a.p, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((key_cg_kernel<MP, D>), dim3(p.U), dim3(1024), 0, s, a.opart, a.hpart,
-                       S, a.Fm, a.alpha, a.r, a.p, a.sdot, a.cg, a.lam_k, a.tol, a.max_iter);
-    e = hipGetLastError();
+    e = launch_cg<MP, D>(p, a, S, s);
     if (e != hipSuccess) return e;
   }
   return launch_pass<MP, D, kFinal, KF>(p, a, kp.S_full, kp.chunk_full, a.alpha, s);
