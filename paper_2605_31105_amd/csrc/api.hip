@@ -31,6 +31,34 @@ static void split_range(int64_t len, int64_t want, int64_t min_len, int* S, int*
   *S = (int)(len > 0 ? ceil_div(len, ch) : 1);
 }
 
+// The split count, down to 5/8 of split_range's, with which `units` such ranges
+// finish first when `slots` blocks run at a time: rounds of blocks, each as long
+// as its tiles plus kBlockTiles tiles' worth of prologue and epilogue.  A last
+// round that is nearly empty costs a whole one: 24 units of 32k tokens in 43
+// splits each (1032 blocks, 512 at a time) took pass B 107 us where 32 units
+// (1024 blocks) took 123, and 8 units of 20011 tokens with 160 rows ran 40
+// splits each (320 blocks, 256 at a time) as two rounds.
+static void split_rounds(int64_t len, int64_t want, int64_t min_len, int64_t units, int64_t slots,
+                         int* S, int* chunk) {
+  constexpr int64_t kBlockTiles = 10;
+  auto cost = [&](int s, int c) {
+    return ceil_div(units * s, slots) * (ceil_div(c, kKeyTile) + kBlockTiles);
+  };
+  split_range(len, want, min_len, S, chunk);
+  int64_t best = cost(*S, *chunk);
+  const int64_t most = *S;
+  for (int64_t w = most - 1; w >= 1 && 8 * w >= 5 * most; --w) {
+    int s, c;
+    split_range(len, w, min_len, &s, &c);
+    // (a change has to be worth 3%)
+    if (100 * cost(s, c) < 97 * best) {
+      best = cost(s, c);
+      *S = s;
+      *chunk = c;
+    }
+  }
+}
+
 static void layout_plan(Plan* p, size_t slots, size_t splits2, size_t splits3, size_t tab);
 
 int make_plan(const grkv_problem* prob, int64_t n, int32_t window, int32_t budget,
@@ -80,10 +108,12 @@ int make_plan(const grkv_problem* prob, int64_t n, int32_t window, int32_t budge
   if (const char* e = getenv("GRKV_TARGET_BLOCKS")) target = atoll(e);       // tuning experiments
   if (const char* e = getenv("GRKV_TARGET_RET_BLOCKS")) target_ret = atoll(e);
   const int64_t want = ceil_div(target, p->U);
-  split_range(n, want, 512, &p->S1, &p->chunk1);
+  // blocks that run at a time: pass B holds two blocks of up to four waves per
+  // compute unit or one of eight, the retained pass one
+  split_rounds(n, want, 512, p->U, p->waves == 8 ? 256 : 512, &p->S1, &p->chunk1);
   p->fast_merge = merge_fast_supported(*p);
   if (p->fast_merge) {
-    split_range(budget, ceil_div(target_ret, p->U), 128, &p->S2, &p->chunk2);
+    split_rounds(budget, ceil_div(target_ret, p->U), 128, p->U, 256, &p->S2, &p->chunk2);
     if (p->chunk2 > 4096) split_range(budget, ceil_div(budget, 4096), 128, &p->S2, &p->chunk2);
   } else {
     split_range(budget, want, 128, &p->S2, &p->chunk2);
@@ -154,11 +184,14 @@ static void make_key_plan(const Plan& p, int steps, KeyPlan* kp) {
   // about 256 blocks (one per compute unit) while every unit is iterating;
   // about 2048 later, when a unit's iteration spanning several compute units
   // keeps it short once only a few units are still converging
-  split_range(p.c, ceil_div(256, p.U), 64, &kp->S_full, &kp->chunk_full);
+  split_range(p.c, 256 / p.U, 64, &kp->S_full, &kp->chunk_full);
   split_range(p.c, ceil_div(2048, p.U), 64, &kp->S4, &kp->chunk4);
   // the ring passes' later iterations: about 1024 blocks (fewer partials for
-  // the separate CG update to combine, measured faster than 2048)
-  split_range(p.c, ceil_div(1024, p.U), 64, &kp->S4r, &kp->chunk4r);
+  // the separate CG update to combine, measured faster than 2048), at most 16
+  // per unit unless the first iterations have more (their blocks already fill
+  // the compute units)
+  const int64_t tail = std::min<int64_t>(ceil_div(1024, p.U), 16);
+  split_range(p.c, std::max<int64_t>(tail, kp->S_full), 64, &kp->S4r, &kp->chunk4r);
   const int Smax = kp->S4 > kp->S_full ? kp->S4 : kp->S_full;
   const size_t U = p.U, mp = p.mp, d = p.d;
   size_t off = p.total;
@@ -276,10 +309,14 @@ int run_compress(const Plan& p, const void* q_obs, const void* K, const void* V,
   auto pass_b = [&](const AttnPass& a) { return fast ? launch_stream(p, a, 1, s) : launch_prob_pass(p, a, s); };
   GRKV_STAGE(GRKV_STAGE_FULL_LSE, pass_a(full));
   // (the bf16 streaming pass B combines the split partials itself, unless a
-  // unit has so many splits that a kernel of its own does it faster)
+  // unit has so many splits that a kernel of its own does it faster: with 256
+  // rows too, where every block's own loop over 32 to 40 splits took most of
+  // pass B; with this and the split counts one layer of 8 units, 20011 tokens
+  // and 160 rows went from 458 to 340 us, 32 units of 128k tokens from 1841 to
+  // 1639 us)
   const bool pre = fast && p.fast_merge && p.S1 >= kPrecombineSplits;
-  full.lse_ready = pre;
-  if (!fast || pre)
+  full.lse_ready = fast && p.S1 >= kPrecombineSplits;
+  if (!fast || full.lse_ready)
     GRKV_STAGE(GRKV_STAGE_FULL_LSE_COMBINE,
                launch_lse_combine(p, full.pmax, full.psum, p.S1, Dd(p.lse1), F(p.lse1_log2), s));
   GRKV_STAGE(GRKV_STAGE_FULL_PROB, pass_b(full));
@@ -652,7 +689,28 @@ static int make_ragged_plan(const grkv_problem* prob, int64_t n, int32_t window,
   const int st = make_plan(prob, n, window, cmean, pool_kernel, lambda, opt, p);
   if (st != GRKV_OK) return st;
   if (!(stream_supported(*p) && p->fast_merge)) return GRKV_OK;
-  const int chunk = p->chunk2, spb = update_slots_per_block(*p, cmean);
+  // slots per retained-pass split and per update block: the mean budget's, or up
+  // to half as many more where the units' own block counts then take fewer
+  // rounds of 256 (one block per compute unit at a time)
+  auto block_len = [&](int len, int most) {
+    constexpr int64_t kBlockTiles = 10;
+    int best = len;
+    int64_t best_cost = 0;
+    for (int k = 0; k <= 4; ++k) {
+      const int l = (int)(ceil_div((int64_t)len * (8 + k), 8 * kKeyTile) * kKeyTile);
+      if (l > most) break;
+      int64_t blocks = 0;
+      for (int u = 0; u < U; ++u) blocks += (budgets[u] + l - 1) / l;
+      const int64_t cost = ceil_div(blocks, 256) * (l / kKeyTile + kBlockTiles);
+      if (k == 0 || 100 * cost < 97 * best_cost) {
+        best = l;
+        best_cost = cost;
+      }
+    }
+    return best;
+  };
+  const int chunk = p->chunk2 = p->chunk3 = block_len(p->chunk2, 4096);
+  const int spb = block_len(update_slots_per_block(*p, cmean), 4096);
   std::vector<int32_t> split_unit, upd_unit;
   tab->assign((size_t)8 * U, 0);
   int64_t off = 0;
