@@ -115,6 +115,14 @@ int make_plan(const grkv_problem* prob, int64_t n, int32_t window, int32_t budge
   if (p->fast_merge) {
     split_rounds(budget, ceil_div(target_ret, p->U), 128, p->U, 256, &p->S2, &p->chunk2);
     if (p->chunk2 > 4096) split_range(budget, ceil_div(budget, 4096), 128, &p->S2, &p->chunk2);
+  } else if (p->dtype == GRKV_F32) {
+    // The fp32 kernels hold one to eight waves per block and little else, and
+    // their key tiles are a serial chain, so a call with few units is split
+    // down to two tiles per block: at most 512 blocks
+    // (2 units of 1024 tokens, 32 rows: with the blocked solve 287 -> 95 us)
+    const int64_t want32 = std::max<int64_t>(512 / p->U, 1);
+    split_range(n, want32, 64, &p->S1, &p->chunk1);
+    split_range(budget, want32, 64, &p->S2, &p->chunk2);
   } else {
     split_range(budget, want, 128, &p->S2, &p->chunk2);
     if (p->chunk2 > 8192) split_range(budget, ceil_div(budget, 8192), 128, &p->S2, &p->chunk2);
@@ -123,7 +131,7 @@ int make_plan(const grkv_problem* prob, int64_t n, int32_t window, int32_t budge
   // to d / 16 blocks per unit (one per compute unit at most)
   p->csplit = 1;
   if (p->fast_merge && (size_t)p->U * (p->d / 16) <= 256) p->csplit = p->d / 16;
-  if (p->fast_merge) {
+  if (p->fast_merge || solve_supported(*p)) {   // (one split count for both in the solve)
     p->S3 = p->S2;
     p->chunk3 = p->chunk2;
   } else {
@@ -281,6 +289,35 @@ int check_pointers(const void* q_obs, const void* K, const void* V, const grkv_p
   return GRKV_OK;
 }
 
+// The solve of up to 128 rows outside the fast path: Y combined already, X V0
+// and Gram partials of S2 splits of the normalised X (no masses to divide by).
+hipError_t generic_solve(const Plan& p, char* ws, float* y, float* stats, hipStream_t s) {
+  auto F = [&](size_t o) { return (float*)(ws + o); };
+  Plan q = p;
+  q.csplit = 1;
+  q.rag = nullptr;
+  // several splits: summed by one launch over all units into resid and gram,
+  // which the solve reads element by element before it writes them
+  const float* xv = F(p.xvpart);
+  const float* np = F(p.npart);
+  int S = p.S2;
+  if (S > 2) {
+    const float* part[kCombineSegs] = {xv, np, nullptr, nullptr};
+    float* const outs[kCombineSegs] = {F(p.resid), F(p.gram), nullptr, nullptr};
+    const size_t per[kCombineSegs] = {(size_t)p.mp * p.d, (size_t)p.mp * p.mp, 0, 0};
+    const int Sc[kCombineSegs] = {S, S, 0, 0};
+    const hipError_t e = launch_combine_parts(p.U, Sc, part, outs, per, s);
+    if (e != hipSuccess) return e;
+    xv = F(p.resid);
+    np = F(p.gram);
+    S = 1;
+  }
+  return launch_solve(q, y, 1, S, xv, np, nullptr, nullptr, 0.f, nullptr, y, F(p.resid),
+                      F(p.gram), F(p.z), (uint16_t*)(ws + p.zhi), (uint16_t*)(ws + p.zlo),
+                      F(p.stats_ws), stats, (double*)(ws + p.zpart), nullptr, nullptr, nullptr,
+                      nullptr, nullptr, s);
+}
+
 // The launch sequence of one call (arguments already checked).
 int run_compress(const Plan& p, const void* q_obs, const void* K, const void* V, int64_t n,
                  hipStream_t s, const grkv_outputs* out, const float* ext_scores = nullptr) {
@@ -363,7 +400,8 @@ int run_compress(const Plan& p, const void* q_obs, const void* K, const void* V,
   // the generic value step needs X itself, which only the generic pass writes
   GRKV_STAGE(GRKV_STAGE_RET_PROB,
              fast_merge ? launch_stream(p, ret, 2, s) : launch_prob_pass(p, ret, s));
-  if (!fast_merge)
+  const bool small_solve = !fast_merge && solve_supported(p);
+  if (!fast_merge && !small_solve)
     GRKV_STAGE(GRKV_STAGE_RESID,
                launch_combine_rows(p, F(p.xvpart), p.S2, F(p.y), F(p.resid), s));
   // 4. value step: N, Cholesky solve for Z, V* = V0 + X_G^T Z
@@ -393,8 +431,8 @@ int run_compress(const Plan& p, const void* q_obs, const void* K, const void* V,
                              (const uint16_t*)(ws + p.zlo), F(p.stats_ws),
                              V, out->idx, out->v_out, Dd(p.zpart), out->stats, s));
   } else {
-    // 256 stacked rows: blocked MFMA factorisation (block-packed in LDS);
-    // otherwise the column-by-column one
+    // 256 stacked rows: blocked factorisation, block-packed in LDS; up to 128
+    // the solve of the fast path (on combined Y, plain X V0 and Gram partials)
     if (solve_big_supported(p)) {
       // the Gram partials summed over all units first (one wide launch, in
       // split order: the solve's own sum, spread over the GPU), into gram,
@@ -414,10 +452,10 @@ int run_compress(const Plan& p, const void* q_obs, const void* K, const void* V,
       GRKV_TRY(launch_solve_big(p, Np, S3, F(p.y), F(p.resid), F(p.gram), F(p.z), F(p.stats_ws),
                                 out->stats, s));
       GRKV_TRY(mark(GRKV_STAGE_SOLVE, 1));
+    } else if (small_solve) {
+      GRKV_STAGE(GRKV_STAGE_SOLVE, generic_solve(p, ws, F(p.y), out->stats, s));
     } else {
-      GRKV_STAGE(GRKV_STAGE_SOLVE, launch_cholesky_solve(p, F(p.npart), F(p.y), F(p.resid),
-                                                         F(p.gram), F(p.z), F(p.stats_ws),
-                                                         out->stats, s));
+      return GRKV_ERR_HIP;   // (every plan has one of the solves)
     }
     GRKV_STAGE(GRKV_STAGE_UPDATE,
                launch_update_gen(p, F(p.x), fixed, F(p.z), F(p.stats_ws), ws + p.v0c,
@@ -593,10 +631,8 @@ int grkv_compress_kv(const void* q_obs, const void* K, const void* V, int64_t n,
           launch_lse_combine(p32, r.pmax, r.psum, p.S2, (double*)(ws + p.lse2), F(p.lse2_log2),
                              s) != hipSuccess ||
           launch_prob_pass(p32, r, s) != hipSuccess ||
-          launch_combine_rows(p32, F(p.xvpart), p.S2, F(p.y), F(p.resid), s) != hipSuccess ||
           launch_gram(p32, x, fixed, F(p.npart), s) != hipSuccess ||
-          launch_cholesky_solve(p32, F(p.npart), F(p.y), F(p.resid), F(p.gram), F(p.z),
-                                F(p.stats_ws), out->stats, s) != hipSuccess ||
+          generic_solve(p32, ws, F(p.y), out->stats, s) != hipSuccess ||
           hipMemcpyAsync(out->v_out, v0f, vbytes, hipMemcpyDeviceToDevice, s) != hipSuccess ||
           launch_update_add(p32, x, fixed, F(p.z), F(p.stats_ws), out->v_out, s) != hipSuccess)
         return GRKV_ERR_HIP;

@@ -148,6 +148,9 @@ hipError_t launch_gather(const Plan& p, const void* K, const void* V,
 hipError_t launch_gram(const Plan& p, const float* x, const uint8_t* fixed,
                        float* npart, hipStream_t s);
 
+// Up to 128 rows: launch_solve applies (bf16 fast path, and the generic path
+// from combined Y and normalised X).
+bool solve_supported(const Plan& p);
 // Fast value step (bf16, mp <= 128): the solve combines the Y, X V0 and Gram
 // partials (writing y, resid and gram) and solves by blocked Cholesky; then
 // v_out = V0 + X_G^T Z is written in one pass from the compact V0 copy.
@@ -183,10 +186,6 @@ hipError_t launch_update(const Plan& p, const void* q, const void* k0,
 // Generic value step (any dtype, mp up to 256): Cholesky in LDS; the update
 // adds X_G^T Z into v_out, which the gather filled with V0.
 // Writes the per-unit stats to stats_ws (always) and stats_user (if not null).
-hipError_t launch_cholesky_solve(const Plan& p, const float* npart,
-                                 const float* y, const float* resid,
-                                 float* gram, float* z, float* stats_ws,
-                                 float* stats_user, hipStream_t s);
 // The same solve for mp = 256 (G * w in (128, 256]) with d 64 or 128: blocked
 // MFMA factorisation of N held block-packed in LDS, one 8-wave block per unit.
 // npart holds S3 Gram partials per unit; it may be gram itself when S3 is 1

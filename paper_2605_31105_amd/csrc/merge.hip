@@ -955,6 +955,8 @@ int update_slots_per_block(const Plan& p, int c) {
   return (spb + 31) / 32 * 32;
 }
 
+bool solve_supported(const Plan& p) { return p.mp <= 128 && (p.d == 64 || p.d == 128); }
+
 bool merge_fast_supported(const Plan& p) {
   return p.dtype == GRKV_BF16 && p.mp <= 128 && (p.d == 64 || p.d == 128);
 }

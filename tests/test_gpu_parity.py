@@ -320,3 +320,22 @@ def test_retained_mass_far_below_full_cache(fix_window, kv_heads):
     for rr in rep:
         print(rr, flush=True)
     assert np.all(gpu["stats"][:, 3] == 0)
+
+
+@pytest.mark.parametrize("label,over", [
+    ("m-128-d-128", dict(group=4, window=32, head_dim=128, n=3000, budget=500)),
+    ("m-96-many-splits", dict(group=3, window=32, n=2501, budget=1001)),
+    ("m-64-one-split", dict(group=2, window=32, head_dim=128, n=700, budget=64)),
+    ("m-256", dict(group=8, window=32, n=1500, budget=300)),
+    ("window-1", dict(group=1, window=1, n=999, budget=65)),
+    ("many-units", dict(layers=150, n=300, budget=70)),
+], ids=lambda v: v if isinstance(v, str) else "")
+def test_fp32_shapes(label, over):
+    # the fp32 split counts, and the solve on one, two and many summed partials
+    _full_check(W.config(1, **over), "fp32-" + label)
+
+
+def test_fp32_singular():
+    cfg = W.config(1, n=1024, budget=128, lam=0.0)
+    gpu = _full_check(cfg, "fp32-status-1", opt=O.Options(beta=1.0), beta=1.0)
+    assert np.all(gpu["stats"][:, 3] == O.STATUS_SINGULAR)
