@@ -130,7 +130,8 @@ int make_plan(const grkv_problem* prob, int64_t n, int32_t window, int32_t budge
   // calls with few units split the solve's right-hand-side columns over up
   // to d / 16 blocks per unit (one per compute unit at most)
   p->csplit = 1;
-  if (p->fast_merge && (size_t)p->U * (p->d / 16) <= 256) p->csplit = p->d / 16;
+  if ((p->fast_merge || solve_big_supported(*p)) && (size_t)p->U * (p->d / 16) <= 256)
+    p->csplit = p->d / 16;
   if (p->fast_merge || solve_supported(*p)) {   // (one split count for both in the solve)
     p->S3 = p->S2;
     p->chunk3 = p->chunk2;
@@ -139,6 +140,15 @@ int make_plan(const grkv_problem* prob, int64_t n, int32_t window, int32_t budge
   }
 
   layout_plan(p, (size_t)p->U * budget, (size_t)p->U * p->S2, (size_t)p->U * p->S3, 0);
+  if (p->dtype == GRKV_F32 && p->total > GRKV_NOALLOC_SCRATCH_BYTES) {
+    // the finer splits' partials would pass the fixed scratch of the
+    // non-allocating entry point: fewer splits (such a call is no small one)
+    split_range(n, want, 512, &p->S1, &p->chunk1);
+    split_range(budget, ceil_div(256, p->U), 256, &p->S2, &p->chunk2);
+    p->S3 = p->S2;
+    p->chunk3 = p->chunk2;
+    layout_plan(p, (size_t)p->U * budget, (size_t)p->U * p->S2, (size_t)p->U * p->S3, 0);
+  }
   return GRKV_OK;
 }
 
@@ -434,24 +444,9 @@ int run_compress(const Plan& p, const void* q_obs, const void* K, const void* V,
     // 256 stacked rows: blocked factorisation, block-packed in LDS; up to 128
     // the solve of the fast path (on combined Y, plain X V0 and Gram partials)
     if (solve_big_supported(p)) {
-      // the Gram partials summed over all units first (one wide launch, in
-      // split order: the solve's own sum, spread over the GPU), into gram,
-      // which the solve then reads and overwrites with N
-      const float* Np = F(p.npart);
-      int S3 = p.S3;
-      GRKV_TRY(mark(GRKV_STAGE_SOLVE, 0));
-      if (S3 > 1) {
-        const float* part[kCombineSegs] = {F(p.npart), nullptr, nullptr, nullptr};
-        float* const outs[kCombineSegs] = {F(p.gram), nullptr, nullptr, nullptr};
-        const size_t per[kCombineSegs] = {(size_t)p.mp * p.mp, 0, 0, 0};
-        const int Sc[kCombineSegs] = {p.S3, 0, 0, 0};
-        GRKV_TRY(launch_combine_parts(p.U, Sc, part, outs, per, s));
-        Np = F(p.gram);
-        S3 = 1;
-      }
-      GRKV_TRY(launch_solve_big(p, Np, S3, F(p.y), F(p.resid), F(p.gram), F(p.z), F(p.stats_ws),
-                                out->stats, s));
-      GRKV_TRY(mark(GRKV_STAGE_SOLVE, 1));
+      GRKV_STAGE(GRKV_STAGE_SOLVE,
+                 launch_solve_big(p, F(p.npart), p.S3, F(p.y), F(p.resid), F(p.gram), F(p.z),
+                                  F(p.stats_ws), out->stats, Dd(p.zpart), s));
     } else if (small_solve) {
       GRKV_STAGE(GRKV_STAGE_SOLVE, generic_solve(p, ws, F(p.y), out->stats, s));
     } else {
@@ -459,7 +454,7 @@ int run_compress(const Plan& p, const void* q_obs, const void* K, const void* V,
     }
     GRKV_STAGE(GRKV_STAGE_UPDATE,
                launch_update_gen(p, F(p.x), fixed, F(p.z), F(p.stats_ws), ws + p.v0c,
-                                 out->v_out, s));
+                                 out->v_out, Dd(p.zpart), out->stats, s));
   }
 #undef GRKV_STAGE
 #undef GRKV_TRY

@@ -112,8 +112,8 @@ constexpr int kUpdGenSlots = 32 * kUpdGenWaves;
 
 template <typename T, int MP, int D>
 __global__ __launch_bounds__(kUpdGenWaves * 64) void update_gen_kernel(
-    const float* x, const uint8_t* fixed, const float* z, const float* stats_ws, const T* v0c,
-    float* v_out, int m, int c) {
+    const float* x, const uint8_t* fixed, const float* z, float* stats_ws, const T* v0c,
+    float* v_out, int m, int c, const double* zpart, int csplit, float lam, float* stats_user) {
   constexpr int DT = D / 16;
   constexpr int ZS = MP + 8;   // LDS row stride (bf16) of Z^T rows
   constexpr int NTH = kUpdGenWaves * 64;
@@ -123,6 +123,16 @@ __global__ __launch_bounds__(kUpdGenWaves * 64) void update_gen_kernel(
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, g = lane >> 4;
   const bool singular = stats_ws[u * 4 + 3] != 0.f;   // block-uniform
   const uint8_t* fu = fixed + (size_t)u * c;
+  if (csplit > 1 && blockIdx.x == 0 && tid == 0) {
+    // D after = lambda^2 ||Z||^2 / ||Y||^2 from the solve blocks' column
+    // shares, summed in block order
+    double Z2 = 0.0;
+    for (int k = 0; k < csplit; ++k) Z2 += zpart[(size_t)u * kZParts + k];
+    const double Y2 = zpart[(size_t)u * kZParts + kZParts - 1], dn = Y2 > 0 ? Y2 : 1.0;
+    const float dafter = singular ? stats_ws[u * 4 + 1] : (float)((double)lam * lam * Z2 / dn);
+    stats_ws[u * 4 + 2] = dafter;
+    if (stats_user) stats_user[u * 4 + 2] = dafter;
+  }
 
   if (!singular) {
     // Z^T to bf16 hi/lo in LDS; a thread's loads of ZB elements are issued
@@ -250,23 +260,27 @@ __global__ __launch_bounds__(kUpdGenWaves * 64) void update_gen_kernel(
 
 template <typename T, int MP, int D>
 hipError_t launch_update_gen_t(const Plan& p, const float* x, const uint8_t* fixed, const float* z,
-                               const float* stats_ws, const void* v0c, float* v_out,
-                               hipStream_t s) {
+                               float* stats_ws, const void* v0c, float* v_out,
+                               const double* zpart, float* stats_user, hipStream_t s) {
   const dim3 grid((p.c + kUpdGenSlots - 1) / kUpdGenSlots, p.U);
   hipLaunchKernelGGL((update_gen_kernel<T, MP, D>), grid, dim3(kUpdGenWaves * 64), 0, s, x, fixed,
-                     z, stats_ws, (const T*)v0c, v_out, p.m, p.c);
+                     z, stats_ws, (const T*)v0c, v_out, p.m, p.c, zpart, p.csplit, p.lam,
+                     stats_user);
   return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_update_gen(const Plan& p, const float* x, const uint8_t* fixed, const float* z,
-                             const float* stats_ws, const void* v0c, float* v_out, hipStream_t s) {
+                             float* stats_ws, const void* v0c, float* v_out, const double* zpart,
+                             float* stats_user, hipStream_t s) {
 #define GRKV_UG(MPV, DV)                                                                      \
   if (p.mp == MPV && p.d == DV)                                                               \
     return p.dtype == GRKV_BF16                                                               \
-               ? launch_update_gen_t<u16, MPV, DV>(p, x, fixed, z, stats_ws, v0c, v_out, s)   \
-               : launch_update_gen_t<float, MPV, DV>(p, x, fixed, z, stats_ws, v0c, v_out, s);
+               ? launch_update_gen_t<u16, MPV, DV>(p, x, fixed, z, stats_ws, v0c, v_out, zpart, \
+                                                 stats_user, s)                              \
+               : launch_update_gen_t<float, MPV, DV>(p, x, fixed, z, stats_ws, v0c, v_out, zpart, \
+                                                   stats_user, s);
   GRKV_UG(32, 64) GRKV_UG(32, 128) GRKV_UG(64, 64) GRKV_UG(64, 128) GRKV_UG(128, 64)
   GRKV_UG(128, 128) GRKV_UG(256, 64) GRKV_UG(256, 128)
 #undef GRKV_UG

@@ -3,23 +3,34 @@
 // too large for the row-major LDS layout of the m <= 128 solve, too slow for
 // a column-by-column factorisation.
 //
-// One block of 8 waves per unit.  N's lower triangle is held in LDS as
-// 136 16 x 16 blocks (139 KB), block (I, J), J <= I, at index I(I+1)/2 + J,
-// each row-major with its four 16-byte chunks of row r rotated by r mod 4 so
-// that a wave's float4 reads of one chunk column fall on distinct banks.
-// The factorisation N = L L^T is the blocked right-looking one of the m <= 128
-// solve: for every 16-wide panel one wave factors the diagonal block and
-// inverts its factor, the blocks below become L_ip = A_ip L_pp^-T, and the
-// trailing lower blocks take A_ij -= L_ip L_jp^T, all on fp32 MFMA (16x16x4).
-// The right-hand sides R are read from global memory straight into registers
-// (16 columns per wave) for the forward and backward substitutions.
+// finish_gram sums the Gram partials of the stored X over all units with one
+// wide launch and completes N (lambda on the diagonal, padding rows and columns
+// as the identity); read by one block per unit, 2 MB of partials take longer
+// than the factorisation.
 //
-// Inputs are the generic value step's: the Gram partials npart [U][S3][mp][mp]
-// of the stored X (the caller sums them over all units with one wide launch
-// first and passes that sum, S3 = 1: read by one block per unit, 2 MB of
-// partials take longer than the factorisation), and Y and R = Y - X V0
-// combined [U][mp][D].  Outputs: the full N (gram), Z^T (z [U][D][mp]) and
-// the stats, as the generic solve.
+// solve_big: blocks of 16 waves.  N's lower triangle is held in LDS as 16 x 16
+// blocks, block (I, J), J <= I, at index I(I+1)/2 + J, each row-major with its
+// four 16-byte chunks of row r rotated by r mod 4 so that a wave's float4 reads
+// of one chunk column fall on distinct banks.  The factorisation N = L L^T is
+// the blocked right-looking one of the m <= 128 solve: for every 16-wide panel
+// one wave factors the diagonal block and inverts its factor, the blocks below
+// become L_ip = A_ip L_pp^-T, and the trailing lower blocks take
+// A_ij -= L_ip L_jp^T, all on fp32 MFMA (16x16x4).  The right-hand sides R are
+// read from global memory straight into registers (16 columns per wave) for
+// the forward and backward substitutions.
+// It is a serial chain of panels, then two of substitutions that keep the fp32
+// matrix units busy, so: only the NP panels that hold rows are touched (160 rows
+// are 10 of 16 panels: 60% of the chain, 40% of the substitution), 15 waves
+// share a panel's update while the 16th factors the next diagonal block, and in
+// calls with few units csplit blocks per unit each factor N and substitute
+// their share of the columns (one wave per SIMD instead of two).  The waves
+// without columns sum ||Y||^2 and ||R||^2 meanwhile.
+// Whole calls: 8 units of 160 rows 340 -> 251 us, 32 units of 256 rows 1639 ->
+// 1602 us.
+//
+// Inputs: the full N (gram), and Y and R = Y - X V0 combined [U][mp][D].
+// Outputs: Z^T (z [U][D][mp]) and the stats, as the generic solve (with
+// csplit > 1 D after is formed by the update from the blocks' ||Z||^2).
 #include "grkv_device.h"
 #include "grkv_internal.h"
 
@@ -27,11 +38,9 @@ namespace grkv {
 namespace {
 
 constexpr int kBigMP = 256;
-constexpr int kBigWaves = 8;
-constexpr int kBigNP = kBigMP / 16;                        // panels
-constexpr int kBigBlocks = kBigNP * (kBigNP + 1) / 2;      // lower 16 x 16 blocks
+constexpr int kBigWaves = 16;
 constexpr int kBigLS = 20;                                 // row stride of the inverted diagonal factors
-constexpr int kBigBatch = 8;                               // N elements loaded together per thread
+constexpr int kGramBatch = 4;                              // partials loaded together per thread
 
 __device__ __forceinline__ int blk_index(int I, int J) { return I * (I + 1) / 2 + J; }
 
@@ -107,75 +116,97 @@ __device__ __forceinline__ bool factor_diag_blk(const float* blk, float* inv, in
   return ok;
 }
 
-template <int D>
+// N of every unit from its S Gram partials: one float4 per thread, summed in
+// split order.
+__global__ __launch_bounds__(256) void finish_gram_kernel(const float4* __restrict__ part, int S,
+                                                          int m, float lam,
+                                                          float4* __restrict__ gram) {
+  constexpr int E = kBigMP * kBigMP / 4;
+  const int u = blockIdx.y, e = blockIdx.x * 256 + threadIdx.x;   // E is a multiple of 256
+  const float4* p = part + (size_t)u * S * E + e;
+  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+  int s0 = 0;
+  for (; s0 + kGramBatch <= S; s0 += kGramBatch) {
+    float4 t[kGramBatch];
+#pragma unroll
+    for (int k = 0; k < kGramBatch; ++k) t[k] = p[(size_t)(s0 + k) * E];
+#pragma unroll
+    for (int k = 0; k < kGramBatch; ++k) { v.x += t[k].x; v.y += t[k].y; v.z += t[k].z; v.w += t[k].w; }
+  }
+  for (; s0 < S; ++s0) {
+    const float4 t = p[(size_t)s0 * E];
+    v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
+  }
+  const int r = e / (kBigMP / 4), c0 = (e % (kBigMP / 4)) * 4;
+  float vv[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int c = c0 + k;
+    if (r >= m || c >= m) vv[k] = 0.f;
+    if (r == c) vv[k] += r < m ? lam : 1.f;
+  }
+  gram[(size_t)u * E + e] = make_float4(vv[0], vv[1], vv[2], vv[3]);
+}
+
+// The lower-triangle block t steps on in row order from (ii, jj).
+__device__ __forceinline__ void tri_advance(int t, int& ii, int& jj) {
+  jj += t;
+  while (jj > ii) {
+    jj -= ii + 1;
+    ++ii;
+  }
+}
+
+// NP: panels that hold the unit's m rows (m <= 16 NP)
+template <int D, int NP>
 __global__ __launch_bounds__(kBigWaves * 64) void solve_big_kernel(
-    const float* npart, int S3, const float* y, const float* resid, float* gram, float* z,
-    float* stats_ws, float* stats_user, int m, float lam) {
-  constexpr int MP = kBigMP, NP = kBigNP, NC = D / 16, NTH = kBigWaves * 64;
-  __shared__ __attribute__((aligned(16))) float A[kBigBlocks * 256];
+    const float* __restrict__ gram, const float* __restrict__ y, const float* __restrict__ resid,
+    float* __restrict__ z, float* __restrict__ stats_ws, float* __restrict__ stats_user,
+    double* __restrict__ zpart, int csplit, int m, float lam) {
+  constexpr int MP = kBigMP, NC = D / 16, NB = NP * (NP + 1) / 2;
+  constexpr int LB = (NB + kBigWaves - 1) / kBigWaves;   // blocks loaded per wave
+  static_assert(NC < kBigWaves, "waves without columns form the sums");
+  __shared__ __attribute__((aligned(16))) float A[NB * 256];
   __shared__ __attribute__((aligned(16))) float Li[NP * 16 * kBigLS];
   __shared__ double red[3][kBigWaves];
   __shared__ int fail;
 
-  const int u = blockIdx.x, tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6, l16 = lane & 15, g = lane >> 4;
+  const int u = blockIdx.x, cblk = blockIdx.y, tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
   if (tid == 0) fail = 0;
 
-  // 1. N = sum of the Gram partials + lambda I (padding rows and columns:
-  // identity), to LDS (lower blocks) and to gram (all of it).  A thread
-  // issues the loads of kBigBatch elements before it uses them (with one
-  // partial, the usual case, they are all in flight together).
+  // 1. N's lower blocks to LDS (lane 4r + q of a wave: chunk q of row r), all
+  // of a wave's loads in flight together
   {
-    constexpr int E = MP * MP / 4;
-    static_assert(E % (kBigBatch * NTH) == 0, "whole batches");
-    const float4* np = reinterpret_cast<const float4*>(npart) + (size_t)u * S3 * E;
-    float4* go = reinterpret_cast<float4*>(gram) + (size_t)u * E;
-    for (int e0 = tid; e0 < E; e0 += kBigBatch * NTH) {
-      float4 vb[kBigBatch];
+    const float* gu = gram + (size_t)u * MP * MP;
+    const int r = lane >> 2, q = lane & 3;
+    float4 v[LB];
+    int ii = 0, jj = 0;
+    tri_advance(wave, ii, jj);
 #pragma unroll
-      for (int b = 0; b < kBigBatch; ++b) vb[b] = np[e0 + b * NTH];
-      for (int s = 1; s < S3; ++s)   // in split order
-#pragma unroll
-        for (int b = 0; b < kBigBatch; ++b) {
-          const float4 t = np[(size_t)s * E + e0 + b * NTH];
-          vb[b].x += t.x; vb[b].y += t.y; vb[b].z += t.z; vb[b].w += t.w;
-        }
-#pragma unroll
-      for (int b = 0; b < kBigBatch; ++b) {
-        const int e = e0 + b * NTH;
-        const int r = e / (MP / 4), c0 = (e % (MP / 4)) * 4;
-        float vv[4] = {vb[b].x, vb[b].y, vb[b].z, vb[b].w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int c = c0 + k;
-          if (r >= m || c >= m) vv[k] = 0.f;
-          if (r == c) vv[k] += r < m ? lam : 1.f;
-        }
-        go[e] = make_float4(vv[0], vv[1], vv[2], vv[3]);
-        const int I = r >> 4, J = c0 >> 4;
-        if (J <= I)
-          *reinterpret_cast<float4*>(A + blk_index(I, J) * 256 + blk_chunk(r & 15, (c0 & 15) >> 2)) =
-              make_float4(vv[0], vv[1], vv[2], vv[3]);
-      }
+    for (int k = 0; k < LB; ++k) {
+      const int I = min(ii, NP - 1), J = min(jj, NP - 1);   // (past the last block: any block)
+      v[k] = *reinterpret_cast<const float4*>(gu + (size_t)(16 * I + r) * MP + 16 * J + 4 * q);
+      tri_advance(kBigWaves, ii, jj);
     }
+#pragma unroll
+    for (int k = 0; k < LB; ++k)
+      if (wave + k * kBigWaves < NB)
+        *reinterpret_cast<float4*>(A + (wave + k * kBigWaves) * 256 + blk_chunk(r, q)) = v[k];
   }
   __syncthreads();
 
   // 2. N = L L^T in place (lower blocks); L_pp^-1 into Li
-  auto tri = [](int t, int& ii, int& jj) {
-    ii = 0;
-    while ((ii + 1) * (ii + 2) / 2 <= t) ++ii;
-    jj = t - ii * (ii + 1) / 2;
-  };
   bool ok_local = true;
   for (int p = 0; p < NP; ++p) {
     if (p > 0) {
       // trailing update from panel q = p - 1 over blocks (p + ii, p + jj),
       // jj <= ii; tile 0, the next diagonal block, goes to wave 0 alone
       const int q = p - 1, T = NP - p, TA = T * (T + 1) / 2;
+      int ii = 0, jj = 0;
+      tri_advance(wave, ii, jj);
       for (int t = wave; t < (wave == 0 ? 1 : TA); t += kBigWaves - 1) {
-        int ii, jj;
-        tri(t, ii, jj);
         const int I = p + ii, J = p + jj;
         const float4 af = *reinterpret_cast<const float4*>(A + blk_index(I, q) * 256 + blk_chunk(l16, g));
         const float4 bf = *reinterpret_cast<const float4*>(A + blk_index(J, q) * 256 + blk_chunk(l16, g));
@@ -189,6 +220,7 @@ __global__ __launch_bounds__(kBigWaves * 64) void solve_big_kernel(
         acc = mfma_f32(-af.w, bf.w, acc);
 #pragma unroll
         for (int i = 0; i < 4; ++i) cb[blk_off(4 * g + i, l16)] = acc[i];
+        tri_advance(kBigWaves - 1, ii, jj);
       }
     }
     if (wave == 0) ok_local = factor_diag_blk(A + blk_index(p, p) * 256, Li + p * 16 * kBigLS, lane) && ok_local;
@@ -218,14 +250,14 @@ __global__ __launch_bounds__(kBigWaves * 64) void solve_big_kernel(
   // 3. forward and backward substitution, 16 right-hand-side columns per
   // wave; tile rows 16t + 4g + i, column c0 + l16 live in r[t][i]
   double sy = 0.0, sr = 0.0, sz = 0.0;
-  for (int cb = wave; cb < NC; cb += kBigWaves) {
-    const int c0 = cb * 16;
-    const float* ru = resid + (size_t)u * MP * D;
-    const float* yu = y + (size_t)u * MP * D;
-    // every row of the [MP][D] arrays is read (rows past m are in bounds)
-    // and masked afterwards: loads without branches stay in flight together.
-    // Row 16t + 4g + i of column c0 + l16 is the uniform row base of 16t + i
-    // plus one 32-bit lane offset.
+  const float* ru = resid + (size_t)u * MP * D;
+  const int tpb = NC / csplit;   // column tiles of this block
+  if (wave < tpb) {
+    const int c0 = (cblk * tpb + wave) * 16;
+    // every row of the tiles is read (rows past m are in bounds) and masked
+    // afterwards: loads without branches stay in flight together.  Row
+    // 16t + 4g + i of column c0 + l16 is the uniform row base of 16t + i plus
+    // one 32-bit lane offset.
     const uint32_t lo = (uint32_t)(4 * g * D + c0 + l16);
     f32x4 r[NP];
 #pragma unroll
@@ -235,12 +267,7 @@ __global__ __launch_bounds__(kBigWaves * 64) void solve_big_kernel(
 #pragma unroll
     for (int t = 0; t < NP; ++t)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const bool in = 16 * t + 4 * g + i < m;
-        const float rv = in ? r[t][i] : 0.f;
-        r[t][i] = rv;
-        sr += (double)rv * rv;
-      }
+      for (int i = 0; i < 4; ++i) r[t][i] = 16 * t + 4 * g + i < m ? r[t][i] : 0.f;
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
       const float4 lf = *reinterpret_cast<const float4*>(Li + (p * 16 + l16) * kBigLS + 4 * g);
@@ -274,30 +301,39 @@ __global__ __launch_bounds__(kBigWaves * 64) void solve_big_kernel(
     }
     float* zr = z + ((size_t)u * D + c0 + l16) * MP;
 #pragma unroll
-    for (int t = 0; t < NP; ++t) {
-      float zv[4];
+    for (int t = 0; t < MP / 16; ++t) {
+      float zv[4] = {0.f, 0.f, 0.f, 0.f};
+      if (t < NP) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = 16 * t + 4 * g + i;
-        zv[i] = ok && row < m ? r[t][i] : 0.f;
-        sz += (double)zv[i] * zv[i];
+        for (int i = 0; i < 4; ++i) {
+          const int row = 16 * t + 4 * g + i;
+          zv[i] = ok && row < m ? r[t < NP ? t : 0][i] : 0.f;
+          sz += (double)zv[i] * zv[i];
+        }
       }
       *reinterpret_cast<float4*>(zr + 16 * t + 4 * g) = make_float4(zv[0], zv[1], zv[2], zv[3]);
     }
-    // ||Y||^2 of these columns (after the substitution, whose registers are
-    // free again), all 64 loads in flight before the sum
-    float yv[NP][4];
+  } else if (cblk == 0) {
+    // ||Y||^2 and ||R||^2 over the m real rows, eight elements of each in
+    // flight per thread
+    const float4* yu4 = reinterpret_cast<const float4*>(y + (size_t)u * MP * D);
+    const float4* ru4 = reinterpret_cast<const float4*>(ru);
+    const int n4 = m * (D / 4), nth = (kBigWaves - tpb) * 64;
+    for (int e0 = tid - tpb * 64; e0 < n4; e0 += 8 * nth) {
+      float4 a[8], b[8];
 #pragma unroll
-    for (int t = 0; t < NP; ++t)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) yv[t][i] = (yu + (16 * t + i) * D)[lo];
-#pragma unroll
-    for (int t = 0; t < NP; ++t)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float yy = 16 * t + 4 * g + i < m ? yv[t][i] : 0.f;
-        sy += (double)yy * yy;
+      for (int k = 0; k < 8; ++k) {
+        const int e = min(e0 + k * nth, n4 - 1);
+        a[k] = yu4[e];
+        b[k] = ru4[e];
       }
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        if (e0 + k * nth >= n4) break;
+        sy += (double)a[k].x * a[k].x + (double)a[k].y * a[k].y + (double)a[k].z * a[k].z + (double)a[k].w * a[k].w;
+        sr += (double)b[k].x * b[k].x + (double)b[k].y * b[k].y + (double)b[k].z * b[k].z + (double)b[k].w * b[k].w;
+      }
+    }
   }
 
   // 4. stats: ||Y||^2, D before = ||R||^2 / ||Y||^2, D after = lambda^2 ||Z||^2 / ||Y||^2
@@ -311,16 +347,30 @@ __global__ __launch_bounds__(kBigWaves * 64) void solve_big_kernel(
   if (tid == 0) {
     double Y2 = 0, R2 = 0, Z2 = 0;
     for (int k = 0; k < kBigWaves; ++k) { Y2 += red[0][k]; R2 += red[1][k]; Z2 += red[2][k]; }
+    if (csplit > 1) zpart[(size_t)u * kZParts + cblk] = Z2;
+    if (cblk != 0) return;
+    if (csplit > 1) zpart[(size_t)u * kZParts + kZParts - 1] = Y2;
     const double dn = Y2 > 0 ? Y2 : 1.0;
     const double dbefore = R2 / dn;
     const double dafter = ok ? (double)lam * lam * Z2 / dn : dbefore;
     const float st[4] = {(float)Y2, (float)dbefore, (float)dafter,
                          ok ? (float)GRKV_UNIT_OK : (float)GRKV_UNIT_SINGULAR};
     for (int k = 0; k < 4; ++k) {
+      if (csplit > 1 && k == 2) continue;   // D after: formed by the update
       stats_ws[u * 4 + k] = st[k];
       if (stats_user) stats_user[u * 4 + k] = st[k];
     }
   }
+}
+
+template <int D, int NP>
+hipError_t launch_solve_big_t(const Plan& p, const float* y, const float* resid, const float* gram,
+                              float* z, float* stats_ws, float* stats_user, double* zpart,
+                              hipStream_t s) {
+  if ((D / 16) % p.csplit != 0) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((solve_big_kernel<D, NP>), dim3(p.U, p.csplit), dim3(kBigWaves * 64), 0, s,
+                     gram, y, resid, z, stats_ws, stats_user, zpart, p.csplit, p.m, p.lam);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -329,16 +379,21 @@ bool solve_big_supported(const Plan& p) { return p.mp == kBigMP && (p.d == 64 ||
 
 hipError_t launch_solve_big(const Plan& p, const float* npart, int S3, const float* y,
                             const float* resid, float* gram, float* z, float* stats_ws,
-                            float* stats_user, hipStream_t s) {
-  if (!solve_big_supported(p) || S3 < 1) return hipErrorInvalidValue;
-  if (npart == gram && S3 != 1) return hipErrorInvalidValue;
-  if (p.d == 128)
-    hipLaunchKernelGGL(solve_big_kernel<128>, dim3(p.U), dim3(kBigWaves * 64), 0, s, npart, S3,
-                       y, resid, gram, z, stats_ws, stats_user, p.m, p.lam);
-  else
-    hipLaunchKernelGGL(solve_big_kernel<64>, dim3(p.U), dim3(kBigWaves * 64), 0, s, npart, S3,
-                       y, resid, gram, z, stats_ws, stats_user, p.m, p.lam);
-  return hipGetLastError();
+                            float* stats_user, double* zpart, hipStream_t s) {
+  if (!solve_big_supported(p) || S3 < 1 || p.m > kBigMP || p.csplit < 1 || p.csplit > kZParts - 1)
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(finish_gram_kernel, dim3(kBigMP * kBigMP / 4 / 256, p.U), dim3(256), 0, s,
+                     reinterpret_cast<const float4*>(npart), S3, p.m, p.lam,
+                     reinterpret_cast<float4*>(gram));
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+#define GRKV_BIG(DV, NPV)                                                                      \
+  if (p.d == DV && p.m <= 16 * NPV)                                                            \
+    return launch_solve_big_t<DV, NPV>(p, y, resid, gram, z, stats_ws, stats_user, zpart, s);
+  GRKV_BIG(64, 10) GRKV_BIG(64, 12) GRKV_BIG(64, 14) GRKV_BIG(64, 16)
+  GRKV_BIG(128, 10) GRKV_BIG(128, 12) GRKV_BIG(128, 14) GRKV_BIG(128, 16)
+#undef GRKV_BIG
+  return hipErrorInvalidValue;
 }
 
 }  // namespace grkv

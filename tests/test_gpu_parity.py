@@ -339,3 +339,23 @@ def test_fp32_singular():
     cfg = W.config(1, n=1024, budget=128, lam=0.0)
     gpu = _full_check(cfg, "fp32-status-1", opt=O.Options(beta=1.0), beta=1.0)
     assert np.all(gpu["stats"][:, 3] == O.STATUS_SINGULAR)
+
+
+@pytest.mark.parametrize("group,head_dim,kv_heads", [(5, 128, 2), (5, 64, 2), (6, 128, 2), (7, 64, 2),
+                                                     (7, 128, 2), (8, 64, 2), (5, 128, 40)])
+def test_rows_past_128(group, head_dim, kv_heads):
+    # 160 to 256 rows: 10 to 16 panels in the solve, its columns split over
+    # blocks (2 units) and not (40).  (n = 400 at 40 units holds a unit with
+    # D_before = 2.7e-4: the 2^-12 relative rounding of Y bounds its relative
+    # error there by 2 * 2^-12 / sqrt(2.7e-4) = 3e-2, so the 2e-3 bar says
+    # nothing about it; at n = 1500 every D_before is above 2.5e-2.)
+    cfg = W.config(2, layers=1, kv_heads=kv_heads, group=group, head_dim=head_dim, n=1500,
+                   budget=300)
+    _full_check(cfg, "rows-%d" % cfg.m)
+
+
+def test_rows_past_128_singular():
+    cfg = W.config(2, layers=1, kv_heads=2, group=5, n=1024, budget=256, lam=0.0)
+    gpu = _full_check(cfg, "rows-160-status-1", opt=O.Options(beta=1.0), beta=1.0)
+    assert np.all(gpu["stats"][:, 3] == O.STATUS_SINGULAR)
+    assert np.array_equal(gpu["stats"][:, 2], gpu["stats"][:, 1])
