@@ -65,6 +65,8 @@ constexpr uint32_t kBandCap = 1024;
 //     sum recomputed in fp64 from the fp32 column sums, then by position (as
 //     the register kernel's refine_boundary does); a band of more than
 //     kBandCap keys keeps the fp32 order with ties to the lower positions;
+//  (prefixes of at most 131072 positions do 2 and 3, and the marking of 4, in
+//  one sweep when the sampled first brackets hold: one_sweep)
 //  4. per segment of 131072 positions: the taken positions are marked in an
 //     LDS bitmap (keys above the band, band entries taken, ties taken), and
 //     one block scan over the bitmap words writes them in ascending order.
@@ -93,6 +95,11 @@ struct KthWork {
   uint32_t sh[4];
   uint32_t ncand[2];
   uint32_t cand[2][kLargeCand];
+  // one_sweep: positions of the candidates, counts at or above the upper
+  // bounds; the smallest and largest key
+  int32_t cpos[2][kLargeCand];
+  uint32_t above[2];
+  uint32_t kmin, kmax;
 };
 
 struct Search {
@@ -101,10 +108,16 @@ struct Search {
   __device__ __forceinline__ bool wide() const { return on && hi - lo > 1 && clo - chi > kLargeCand; }
 };
 
-__device__ __forceinline__ uint32_t wave_sum_u(uint32_t v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += (uint32_t)__shfl_xor((int)v, off);
-  return v;
+// Sum over the 64 lanes of a wave, in every lane (DPP within 16-lane rows,
+// then the four row totals).
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
+  int x = (int)v;
+  x += __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x141, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x140, 0xF, 0xF, false);
+  return (uint32_t)(__builtin_amdgcn_readlane(x, 0) + __builtin_amdgcn_readlane(x, 16) +
+                    __builtin_amdgcn_readlane(x, 32) + __builtin_amdgcn_readlane(x, 48));
 }
 
 // Radix rounds over the candidates of one search (8-bit offsets in the bracket).
@@ -170,14 +183,15 @@ __device__ void radix_finish(Search& b, const uint32_t* cand, uint32_t L, KthWor
 // registers; the samples about 4 sqrt(r) + 16 ranks either side of rank
 // r = k / stride bound T, found by one joint bisection of the four order
 // statistics (counts of two of them packed per word, one barrier per step).
-// One sweep then counts the keys at or above both bounds of both searches
-// exactly; a bracket is taken only when it provably holds T
-// (count(>= lo) >= k > count(>= hi)), so a poor sample costs that sweep and
-// the searches start from the full range as before.
+// Exact counts decide whether a bracket is taken: it must provably hold T
+// (count(>= lo) >= k > count(>= hi)), so a poor sample costs a sweep and the
+// searches start from the full range.
 constexpr int kSample = 2 * kLargeCand;
 constexpr int kSamplePer = kSample / kSelectThreads;
+constexpr uint32_t kSampleSlack = 4096;   // 2^-11 relative: far inside the ranks' width
 
-__device__ void sampled_bracket(const float* p, int P, Search (&b)[2], KthWork& wk) {
+__device__ void sample_bounds(const float* p, int P, const Search (&b)[2], KthWork& wk,
+                              uint32_t (&lo)[2], uint32_t (&hi)[2], bool (&try_)[2]) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   constexpr int NW = kSelectThreads / 64;
   static_assert(kSample % kSelectThreads == 0 && kSample < 65536, "packed 16-bit counts");
@@ -194,8 +208,6 @@ __device__ void sampled_bracket(const float* p, int P, Search (&b)[2], KthWork& 
   // targets 2t (rank jh: the bound above T) and 2t + 1 (rank jl: below T)
   int J[4];
   bool act[4];
-  uint32_t lo[2], hi[2];
-  bool try_[2];
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     lo[t] = b[t].lo;
@@ -210,16 +222,17 @@ __device__ void sampled_bracket(const float* p, int P, Search (&b)[2], KthWork& 
     try_[t] = act[2 * t] || act[2 * t + 1];
   }
   // the J-th largest sample (0-based) is the largest x with count(>= x) > J:
-  // L keeps count(>= L) > J, H count(>= H) <= J (key 0 counts every sample)
+  // L keeps count(>= L) > J, H count(>= H) <= J, from the key range down to
+  // kSampleSlack units in the last place (each bound kept on its safe side)
   uint32_t L[4], H[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) { L[i] = 0u; H[i] = 0x7F800001u; }
+  for (int i = 0; i < 4; ++i) { L[i] = b[i >> 1].lo; H[i] = b[i >> 1].hi; }
   int parity = 0;
 #pragma unroll 1
   for (int it = 0; it < 32; ++it) {
     bool more = false;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) more |= act[i] && H[i] - L[i] > 1;
+    for (int i = 0; i < 4; ++i) more |= act[i] && H[i] - L[i] > kSampleSlack;
     if (!more) break;   // uniform
     uint32_t mid[4];
 #pragma unroll
@@ -230,8 +243,8 @@ __device__ void sampled_bracket(const float* p, int P, Search (&b)[2], KthWork& 
       c01 += (uint32_t)(sv[m] >= mid[0]) + ((uint32_t)(sv[m] >= mid[1]) << 16);
       c23 += (uint32_t)(sv[m] >= mid[2]) + ((uint32_t)(sv[m] >= mid[3]) << 16);
     }
-    c01 = wave_sum_u(c01);
-    c23 = wave_sum_u(c23);
+    c01 = wave_sum(c01);
+    c23 = wave_sum(c23);
     if (lane == 0) { wk.part[wave][2 * parity] = c01; wk.part[wave][2 * parity + 1] = c23; }
     __syncthreads();
     uint32_t t01 = 0, t23 = 0;
@@ -241,18 +254,28 @@ __device__ void sampled_bracket(const float* p, int P, Search (&b)[2], KthWork& 
     const uint32_t cnt[4] = {t01 & 0xFFFFu, t01 >> 16, t23 & 0xFFFFu, t23 >> 16};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      if (!(act[i] && H[i] - L[i] > 1)) continue;
+      if (!(act[i] && H[i] - L[i] > kSampleSlack)) continue;
       if (cnt[i] > (uint32_t)J[i]) L[i] = mid[i];
       else H[i] = mid[i];
     }
   }
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
-    if (act[2 * t]) hi[t] = __builtin_amdgcn_readfirstlane(L[2 * t]);
+    if (act[2 * t]) hi[t] = __builtin_amdgcn_readfirstlane(H[2 * t]);
     if (act[2 * t + 1]) lo[t] = __builtin_amdgcn_readfirstlane(L[2 * t + 1]);
     if (!(lo[t] < hi[t])) try_[t] = false;
   }
   __syncthreads();   // the last step's words are read before part is reused
+}
+
+// The bounds as brackets of both searches, where one sweep's exact counts
+// confirm them.
+__device__ void sampled_bracket(const float* p, int P, Search (&b)[2], KthWork& wk) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int NW = kSelectThreads / 64;
+  uint32_t lo[2], hi[2];
+  bool try_[2];
+  sample_bounds(p, P, b, wk, lo, hi, try_);
   if (!try_[0] && !try_[1]) return;
   uint32_t cl[2] = {0u, 0u}, ch[2] = {0u, 0u};
   for (int j0 = tid; j0 < P; j0 += kLoadBatch * kSelectThreads) {
@@ -270,7 +293,7 @@ __device__ void sampled_bracket(const float* p, int P, Search (&b)[2], KthWork& 
   }
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
-    const uint32_t x = wave_sum_u(cl[t]), y = wave_sum_u(ch[t]);
+    const uint32_t x = wave_sum(cl[t]), y = wave_sum(ch[t]);
     if (lane == 0) { wk.part[wave][2 * t] = x; wk.part[wave][2 * t + 1] = y; }
   }
   __syncthreads();
@@ -328,7 +351,7 @@ __device__ void kth_pair(const float* p, int P, Search (&b)[2], KthWork& wk) {
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int w = 0; w < kWays - 1; ++w) {
-        const uint32_t v = wave_sum_u(cnt[t][w]);
+        const uint32_t v = wave_sum(cnt[t][w]);
         if (lane == 0) wk.part[wave][t * kWays + w] = v;
       }
     __syncthreads();
@@ -409,10 +432,140 @@ __device__ __forceinline__ uint32_t band_hi(uint32_t T) {
   return T < 0x7F800000u - kBandUlps ? T + kBandUlps : 0x7F800000u;
 }
 
+// Both thresholds, their bands and the taken positions from one sweep over the
+// pooled scores (a prefix of at most kSegBits positions).  With the sampled
+// bounds [lo, hi) of each search, the sweep marks the keys at or above hi in
+// bits[t] (a wave's 64 positions are two whole words, written by one lane) and
+// appends the keys inside, with their positions, to wk (one LDS atomic per wave
+// and batch).  The counts confirm the bracket; radix rounds on the candidates
+// give T; the band around T then lies among the candidates, and the candidates
+// above it are marked.  Returns false, with nothing kept, when a bracket is
+// not confirmed, its candidates do not fit, or a band reaches past it or is
+// too large (the caller's general sweeps then run).  The general sweeps read
+// the scores four more times, and what one compute unit can read bounds this
+// kernel: 32 units of 131008 scores 231 -> about 170 us.
+__device__ bool one_sweep(const float* p, int P, Search (&b)[2], KthWork& wk, BandSet (&band)[2],
+                          uint32_t (&bits)[3][kSegWords], uint32_t* cnt_sh) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  uint32_t lo[2], hi[2];
+  bool try_[2];
+  sample_bounds(p, P, b, wk, lo, hi, try_);
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    // a narrow search keeps its own bounds (its keys fit); a wide one needs
+    // the sample's
+    if (b[t].on && b[t].wide() && !try_[t]) return false;   // (block-uniform)
+    if (!b[t].on) lo[t] = hi[t] = 0xFFFFFFFFu;              // nothing marked, nothing inside
+  }
+  if (tid < 2) { wk.ncand[tid] = 0u; cnt_sh[tid] = 0u; }
+  for (int w = tid; w < 3 * kSegWords; w += kSelectThreads) (&bits[0][0])[w] = 0u;
+  __syncthreads();
+  uint32_t above[2] = {0u, 0u};   // of this wave, in every lane
+  for (int j0 = tid; j0 - lane < P; j0 += kLoadBatch * kSelectThreads) {   // wave-uniform count
+    uint32_t kk[kLoadBatch];
+    load_strided(p, j0, P, kk);
+    uint32_t in[2] = {0u, 0u};   // bit q: key q inside bracket t
+#pragma unroll
+    for (int q = 0; q < kLoadBatch; ++q) {
+      const int j = j0 + q * kSelectThreads;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const uint64_t m = __ballot(j < P && kk[q] >= hi[t]);
+        above[t] += (uint32_t)__builtin_popcountll(m);
+        if (lane == 0 && j < P)
+          *reinterpret_cast<uint64_t*>(&bits[t][j >> 5]) = m;   // j is a multiple of 64
+        in[t] |= (uint32_t)(j < P && kk[q] - lo[t] < hi[t] - lo[t]) << q;
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      if (__ballot(in[t] != 0u) == 0ull) continue;
+      const uint32_t cnt = __builtin_popcount(in[t]);
+      uint32_t incl = cnt;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t x = (uint32_t)__shfl_up((int)incl, off);
+        if (lane >= off) incl += x;
+      }
+      const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+      uint32_t base = 0u;
+      if (lane == 0) base = atomicAdd(&wk.ncand[t], tot);
+      uint32_t o = (uint32_t)__builtin_amdgcn_readfirstlane((int)base) + incl - cnt;
+      uint32_t m = in[t];
+      while (m) {   // (few keys: read again)
+        const int j = j0 + __builtin_ctz(m) * kSelectThreads;
+        m &= m - 1;
+        const uint32_t x = __float_as_uint(p[j]);
+        if (o < kLargeCand) { wk.cand[t][o] = x; wk.cpos[t][o] = j; }
+        ++o;
+      }
+    }
+  }
+  if (lane == 0) {
+    if (above[0]) atomicAdd(&cnt_sh[0], above[0]);
+    if (above[1]) atomicAdd(&cnt_sh[1], above[1]);
+  }
+  __syncthreads();
+  uint32_t nc[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    nc[t] = wk.ncand[t];
+    const uint32_t chi = cnt_sh[t], clo = chi + nc[t];
+    if (!b[t].on) continue;
+    if (nc[t] > kLargeCand || clo < b[t].k || chi >= b[t].k) return false;   // (block-uniform)
+    b[t].lo = __builtin_amdgcn_readfirstlane(lo[t]);
+    b[t].hi = __builtin_amdgcn_readfirstlane(hi[t]);
+    b[t].clo = __builtin_amdgcn_readfirstlane(clo);
+    b[t].chi = __builtin_amdgcn_readfirstlane(chi);
+  }
+  if (tid < 2) wk.above[tid] = cnt_sh[tid];
+  __syncthreads();   // the counts are read before cnt_sh is reused
+  if (b[0].on && b[0].hi - b[0].lo > 1) radix_finish(b[0], wk.cand[0], nc[0], wk);
+  if (b[1].on && b[1].hi - b[1].lo > 1) radix_finish(b[1], wk.cand[1], nc[1], wk);
+  // the bands, from the candidates
+  bool fits = true;
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+    if (b[t].on) {
+      // (no key lies below the smallest or above the largest: a band may reach
+      // past a bound that is the key range's own)
+      fits &= band_lo(b[t].lo) >= lo[t] || lo[t] <= wk.kmin;
+      fits &= band_hi(b[t].lo) < hi[t] || hi[t] > wk.kmax;
+    }
+  if (!fits) return false;   // (block-uniform)
+  if (tid < 2) { band[tid].n = 0u; cnt_sh[2 * tid] = 0u; cnt_sh[2 * tid + 1] = 0u; }
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    if (!b[t].on) continue;
+    const uint32_t T = b[t].lo, blo = band_lo(T), bhi = band_hi(T);
+    for (uint32_t e = tid; e < nc[t]; e += kSelectThreads) {
+      const uint32_t x = wk.cand[t][e];
+      const int j = wk.cpos[t][e];
+      if (x > T) atomicAdd(&cnt_sh[2 * t + 1], 1u);
+      if (x > bhi) {
+        atomicAdd(&cnt_sh[2 * t], 1u);
+        atomicOr(&bits[t][j >> 5], 1u << (j & 31));
+      } else if (x >= blo) {
+        const uint32_t o = atomicAdd(&band[t].n, 1u);
+        if (o < kBandCap) band[t].pos[o] = j;
+      }
+    }
+  }
+  __syncthreads();
+  const bool big = (b[0].on && band[0].n > kBandCap) || (b[1].on && band[1].n > kBandCap);
+  if (big) return false;   // (block-uniform)
+  // counts above the band and above T, with the keys at or above hi
+  if (tid < 4) cnt_sh[tid] += tid < 2 ? wk.above[0] : wk.above[1];
+  __syncthreads();
+  return true;
+}
+
 __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelK a) {
   __shared__ BandSet band[2];
   __shared__ KthWork wk;
-  __shared__ uint32_t bits[3][kSegWords];   // taken (T0), taken (T1), ties at T (big band)
+  __shared__ __attribute__((aligned(16))) uint32_t bits[3][kSegWords];   // taken (T0), taken (T1), ties at T (big band)
   __shared__ uint32_t scan_scratch[16];
   __shared__ uint32_t mm[2][kSelectThreads / 64];
   __shared__ uint32_t cnt_sh[4];
@@ -507,15 +660,24 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelK a) {
   Search b[2];
   b[0] = {(uint32_t)us.s_sel, kmin, kmax + 1, (uint32_t)P, 0u, any[0]};
   b[1] = {(uint32_t)us.n_top, kmin, kmax + 1, (uint32_t)P, 0u, any[1]};
-  kth_pair(p, P, b, wk);
+  const Search b0[2] = {b[0], b[1]};
+  if (tid == 0) { wk.kmin = kmin; wk.kmax = kmax; }
+  __syncthreads();   // (also: pooling's stage, on bits, is no longer read)
+  const bool single = P <= kSegBits && one_sweep(p, P, b, wk, band, bits, cnt_sh);
+  if (!single) {
+    __syncthreads();
+    b[0] = b0[0];
+    b[1] = b0[1];
+    kth_pair(p, P, b, wk);
+  }
   const uint32_t T[2] = {b[0].lo, b[1].lo};
   const uint32_t lo[2] = {band_lo(T[0]), band_lo(T[1])}, hi[2] = {band_hi(T[0]), band_hi(T[1])};
   const uint32_t kk_[2] = {(uint32_t)us.s_sel, (uint32_t)us.n_top};
 
   // 3. the boundary bands: entries (unordered), counts above the band and above T
-  if (tid < 2) { band[tid].n = 0u; cnt_sh[2 * tid] = 0u; cnt_sh[2 * tid + 1] = 0u; }
-  __syncthreads();
-  {
+  if (!single) {
+    if (tid < 2) { band[tid].n = 0u; cnt_sh[2 * tid] = 0u; cnt_sh[2 * tid + 1] = 0u; }
+    __syncthreads();
     uint32_t nab[2] = {0u, 0u}, ngt[2] = {0u, 0u};
     for (int j0 = tid; j0 < P; j0 += kLoadBatch * kSelectThreads) {
       uint32_t kk[kLoadBatch];
@@ -538,7 +700,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelK a) {
     }
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      const uint32_t x = wave_sum_u(nab[t]), y = wave_sum_u(ngt[t]);
+      const uint32_t x = wave_sum(nab[t]), y = wave_sum(ngt[t]);
       if (lane == 0) { atomicAdd(&cnt_sh[2 * t], x); atomicAdd(&cnt_sh[2 * t + 1], y); }
     }
   }
@@ -594,12 +756,14 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelK a) {
   for (int seg0 = 0; seg0 < P; seg0 += kSegBits) {
     const int seg1 = min(P, seg0 + kSegBits);
     __syncthreads();
-    for (int wd = tid; wd < 3 * kSegWords; wd += kSelectThreads) (&bits[0][0])[wd] = 0u;
+    if (!single)
+      for (int wd = tid; wd < 3 * kSegWords; wd += kSelectThreads) (&bits[0][0])[wd] = 0u;
     __syncthreads();
     for (int t = 0; t < 2; ++t) {
       if (!any[t]) continue;
-      // keys above the band (or, for a big band, above T; ties marked apart)
-      for (int j0 = seg0 + tid; j0 < seg1; j0 += kLoadBatch * kSelectThreads) {
+      // keys above the band (or, for a big band, above T; ties marked apart),
+      // unless one_sweep has marked them
+      for (int j0 = seg0 + tid; !single && j0 < seg1; j0 += kLoadBatch * kSelectThreads) {
         uint32_t kk[kLoadBatch];
         load_strided(p, j0, seg1, kk);
 #pragma unroll
@@ -685,18 +849,6 @@ constexpr uint32_t kCandCap = 4096;    // candidates finished by one wave (64 pe
 // A value known to be the same in every lane, kept in a scalar register.
 __device__ __forceinline__ uint32_t uniform_u(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
-}
-
-// Sum over the 64 lanes of a wave, in every lane (DPP within 16-lane rows,
-// then the four row totals).
-__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
-  int x = (int)v;
-  x += __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, false);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, false);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x141, 0xF, 0xF, false);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x140, 0xF, 0xF, false);
-  return (uint32_t)(__builtin_amdgcn_readlane(x, 0) + __builtin_amdgcn_readlane(x, 16) +
-                    __builtin_amdgcn_readlane(x, 32) + __builtin_amdgcn_readlane(x, 48));
 }
 
 // Block-wide sum of one value per thread; `part` holds 2 x 16 words and
