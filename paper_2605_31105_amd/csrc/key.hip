@@ -70,14 +70,16 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
 }
 
 // ------------------------------------------------------------------ init ----
+constexpr int kInitTh = 1024;
+
 template <int MP, int D>
-__global__ __launch_bounds__(256) void key_init_kernel(
+__global__ __launch_bounds__(kInitTh) void key_init_kernel(
     const u16* __restrict__ q, const float* __restrict__ y, const float* __restrict__ zt,
     const float* __restrict__ stats_ws, float lam_v, int m, float* __restrict__ Fm,
     float* __restrict__ alpha, float* __restrict__ r, float* __restrict__ p,
     float* __restrict__ sdot, float* __restrict__ W, double* __restrict__ cg,
     int* __restrict__ cgcount) {
-  __shared__ double red[4];
+  __shared__ double red[kInitTh / 64];
   // E = lam_v Z and F = Y - E of this unit, rows padded by one float
   constexpr int ES = D + 1;
   __shared__ float Es[MP * ES], Fs[MP * ES];
@@ -88,26 +90,27 @@ __global__ __launch_bounds__(256) void key_init_kernel(
   // thread loads kInitBatch elements before it uses them; every row of the
   // [mp]-row arrays is read (in bounds) and rows past m are masked.
   constexpr int NE = MP * D;
-  static_assert(NE % (256 * kInitBatch) == 0, "whole batches");
-  for (int e0 = tid; e0 < NE; e0 += 256 * kInitBatch) {
-    float zv[kInitBatch];
+  constexpr int IB = NE / kInitTh < kInitBatch ? NE / kInitTh : kInitBatch;
+  static_assert(IB >= 1 && NE % (kInitTh * IB) == 0, "whole batches");
+  for (int e0 = tid; e0 < NE; e0 += kInitTh * IB) {
+    float zv[IB];
 #pragma unroll
-    for (int b = 0; b < kInitBatch; ++b) zv[b] = zt[(size_t)u * D * MP + e0 + 256 * b];
+    for (int b = 0; b < IB; ++b) zv[b] = zt[(size_t)u * D * MP + e0 + kInitTh * b];
 #pragma unroll
-    for (int b = 0; b < kInitBatch; ++b) {
-      const int e = e0 + 256 * b, col = e / MP, row = e % MP;
+    for (int b = 0; b < IB; ++b) {
+      const int e = e0 + kInitTh * b, col = e / MP, row = e % MP;
       Es[row * ES + col] = (!skip && row < m) ? lam_v * zv[b] : 0.f;
     }
   }
   __syncthreads();
   double ee = 0;
-  for (int e0 = tid; e0 < NE; e0 += 256 * kInitBatch) {
-    float yv[kInitBatch];
+  for (int e0 = tid; e0 < NE; e0 += kInitTh * IB) {
+    float yv[IB];
 #pragma unroll
-    for (int b = 0; b < kInitBatch; ++b) yv[b] = y[(size_t)u * MP * D + e0 + 256 * b];
+    for (int b = 0; b < IB; ++b) yv[b] = y[(size_t)u * MP * D + e0 + kInitTh * b];
 #pragma unroll
-    for (int b = 0; b < kInitBatch; ++b) {
-      const int e = e0 + 256 * b, row = e / D, col = e % D;
+    for (int b = 0; b < IB; ++b) {
+      const int e = e0 + kInitTh * b, row = e / D, col = e % D;
       const size_t o = (size_t)u * MP * D + e;
       const float E = Es[row * ES + col];
       const float F = row < m ? yv[b] - E : 0.f;
@@ -122,7 +125,7 @@ __global__ __launch_bounds__(256) void key_init_kernel(
   __syncthreads();
   // s = rowdot(F, p) for the first direction p = E, summed over the columns
   // in order (one thread per row, from LDS)
-  for (int row = tid; row < MP; row += 256) {
+  for (int row = tid; row < MP; row += kInitTh) {
     float acc = 0.f;
     if (!skip && row < m)
       for (int col = 0; col < D; ++col) acc += Fs[row * ES + col] * Es[row * ES + col];
@@ -130,7 +133,7 @@ __global__ __launch_bounds__(256) void key_init_kernel(
   }
   // W = Q Q^T / d (bf16 products are exact; fp32 sums)
   const u16* qu = q + (size_t)u * m * D;
-  for (int t = wave; t < (MP / 16) * (MP / 16); t += 4) {
+  for (int t = wave; t < (MP / 16) * (MP / 16); t += kInitTh / 64) {
     const int ta = t / (MP / 16), tb = t % (MP / 16);
     const int ra = ta * 16 + l16, rb = tb * 16 + l16;
     f32x4 acc = zero4();
@@ -690,8 +693,8 @@ __global__ __launch_bounds__(1024) void key_rhs_kernel(
 // last (cgcount, which it sets back to zero) makes the update.  No block waits
 // for another.  One layer of 8 units at 3277 retained keys, the whole call:
 // 1368 -> 1176 us.
-constexpr int kCgTh = 256;
-constexpr int kCgLoads = 16;   // split partials a thread loads together
+constexpr int kCgTh = 1024;
+constexpr int kCgLoads = 8;    // split partials a thread loads together
 
 template <int MP, int D>
 __global__ __launch_bounds__(kCgTh) void key_cg_kernel(
@@ -700,17 +703,39 @@ __global__ __launch_bounds__(kCgTh) void key_cg_kernel(
     float lam_k, float tol, int max_iter) {
   constexpr int E4 = MP * D / 4, RW = D / 4;
   constexpr int EB = E4 / kCgBlocks;                    // elements (float4) of a block
-  constexpr int PB = (EB + kCgTh - 1) / kCgTh;          // of a thread of it
+  constexpr int SG = kCgTh / EB;                        // threads per element: split classes
   constexpr int RB = MP / kCgBlocks;                    // rows of a block
-  static_assert(E4 % kCgBlocks == 0 && MP % kCgBlocks == 0 && EB == RB * RW, "whole rows per block");
+  static_assert(E4 % kCgBlocks == 0 && MP % kCgBlocks == 0 && EB == RB * RW && SG >= 1 && SG * EB == kCgTh, "whole rows per block");
   __shared__ float hsum[RB];
+  __shared__ float4 psum[kCgTh];
   __shared__ double red[kCgTh / 64];
   __shared__ int last;
   const int u = blockIdx.y, blk = blockIdx.x, tid = threadIdx.x;
   if ((int)cg[u * 4 + 3] != kKeyRunning) return;
-  // the split partials are loaded kCgLoads splits at a time (indices past S
-  // read split S - 1, in bounds, and are not summed) and summed in split
-  // order: the loads of a batch are in flight together
+  const size_t base = (size_t)u * E4;
+  float4* op4 = reinterpret_cast<float4*>(opart) + (size_t)u * S * E4;
+  const float4* __restrict__ F4 = reinterpret_cast<const float4*>(Fm) + base;
+  float4* a4 = reinterpret_cast<float4*>(alpha) + base;
+  float4* r4 = reinterpret_cast<float4*>(r) + base;
+  float4* p4 = reinterpret_cast<float4*>(p) + base;
+  const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
+  // thread (class sg, element eb) sums the partials of splits sg, sg + SG, ...
+  // in order, kCgLoads loads in flight together (splits past the last read the
+  // last one, in bounds, and are not summed); the classes are then summed in
+  // order from LDS
+  const int sg = tid / EB, eb = tid % EB, e0 = blk * EB + eb;
+  {
+    float4 acc = z4;
+    for (int s0 = sg; s0 < S; s0 += SG * kCgLoads) {
+      float4 ov[kCgLoads];
+#pragma unroll
+      for (int j = 0; j < kCgLoads; ++j) ov[j] = op4[(size_t)min(s0 + j * SG, S - 1) * E4 + e0];
+#pragma unroll
+      for (int j = 0; j < kCgLoads; ++j)
+        if (s0 + j * SG < S) { acc.x += ov[j].x; acc.y += ov[j].y; acc.z += ov[j].z; acc.w += ov[j].w; }
+    }
+    psum[tid] = acc;
+  }
   if (tid < RB) {
     float h = 0.f;
     for (int k0 = 0; k0 < S; k0 += kCgLoads) {
@@ -724,59 +749,40 @@ __global__ __launch_bounds__(kCgTh) void key_cg_kernel(
     }
     hsum[tid] = h;
   }
-  const size_t base = (size_t)u * E4;
-  float4* op4 = reinterpret_cast<float4*>(opart) + (size_t)u * S * E4;
-  const float4* __restrict__ F4 = reinterpret_cast<const float4*>(Fm) + base;
-  float4* a4 = reinterpret_cast<float4*>(alpha) + base;
-  float4* r4 = reinterpret_cast<float4*>(r) + base;
-  float4* p4 = reinterpret_cast<float4*>(p) + base;
-  const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
-  float4 osum[PB];
-#pragma unroll
-  for (int k = 0; k < PB; ++k) osum[k] = z4;
-  for (int s0 = 0; s0 < S; s0 += kCgLoads) {
-    float4 ov[kCgLoads][PB];
-#pragma unroll
-    for (int j = 0; j < kCgLoads; ++j)
-#pragma unroll
-      for (int k = 0; k < PB; ++k)
-        ov[j][k] = op4[(size_t)min(s0 + j, S - 1) * E4 + blk * EB + min(tid + k * kCgTh, EB - 1)];
-#pragma unroll
-    for (int j = 0; j < kCgLoads; ++j)
-      if (s0 + j < S)
-#pragma unroll
-        for (int k = 0; k < PB; ++k) {
-          osum[k].x += ov[j][k].x; osum[k].y += ov[j][k].y;
-          osum[k].z += ov[j][k].z; osum[k].w += ov[j][k].w;
-        }
-  }
-  __syncthreads();   // hsum
+  __syncthreads();
   double pap = 0;
+  if (tid < EB) {
+    float4 v = psum[tid];
 #pragma unroll
-  for (int k = 0; k < PB; ++k) {
-    const int eb = tid + k * kCgTh, e = blk * EB + eb;
-    if (eb < EB) {
-      float4 v = osum[k];
-      const float4 pe = p4[e], f = F4[e];
-      const float h = hsum[eb / RW];
-      v.x += lam_k * pe.x - h * f.x;
-      v.y += lam_k * pe.y - h * f.y;
-      v.z += lam_k * pe.z - h * f.z;
-      v.w += lam_k * pe.w - h * f.w;
-      op4[e] = v;   // Ap (split 0's partial of these rows has been read by this thread)
-      pap += (double)dot4(pe, v);
+    for (int k = 1; k < SG; ++k) {
+      const float4 t = psum[k * EB + tid];
+      v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
     }
+    const float4 pe = p4[e0], f = F4[e0];
+    const float h = hsum[eb / RW];
+    v.x += lam_k * pe.x - h * f.x;
+    v.y += lam_k * pe.y - h * f.y;
+    v.z += lam_k * pe.z - h * f.z;
+    v.w += lam_k * pe.w - h * f.w;
+    op4[e0] = v;   // Ap (the block has read split 0's partial of these elements)
+    pap = (double)dot4(pe, v);
   }
   pap = block_sum(pap, red);
   // publish Ap and the share of p . Ap, then count in; the last block sees
   // every other block's
-  if (tid == 0) cgpart[(size_t)u * kCgBlocks + blk] = pap;
-  __threadfence();
+  // (one thread releases for the block, after the barrier: a release at device
+  // scope writes the compute die's dirty cache lines back, and one by each wave
+  // of the block costs more than the sums)
   __syncthreads();
-  if (tid == 0) last = atomicAdd(&cgcount[u], 1) == kCgBlocks - 1;
+  if (tid == 0) {
+    cgpart[(size_t)u * kCgBlocks + blk] = pap;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    last = __hip_atomic_fetch_add(&cgcount[u], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+           kCgBlocks - 1;
+  }
   __syncthreads();
   if (!last) return;
-  __threadfence();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   if (tid == 0) cgcount[u] = 0;
 
   constexpr int PER = (E4 + kCgTh - 1) / kCgTh;
@@ -886,7 +892,7 @@ hipError_t launch_pass(const Plan& p, const KeyArgs& a, int S, int chunk, const 
 
 template <int MP, int D, bool KF>
 hipError_t launch_key_t(const Plan& p, const KeyPlan& kp, const KeyArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL((key_init_kernel<MP, D>), dim3(p.U), dim3(256), 0, s, a.q, a.y, a.zt,
+  hipLaunchKernelGGL((key_init_kernel<MP, D>), dim3(p.U), dim3(kInitTh), 0, s, a.q, a.y, a.zt,
                      a.stats_ws, p.lam, p.m, a.Fm, a.alpha, a.r, a.p, a.sdot, a.W, a.cg, a.cgcount);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
