@@ -31,31 +31,39 @@ static void split_range(int64_t len, int64_t want, int64_t min_len, int* S, int*
   *S = (int)(len > 0 ? ceil_div(len, ch) : 1);
 }
 
-// The split count, down to 5/8 of split_range's, with which `units` such ranges
-// finish first when `slots` blocks run at a time: rounds of blocks, each as long
-// as its tiles plus kBlockTiles tiles' worth of prologue and epilogue.  A last
-// round that is nearly empty costs a whole one: 24 units of 32k tokens in 43
-// splits each (1032 blocks, 512 at a time) took pass B 107 us where 32 units
-// (1024 blocks) took 123, and 8 units of 20011 tokens with 160 rows ran 40
-// splits each (320 blocks, 256 at a time) as two rounds.
-static void split_rounds(int64_t len, int64_t want, int64_t min_len, int64_t units, int64_t slots,
-                         int* S, int* chunk) {
-  constexpr int64_t kBlockTiles = 10;
-  auto cost = [&](int s, int c) {
-    return ceil_div(units * s, slots) * (ceil_div(c, kKeyTile) + kBlockTiles);
-  };
+// The split count with which `units` such ranges finish first when `slots`
+// blocks run at a time: rounds of blocks, each as long as its tiles plus
+// kBlockTiles tiles' worth of prologue and epilogue.  Looked for from ranges of
+// min_len keys, with `fine` half as many (at most `want` ranges), up to 8/5 of split_range's length
+// for min_len, in steps of a tile or 1/32 of the length.  A last round that is
+// nearly empty costs a whole one: 24 units of 32k tokens in 43 splits each
+// (1032 blocks, 512 at a time) took pass B 107 us where 32 units (1024 blocks)
+// took 123, and 8 units of 20011 tokens with 160 rows ran 40 splits each (320
+// blocks, 256 at a time) as two rounds.  Ranges shorter than min_len pay where
+// they still fit one round: 8 units of 8192 tokens in 32 splits 122 us a call, in
+// 16 129 us; of 32k tokens in 128 (two rounds) 181 us, in 64 162 us.
+static void split_rounds(int64_t len, int64_t want, int64_t min_len, bool fine, int64_t units,
+                         int64_t slots, int* S, int* chunk) {
+  constexpr uint32_t kBlockTiles = 10;
   split_range(len, want, min_len, S, chunk);
-  int64_t best = cost(*S, *chunk);
-  const int64_t most = *S;
-  for (int64_t w = most - 1; w >= 1 && 8 * w >= 5 * most; --w) {
-    int s, c;
-    split_range(len, w, min_len, &s, &c);
+  const uint32_t usual = (uint32_t)*S, n = (uint32_t)len;
+  if (fine) split_range(len, want, min_len / 2, S, chunk);
+  auto cost = [&](uint32_t s, uint32_t c) {
+    return (uint64_t)(((uint32_t)units * s + (uint32_t)slots - 1) / (uint32_t)slots) *
+           (c / kKeyTile + kBlockTiles);
+  };
+  uint64_t best = cost(*S, *chunk);
+  const uint32_t step = std::max<uint32_t>(1, (uint32_t)*chunk / (32 * kKeyTile)) * kKeyTile;
+  for (uint32_t c = (uint32_t)*chunk + step;; c += step) {
+    const uint32_t s = (n + c - 1) / c;
+    if (s < 1 || 8 * s < 5 * usual) break;
     // (a change has to be worth 3%)
     if (100 * cost(s, c) < 97 * best) {
       best = cost(s, c);
-      *S = s;
-      *chunk = c;
+      *S = (int)s;
+      *chunk = (int)c;
     }
+    if (s == 1) break;
   }
 }
 
@@ -108,46 +116,51 @@ int make_plan(const grkv_problem* prob, int64_t n, int32_t window, int32_t budge
   if (const char* e = getenv("GRKV_TARGET_BLOCKS")) target = atoll(e);       // tuning experiments
   if (const char* e = getenv("GRKV_TARGET_RET_BLOCKS")) target_ret = atoll(e);
   const int64_t want = ceil_div(target, p->U);
-  // blocks that run at a time: pass B holds two blocks of up to four waves per
-  // compute unit or one of eight, the retained pass one
-  split_rounds(n, want, 512, p->U, p->waves == 8 ? 256 : 512, &p->S1, &p->chunk1);
   p->fast_merge = merge_fast_supported(*p);
-  if (p->fast_merge) {
-    split_rounds(budget, ceil_div(target_ret, p->U), 128, p->U, 256, &p->S2, &p->chunk2);
-    if (p->chunk2 > 4096) split_range(budget, ceil_div(budget, 4096), 128, &p->S2, &p->chunk2);
-  } else if (p->dtype == GRKV_F32) {
-    // The fp32 kernels hold one to eight waves per block and little else, and
-    // their key tiles are a serial chain, so a call with few units is split
-    // down to two tiles per block: at most 512 blocks
-    // (2 units of 1024 tokens, 32 rows: with the blocked solve 287 -> 95 us)
-    const int64_t want32 = std::max<int64_t>(512 / p->U, 1);
-    split_range(n, want32, 64, &p->S1, &p->chunk1);
-    split_range(budget, want32, 64, &p->S2, &p->chunk2);
-  } else {
-    split_range(budget, want, 128, &p->S2, &p->chunk2);
-    if (p->chunk2 > 8192) split_range(budget, ceil_div(budget, 8192), 128, &p->S2, &p->chunk2);
-  }
   // calls with few units split the solve's right-hand-side columns over up
   // to d / 16 blocks per unit (one per compute unit at most)
   p->csplit = 1;
   if ((p->fast_merge || solve_big_supported(*p)) && (size_t)p->U * (p->d / 16) <= 256)
     p->csplit = p->d / 16;
-  if (p->fast_merge || solve_supported(*p)) {   // (one split count for both in the solve)
-    p->S3 = p->S2;
-    p->chunk3 = p->chunk2;
-  } else {
-    split_range(budget, ceil_div(256, p->U), 256, &p->S3, &p->chunk3);
-  }
-
-  layout_plan(p, (size_t)p->U * budget, (size_t)p->U * p->S2, (size_t)p->U * p->S3, 0);
-  if (p->dtype == GRKV_F32 && p->total > GRKV_NOALLOC_SCRATCH_BYTES) {
-    // the finer splits' partials would pass the fixed scratch of the
-    // non-allocating entry point: fewer splits (such a call is no small one)
-    split_range(n, want, 512, &p->S1, &p->chunk1);
-    split_range(budget, ceil_div(256, p->U), 256, &p->S2, &p->chunk2);
-    p->S3 = p->S2;
-    p->chunk3 = p->chunk2;
+  auto splits = [&](bool fine) {
+    // blocks that run at a time: pass B holds two blocks of up to four waves per
+    // compute unit or one of eight, the retained pass one
+    split_rounds(n, want, 512, fine, p->U, p->waves == 8 ? 256 : 512, &p->S1, &p->chunk1);
+    if (p->fast_merge) {
+      // (from 16 splits on, more of them cost the combine more than the pass
+      // gains: 2048 retained keys in 32 splits 164 us a call, in 16 162 us; 512
+      // in 8 124 us, in 4 129 us)
+      const int64_t want_ret = ceil_div(target_ret, p->U);
+      split_rounds(budget, std::min(want_ret, std::max<int64_t>(16, ceil_div(budget, 128))), 128,
+                   fine, p->U, 256, &p->S2, &p->chunk2);
+      if (p->chunk2 > 4096) split_range(budget, ceil_div(budget, 4096), 128, &p->S2, &p->chunk2);
+    } else if (p->dtype == GRKV_F32) {
+      // The fp32 kernels hold one to eight waves per block and little else, and
+      // their key tiles are a serial chain, so a call with few units is split
+      // down to two tiles per block: at most 512 blocks
+      // (2 units of 1024 tokens, 32 rows: with the blocked solve 287 -> 95 us)
+      const int64_t want32 = std::max<int64_t>(512 / p->U, 1);
+      split_range(n, fine ? want32 : want, fine ? 64 : 512, &p->S1, &p->chunk1);
+      split_range(budget, fine ? want32 : ceil_div(256, p->U), fine ? 64 : 256, &p->S2, &p->chunk2);
+    } else {
+      split_range(budget, want, 128, &p->S2, &p->chunk2);
+      if (p->chunk2 > 8192) split_range(budget, ceil_div(budget, 8192), 128, &p->S2, &p->chunk2);
+    }
+    if (p->fast_merge || solve_supported(*p)) {   // (one split count for both in the solve)
+      p->S3 = p->S2;
+      p->chunk3 = p->chunk2;
+    } else {
+      split_range(budget, ceil_div(256, p->U), fine && p->dtype == GRKV_BF16 ? 128 : 256, &p->S3,
+                  &p->chunk3);
+    }
     layout_plan(p, (size_t)p->U * budget, (size_t)p->U * p->S2, (size_t)p->U * p->S3, 0);
+  };
+  // the finer splits of small calls, unless only their partials take the call
+  // past the fixed scratch of the non-allocating entry point
+  splits(true);
+  if (p->total > GRKV_NOALLOC_SCRATCH_BYTES) {
+    splits(false);
+    if (p->total > GRKV_NOALLOC_SCRATCH_BYTES && p->dtype == GRKV_BF16) splits(true);
   }
   return GRKV_OK;
 }
