@@ -43,7 +43,7 @@ constexpr int kKT = 32;   // retained keys per tile (the key orders below assume
 constexpr int kKeyEarlyIters = 13;  // CG iterations run with the fewest splits
 constexpr int kKeyRingEarlyIters = 16;  // the same for the ring passes
 constexpr int kInitBatch = 8;           // key_init: elements a thread loads together
-constexpr int kCgBatch = 4;             // key_cg: split partials a thread loads together
+constexpr int kCgBatch = 4;             // key_rhs: split partials a thread loads together
 
 // Position, inside a block of 32, of the index a lane holds as element j of an
 // MFMA operand when the operand comes from an MFMA result: elements
@@ -691,8 +691,10 @@ __global__ __launch_bounds__(1024) void key_rhs_kernel(
 // unit each sum a range of rows, leave Ap in place of split 0's partial (their
 // own rows of it) and their share of p . Ap in cgpart; the block that finishes
 // last (cgcount, which it sets back to zero) makes the update.  No block waits
-// for another.  One layer of 8 units at 3277 retained keys, the whole call:
-// 1368 -> 1176 us.
+// for another, and each block releases its part with one thread's fence: with
+// a fence by every wave (each a write-back of the XCD's L2) the whole call of
+// one layer of 8 units at 3277 retained keys took 1.02 of the one-block
+// update's time, so it takes 0.72 (1801 -> 1298 us).
 constexpr int kCgTh = 1024;
 constexpr int kCgLoads = 8;    // split partials a thread loads together
 

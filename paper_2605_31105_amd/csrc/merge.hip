@@ -20,11 +20,19 @@ namespace {
 // ------------------------------------------------------------------ gram ----
 // One block per (unit, column split).  Each 32-column slab of X_G (all mp rows)
 // is loaded with 16-byte loads, masked, split into bf16 hi/lo and staged in LDS
-// as [mp][32] (+8 pad) rows; every wave then forms its 32 rows of N against
-// all mp rows.  The next slab's loads are in flight during the MFMAs.
+// as [mp][32] (+8 pad) rows, four columns per store; every wave then forms two
+// 16-row tiles of N, w and NT - 1 - w (a short and a long row of the lower
+// triangle), against the row tiles up to theirs, and writes the blocks and
+// their mirrors.  Row tiles past the m real rows are neither loaded nor
+// multiplied (their blocks are zero).  The next slab's loads are in flight
+// during the MFMAs.  What bounds it is the latency of X's loads with one slab
+// in flight per block: 32 units of 256 rows and 4096 keys 70 -> 64 us (all
+// blocks formed, single 16-bit stores before), 8 units of 160 rows 241 -> 238
+// us a call.
 template <int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void gram_kernel(const float* x, const uint8_t* fixed,
-                                                          float* npart, int c, int S3, int chunk3) {
+                                                          float* npart, int m, int c, int S3,
+                                                          int chunk3) {
   constexpr int MP = WAVES * 32;
   constexpr int NT = MP / 16;              // 16-row tiles of N
   constexpr int RS = 40;                   // LDS row stride in bf16 (32 + 8 pad)
@@ -34,11 +42,14 @@ __global__ __launch_bounds__(WAVES * 64) void gram_kernel(const float* x, const 
   __shared__ __attribute__((aligned(16))) u16 lo[MP * RS];
 
   const int s = blockIdx.x, u = blockIdx.y, tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6, l16 = lane & 15, g = lane >> 4;
+  const int lane = tid & 63, l16 = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int t0 = s * chunk3, t1 = min(t0 + chunk3, c);
   const float* xu = x + (size_t)u * MP * c;
   const uint8_t* fu = fixed + (size_t)u * c;
   const bool vec = (c & 3) == 0;
+  const int nt = (m + 15) / 16;            // row tiles that hold rows
+  const int rtile[2] = {wave, NT - 1 - wave};
 
   f32x4 acc[2][NT];
 #pragma unroll
@@ -55,7 +66,9 @@ __global__ __launch_bounds__(WAVES * 64) void gram_kernel(const float* x, const 
       const int r = e / 32, cc = e % 32, t = tk + cc;
       float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
       const float* src = xu + (size_t)r * c + t;
-      if (vec && t + 3 < t1) {
+      if (r >= 16 * nt) {
+        // (padding rows: zero)
+      } else if (vec && t + 3 < t1) {
         v = *reinterpret_cast<const float4*>(src);
       } else {
         float tmp[4] = {0.f, 0.f, 0.f, 0.f};
@@ -81,46 +94,52 @@ __global__ __launch_bounds__(WAVES * 64) void gram_kernel(const float* x, const 
       const int r = e / 32, cc = e % 32, t = tk + cc;
       float v[4] = {rg[i].x, rg[i].y, rg[i].z, rg[i].w};
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float xv = (t + q < t1 && ((fg[i] >> (8 * q)) & 0xffu) == 0) ? v[q] : 0.f;
-        const __bf16 h = (__bf16)xv;
-        const __bf16 l = (__bf16)(xv - (float)h);
-        hi[r * RS + cc + q] = __builtin_bit_cast(u16, h);
-        lo[r * RS + cc + q] = __builtin_bit_cast(u16, l);
-      }
+      for (int q = 0; q < 4; ++q)
+        v[q] = (t + q < t1 && ((fg[i] >> (8 * q)) & 0xffu) == 0) ? v[q] : 0.f;
+      uint32_t l0, l1;
+      const uint32_t h0 = pack_bf16x2(v[0], v[1], &l0), h1 = pack_bf16x2(v[2], v[3], &l1);
+      *reinterpret_cast<uint2*>(&hi[r * RS + cc]) = make_uint2(h0, h1);
+      *reinterpret_cast<uint2*>(&lo[r * RS + cc]) = make_uint2(l0, l1);
     }
     __syncthreads();
     if (tk + 32 < t1) load(tk + 32);
     bf16x8 ah[2], al[2];
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt) {
-      const int r = wave * 32 + rt * 16 + l16;
+      const int r = rtile[rt] * 16 + l16;
       ah[rt] = as_bf16x8(*reinterpret_cast<const uint4*>(&hi[r * RS + 8 * g]));
       al[rt] = as_bf16x8(*reinterpret_cast<const uint4*>(&lo[r * RS + 8 * g]));
     }
 #pragma unroll
     for (int bt = 0; bt < NT; ++bt) {
+      if (bt >= nt || bt > rtile[1]) continue;   // (wave-uniform; tile NT - 1 - w is the longer row)
       const int r = bt * 16 + l16;
       const bf16x8 bh = as_bf16x8(*reinterpret_cast<const uint4*>(&hi[r * RS + 8 * g]));
       const bf16x8 bl = as_bf16x8(*reinterpret_cast<const uint4*>(&lo[r * RS + 8 * g]));
 #pragma unroll
       for (int rt = 0; rt < 2; ++rt) {
+        if (bt > rtile[rt] || rtile[rt] >= nt) continue;
         acc[rt][bt] = mfma_bf16(ah[rt], bh, acc[rt][bt]);
         acc[rt][bt] = mfma_bf16(ah[rt], bl, acc[rt][bt]);
         acc[rt][bt] = mfma_bf16(al[rt], bh, acc[rt][bt]);
       }
     }
   }
+  // blocks (I, J), J <= I, and their mirrors
   float* out = npart + ((size_t)u * S3 + s) * MP * MP;
 #pragma unroll
   for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
-    for (int bt = 0; bt < NT; ++bt)
+    for (int bt = 0; bt < NT; ++bt) {
+      const int I = rtile[rt];
+      if (bt > I) continue;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = wave * 32 + rt * 16 + 4 * g + i;
-        out[(size_t)row * MP + bt * 16 + l16] = acc[rt][bt][i];
-      }
+      for (int i = 0; i < 4; ++i)
+        out[(size_t)(I * 16 + 4 * g + i) * MP + bt * 16 + l16] = acc[rt][bt][i];
+      if (bt < I)
+        *reinterpret_cast<float4*>(out + (size_t)(bt * 16 + l16) * MP + I * 16 + 4 * g) =
+            make_float4(acc[rt][bt][0], acc[rt][bt][1], acc[rt][bt][2], acc[rt][bt][3]);
+    }
 }
 
 // ----------------------------------------------------------------- solve ----
@@ -888,7 +907,7 @@ template <int WAVES>
 hipError_t launch_gram_w(const Plan& p, const float* x, const uint8_t* fixed, float* npart,
                          hipStream_t s) {
   hipLaunchKernelGGL(gram_kernel<WAVES>, dim3(p.S3, p.U), dim3(WAVES * 64), 0, s, x, fixed, npart,
-                     p.c, p.S3, p.chunk3);
+                     p.m, p.c, p.S3, p.chunk3);
   return hipGetLastError();
 }
 
