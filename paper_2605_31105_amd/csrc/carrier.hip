@@ -18,7 +18,7 @@
 // compare and two selects (16 cycles of a SIMD) and the MFMAs 16, and staging a
 // key costs every block the same.  The products of the next 16 keys are issued
 // among the compares of the current ones, with one barrier per tile; the norm
-// is the hardware estimate with a Newton step, and row addresses are looked up
+// is a corrected hardware estimate, and row addresses are looked up
 // a tile ahead.  64 units of 32k tokens and 2048 keys: 1606 -> 1345 us (four row
 // tiles per wave, at one block per compute unit, 1570 us).
 // stats_kernel: one block per unit; loads by LDS atomics, then b, b_eff, A_max,
@@ -46,13 +46,20 @@ __device__ __forceinline__ float row_sum(float v) {
   return v;
 }
 
-// 1 / sqrt(ss), 0 for ss = 0 or infinite (ss scaled by a power of four where
-// the estimate would leave its normal range).
+// 1 / sqrt(ss) with the square root and then the reciprocal rounded to nearest
+// (Markstein's residual corrections of the hardware estimates; over all
+// mantissas and estimates an ulp off either way, the result differs from the
+// IEEE operations' in 1 of 10^7), 0 for ss = 0 or infinite; ss is scaled by a
+// power of four where the estimate would leave its normal range.
 __device__ __forceinline__ float inv_norm(float ss) {
   const bool tiny = ss < 0x1p-100f;
   const float x = tiny ? ss * 0x1p48f : ss;
-  float r = __builtin_amdgcn_rsqf(x);
-  r = fmaf(fmaf(-x * r, r, 1.f), 0.5f * r, r);
+  const float y = __builtin_amdgcn_rsqf(x);
+  float q = x * y;
+  q = fmaf(fmaf(-q, q, x), 0.5f * y, q);
+  float r = __builtin_amdgcn_rcpf(q);
+  r = fmaf(fmaf(-q, r, 1.f), r, r);
+  r = fmaf(fmaf(-q, r, 1.f), r, r);
   if (tiny) r *= 0x1p24f;
   return ss > 0.f && ss < __builtin_huge_valf() ? r : 0.f;
 }
@@ -121,8 +128,8 @@ __global__ __launch_bounds__(kMatchWaves * 64) void match_kernel(
       }
       // the CPR chunks of a key sit in CPR consecutive lanes
       ss = row_sum<CPR>(ss);
-      // 1 / ||k||: the hardware estimate and one Newton step (within an ulp,
-      // as a division by the square root is, at a tenth of its instructions)
+      // 1 / ||k|| (the IEEE square root and division take the kernel past 128
+      // registers, one block per compute unit less: 1342 -> 1845 us)
       if (ch == 0)
         inv_s[buf][key] = t * kRetTile + key >= c ? __builtin_nanf("") : inv_norm(ss);
     }

@@ -78,6 +78,7 @@ constexpr int kAdaWaves = kAdaThreads / 64;
 constexpr int kAdaSamplePer = 8;
 constexpr int kAdaSample = kAdaSamplePer * kAdaThreads;
 constexpr uint32_t kAdaCand = 12288;   // candidates held in LDS
+constexpr int64_t kAdaInside = 10240;  // ranks a bracket may span (its ends are rounded outwards)
 constexpr uint32_t kAdaTop = 0x7F800001u;
 constexpr uint32_t kAdaSlack = 32768u;
 constexpr int64_t kAdaSparse = 65536;  // four samples span at least 32 keys (one line) from here
@@ -113,18 +114,29 @@ __device__ bool bracket_search(const uint32_t* __restrict__ key, int64_t N, int 
     t1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)t1);
     parity ^= 1;
   };
-  // 1. the bracket [lo, hi): the samples about 4 sqrt(r) + 16 ranks either
-  // side of rank r = k / stride, each bisected down to kAdaSlack units in the
+  // 1. the bracket [lo, hi): the samples about four standard deviations + 16
+  // ranks either side of rank r = k / stride (fewer where they would hold more
+  // keys than fit), each bisected down to kAdaSlack units in the
   // last place (2^-8 relative: far less than the ranks' width) and kept on its
   // safe side
   uint32_t lo = 0u, hi = kAdaTop;
   if (N > (int64_t)kAdaCand) {
+    // (one or two heads of a layer that one batch of loads covers: the radix's
+    // sweeps are as short as the bisection; 30000 keys of one head 21.9 us
+    // against 25.1, four heads of 3200 28.2 against 24.6)
+    if (H <= 2 && N <= (int64_t)kAdaThreads * kAdaUnroll) return false;
     // sample i is key i * stride, or (layers of at least kAdaSparse keys) key
     // (i / 4) * 4 stride + 8 (i % 4): of four neighbouring samples' span, the
     // first 25 keys
     const int64_t stride = (N + kAdaSample - 1) / kAdaSample;
     const int ns = (int)((N + stride - 1) / stride);
     const bool sparse = N >= kAdaSparse;
+    // (three standard deviations of a sampled rank at least: with fewer the
+    // bracket often misses T, and the sweep is lost)
+    const int r = (int)((int64_t)kk / stride);
+    const float sd = sqrtf((float)r * (1.f - fminf((float)r / ns, 1.f)));
+    const int delta = min(4 * (int)sd + 16, (int)(kAdaInside / (2 * stride)));
+    if (delta < 3.f * sd + 1.f) return false;
     uint32_t sv[kAdaSamplePer];
 #pragma unroll
     for (int m = 0; m < kAdaSamplePer; ++m) {
@@ -133,7 +145,6 @@ __device__ bool bracket_search(const uint32_t* __restrict__ key, int64_t N, int 
       const uint32_t x = key[j < N ? j : N - 1];
       sv[m] = i < ns && j < N ? x : 0u;
     }
-    const int r = (int)((int64_t)kk / stride), delta = 4 * (int)sqrtf((float)r) + 16;
     const bool act[2] = {r - delta >= 0, r + delta < ns};
     const uint32_t J[2] = {(uint32_t)(r - delta), (uint32_t)(r + delta)};
     uint32_t L[2] = {0u, 0u}, U[2] = {kAdaTop, kAdaTop};
@@ -156,51 +167,61 @@ __device__ bool bracket_search(const uint32_t* __restrict__ key, int64_t N, int 
     if (act[1]) lo = L[1];
     if (!(lo < hi)) return false;
   }
-  // 2. one sweep, head by head: keys at or above hi counted, keys in [lo, hi)
-  // appended
+  // 2. one sweep: keys at or above hi counted, keys in [lo, hi) appended.  A
+  // wave takes a segment of one head at a time (up to kAdaUnroll keys a lane;
+  // shorter where the waves outnumber the heads), so layers of short heads
+  // keep every lane's loads in flight: 8 heads of 3.3k keys 25 us a call (head
+  // by head 48, the radix 39), 128 heads of 500 63 us (442, 336).
   __syncthreads();
   if (tid == 0) w.n = 0u;
   __syncthreads();
   const uint32_t width = hi - lo;
-  uint32_t above = 0;
-  for (int h = 0; h < H; ++h) {
+  uint32_t above = 0;   // (this wave's share)
+  const bool whole = N <= (int64_t)kAdaCand;   // every key is inside
+  const int want = max((P + 64 * kAdaUnroll - 1) / (64 * kAdaUnroll), max(1, kAdaWaves / H));
+  const int len = ((P + want - 1) / want + 63) / 64 * 64, nseg = (P + len - 1) / len;
+  for (int q = wave; q < H * nseg; q += kAdaWaves) {
+    const int h = q / nseg, e0 = (q - h * nseg) * len + lane, end = min(e0 - lane + len, P);
     const uint32_t* kh = key + (size_t)h * P;
-    uint32_t ch = 0;
-    for (int e0 = 0; e0 < P; e0 += kAdaThreads * kAdaUnroll) {
-      uint32_t x[kAdaUnroll];
+    uint32_t x[kAdaUnroll];
 #pragma unroll
-      for (int k = 0; k < kAdaUnroll; ++k) x[k] = kh[min(e0 + k * kAdaThreads + tid, P - 1)];
-      uint32_t in = 0;   // bit k: key k lies inside the bracket
+    for (int k = 0; k < kAdaUnroll; ++k) x[k] = kh[min(e0 + k * 64, P - 1)];
+    uint32_t ch = 0, in = 0;   // in, bit k: key k lies inside the bracket
 #pragma unroll
-      for (int k = 0; k < kAdaUnroll; ++k) {
-        const bool live = e0 + k * kAdaThreads + tid < P;
-        ch += live && x[k] >= hi;
-        in |= (uint32_t)(live && x[k] - lo < width) << k;
-      }
-      const uint32_t cnt = __builtin_popcount(in);
-      uint32_t incl = cnt;
+    for (int k = 0; k < kAdaUnroll; ++k) {
+      const bool live = e0 + k * 64 < end;
+      ch += live && x[k] >= hi;
+      in |= (uint32_t)(live && x[k] - lo < width) << k;
+    }
+    const uint32_t cnt = __builtin_popcount(in);
+    uint32_t incl = cnt;
 #pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t t = __shfl_up(incl, off);
-        if (lane >= off) incl += t;
-      }
-      const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-      uint32_t base = 0;
-      if (lane == 0 && tot) base = atomicAdd(&w.n, tot);
-      uint32_t o = (uint32_t)__builtin_amdgcn_readfirstlane((int)base) + incl - cnt;
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t t = __shfl_up(incl, off);
+      if (lane >= off) incl += t;
+    }
+    const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    uint32_t base = 0;
+    if (lane == 0 && tot) base = atomicAdd(&w.n, tot);
+    uint32_t o = (uint32_t)__builtin_amdgcn_readfirstlane((int)base) + incl - cnt;
+    if (whole) {
+#pragma unroll
+      for (int k = 0; k < kAdaUnroll; ++k)
+        if ((in >> k & 1u) && o < kAdaCand) { w.key[o] = x[k]; w.head[o] = (uint8_t)h; ++o; }
+    } else {
       // the few keys inside are read again (from cache): a test per key of
       // the 32 in registers costs more
       while (in) {
         const int k = __builtin_ctz(in);
         in &= in - 1;
-        const uint32_t y = kh[e0 + k * kAdaThreads + tid];
+        const uint32_t y = kh[e0 + k * 64];
         if (o < kAdaCand) { w.key[o] = y; w.head[o] = (uint8_t)h; }
         ++o;
       }
     }
     ch = wave_sum_dpp(ch);
     if (lane == 0 && ch) atomicAdd(&gt[h], ch);
-    above += ch;   // (this wave's share)
+    above += ch;
   }
   uint32_t chi, unused;
   totals(lane == 0 ? above : 0u, 0u, chi, unused);   // the barrier also publishes the candidates

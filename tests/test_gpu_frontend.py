@@ -158,6 +158,13 @@ def test_ragged_generic_path(label, cfg_id, over, budgets):
     (2, 8, 20000, 1500, "sampled-low"),  # the same with four samples per cache line
     (2, 4, 6000, 6032, "normal"),       # every token of the layer taken
     (2, 4, 6000, 32, "normal"),         # none taken
+    (2, 1, 20000, 900, "normal"),       # few heads, one batch of loads: radix
+    (2, 1, 40000, 900, "normal"),
+    (3, 17, 997, 90, "normal"),         # more heads than waves, short segments
+    (2, 128, 130, 40, "normal"),
+    (1, 3, 70001, 30000, "normal"),     # a high rank: the bracket's width is capped
+    (1, 8, 65537, 4096, "normal"),
+    (1, 8, 131000, 8192, "normal"),     # too many keys per sample: radix
 ])
 def test_adaptive_budgets_search_paths(layers, heads, P, budget, dist):
     import paper_2605_31105_amd as G
