@@ -43,7 +43,7 @@ constexpr int kKT = 32;   // retained keys per tile (the key orders below assume
 constexpr int kKeyEarlyIters = 13;  // CG iterations run with the fewest splits
 constexpr int kKeyRingEarlyIters = 16;  // the same for the ring passes
 constexpr int kInitBatch = 8;           // key_init: elements a thread loads together
-constexpr int kCgBatch = 4;             // key_rhs: split partials a thread loads together
+constexpr int kCgBatch = 4;             // key_cg, key_rhs: split partials a thread loads together
 
 // Position, inside a block of 32, of the index a lane holds as element j of an
 // MFMA operand when the operand comes from an MFMA result: elements
@@ -685,21 +685,148 @@ __global__ __launch_bounds__(1024) void key_rhs_kernel(
 // One conjugate-gradient update per unit: Ap = sum_s opart - (sum_s hpart) o F
 // + lambda_k p; alpha += a p; r -= a Ap; p = r + beta p; and the row dots
 // s = rowdot(F, p) of the new direction for the next operator pass.
+
+// One block per unit, for calls with many units or few splits.
+template <int MP, int D>
+__global__ __launch_bounds__(1024) void key_cg_kernel(
+    const float* __restrict__ opart, const float* __restrict__ hpart, int S,
+    const float* __restrict__ Fm, float* __restrict__ alpha, float* __restrict__ r,
+    float* __restrict__ p, float* __restrict__ sdot, double* __restrict__ cg, float lam_k,
+    float tol, int max_iter) {
+  constexpr int NTH = 1024, E4 = MP * D / 4, PER = (E4 + NTH - 1) / NTH, RW = D / 4;
+  __shared__ float hsum[MP];
+  __shared__ double red[16];
+  const int u = blockIdx.x, tid = threadIdx.x;
+  if ((int)cg[u * 4 + 3] != kKeyRunning) return;
+  // the split partials are loaded kCgBatch splits at a time (indices past S
+  // read split S - 1, in bounds, and are not summed) and summed in split
+  // order: the loads of a batch are in flight together
+  for (int i = tid; i < MP; i += NTH) {
+    float h = 0.f;
+    for (int k0 = 0; k0 < S; k0 += kCgBatch) {
+      float hv[kCgBatch];
+#pragma unroll
+      for (int j = 0; j < kCgBatch; ++j) hv[j] = hpart[((size_t)u * S + min(k0 + j, S - 1)) * MP + i];
+#pragma unroll
+      for (int j = 0; j < kCgBatch; ++j)
+        if (k0 + j < S) h += hv[j];
+    }
+    hsum[i] = h;
+  }
+  __syncthreads();
+  const size_t base = (size_t)u * E4;
+  const float4* __restrict__ op4 = reinterpret_cast<const float4*>(opart) + (size_t)u * S * E4;
+  const float4* __restrict__ F4 = reinterpret_cast<const float4*>(Fm) + base;
+  float4* __restrict__ a4 = reinterpret_cast<float4*>(alpha) + base;
+  float4* __restrict__ r4 = reinterpret_cast<float4*>(r) + base;
+  float4* __restrict__ p4 = reinterpret_cast<float4*>(p) + base;
+  const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
+  float4 osum[PER];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) osum[k] = z4;
+  for (int s0 = 0; s0 < S; s0 += kCgBatch) {
+    float4 ov[kCgBatch][PER];
+#pragma unroll
+    for (int j = 0; j < kCgBatch; ++j)
+#pragma unroll
+      for (int k = 0; k < PER; ++k)
+        ov[j][k] = op4[(size_t)min(s0 + j, S - 1) * E4 + min(tid + k * NTH, E4 - 1)];
+#pragma unroll
+    for (int j = 0; j < kCgBatch; ++j)
+      if (s0 + j < S)
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+          osum[k].x += ov[j][k].x; osum[k].y += ov[j][k].y;
+          osum[k].z += ov[j][k].z; osum[k].w += ov[j][k].w;
+        }
+  }
+  float4 ap[PER], pp[PER], fv[PER];
+  double pap = 0;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int e = tid + k * NTH;
+    ap[k] = pp[k] = fv[k] = z4;
+    if (e < E4) {
+      float4 v = osum[k];
+      const float4 pe = p4[e], f = F4[e];
+      const float h = hsum[e / RW];
+      v.x += lam_k * pe.x - h * f.x;
+      v.y += lam_k * pe.y - h * f.y;
+      v.z += lam_k * pe.z - h * f.z;
+      v.w += lam_k * pe.w - h * f.w;
+      ap[k] = v;
+      pp[k] = pe;
+      fv[k] = f;
+      pap += (double)dot4(pe, v);
+    }
+  }
+  pap = block_sum(pap, red);
+  const double rr = cg[u * 4 + 0], rr0 = cg[u * 4 + 1];
+  const int it = (int)cg[u * 4 + 2] + 1;
+  if (!(pap > 0)) {
+    if (tid == 0) cg[u * 4 + 3] = kKeyBreakdown;
+    return;
+  }
+  const float a = (float)(rr / pap);
+  float4 rv[PER];
+  double rn = 0;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int e = tid + k * NTH;
+    rv[k] = z4;
+    if (e < E4) {
+      float4 al = a4[e], re = r4[e];
+      al.x += a * pp[k].x; al.y += a * pp[k].y; al.z += a * pp[k].z; al.w += a * pp[k].w;
+      re.x -= a * ap[k].x; re.y -= a * ap[k].y; re.z -= a * ap[k].z; re.w -= a * ap[k].w;
+      a4[e] = al;
+      r4[e] = re;
+      rv[k] = re;
+      rn += (double)dot4(re, re);
+    }
+  }
+  rn = block_sum(rn, red);
+  int st = kKeyRunning;
+  if (sqrt(rn) <= (double)tol * sqrt(rr0)) st = kKeyConverged;
+  else if (it >= max_iter) st = kKeyMaxIter;
+  if (st == kKeyRunning) {
+    const float beta = (float)(rn / rr);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int e = tid + k * NTH;
+      float4 pn = z4;
+      if (e < E4) {
+        pn = make_float4(rv[k].x + beta * pp[k].x, rv[k].y + beta * pp[k].y,
+                         rv[k].z + beta * pp[k].z, rv[k].w + beta * pp[k].w);
+        p4[e] = pn;
+      }
+      // row dot over the RW consecutive threads of a row (whole rows only)
+      float sd = dot4(fv[k], pn);
+#pragma unroll
+      for (int off = 1; off < RW; off <<= 1) sd += __shfl_xor(sd, off);
+      if (e < E4 && (e % RW) == 0) sdot[(size_t)u * MP + e / RW] = sd;
+    }
+  }
+  if (tid == 0) {
+    cg[u * 4 + 0] = rn;
+    cg[u * 4 + 2] = it;
+    cg[u * 4 + 3] = st;
+  }
+}
+
 // The split partials are what it reads most (S of them, 64 KB each at m = 128,
 // d = 128), and a single compute unit reads some 60 GB/s: summed by one block
-// per unit, 26 splits took about 36 us per iteration.  So kCgBlocks blocks per
-// unit each sum a range of rows, leave Ap in place of split 0's partial (their
-// own rows of it) and their share of p . Ap in cgpart; the block that finishes
-// last (cgcount, which it sets back to zero) makes the update.  No block waits
-// for another, and each block releases its part with one thread's fence: with
-// a fence by every wave (each a write-back of the XCD's L2) the whole call of
-// one layer of 8 units at 3277 retained keys took 1.02 of the one-block
-// update's time, so it takes 0.72 (1801 -> 1298 us).
+// per unit, 26 splits take about 36 us per iteration.  So with few units and
+// many splits kCgBlocks blocks per unit each sum a range of rows, leave Ap in
+// place of split 0's partial (their own rows of it) and their share of p . Ap
+// in cgpart; the block that finishes last (cgcount, which it sets back to zero)
+// makes the update.  No block waits for another, and each block releases its
+// part with one thread's fence (one by every wave, each a write-back of the
+// XCD's L2, costs what the split saves).
 constexpr int kCgTh = 1024;
 constexpr int kCgLoads = 8;    // split partials a thread loads together
 
 template <int MP, int D>
-__global__ __launch_bounds__(kCgTh) void key_cg_kernel(
+__global__ __launch_bounds__(kCgTh) void key_cg_split_kernel(
     float* opart, const float* __restrict__ hpart, int S, const float* __restrict__ Fm,
     float* alpha, float* r, float* p, float* sdot, double* cg, double* cgpart, int* cgcount,
     float lam_k, float tol, int max_iter) {
@@ -869,9 +996,18 @@ __global__ __launch_bounds__(kCgTh) void key_cg_kernel(
 
 template <int MP, int D>
 hipError_t launch_cg(const Plan& p, const KeyArgs& a, int S, hipStream_t s) {
-  hipLaunchKernelGGL((key_cg_kernel<MP, D>), dim3(kCgBlocks, p.U), dim3(kCgTh), 0, s, a.opart,
-                     a.hpart, S, a.Fm, a.alpha, a.r, a.p, a.sdot, a.cg, a.cgpart, a.cgcount,
-                     a.lam_k, a.tol, a.max_iter);
+  // The blocks of one unit cost a fence each: they pay from a megabyte of
+  // partials per unit and with at most kCgBlocks units.  Whole calls, one block
+  // per unit against kCgBlocks: 8 units of 3277 keys (26 splits) 1360 / 1067 us,
+  // 16 of 2048 (16) 1802 / 1590; 8 of 512 (8) 1546 / 1631, 32 of 1024 2237 / 2602,
+  // 128 of 496 3198 / 8771.
+  if (p.U <= kCgBlocks && (size_t)S * MP * D * sizeof(float) >= (size_t)1 << 20)
+    hipLaunchKernelGGL((key_cg_split_kernel<MP, D>), dim3(kCgBlocks, p.U), dim3(kCgTh), 0, s,
+                       a.opart, a.hpart, S, a.Fm, a.alpha, a.r, a.p, a.sdot, a.cg, a.cgpart,
+                       a.cgcount, a.lam_k, a.tol, a.max_iter);
+  else
+    hipLaunchKernelGGL((key_cg_kernel<MP, D>), dim3(p.U), dim3(1024), 0, s, a.opart, a.hpart, S,
+                       a.Fm, a.alpha, a.r, a.p, a.sdot, a.cg, a.lam_k, a.tol, a.max_iter);
   return hipGetLastError();
 }
 
