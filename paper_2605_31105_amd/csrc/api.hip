@@ -125,14 +125,22 @@ int make_plan(const grkv_problem* prob, int64_t n, int32_t window, int32_t budge
   auto splits = [&](bool fine) {
     // blocks that run at a time: pass B holds two blocks of up to four waves per
     // compute unit or one of eight, the retained pass one
+    // (shorter ranges only from where the partials are combined by a launch of
+    // their own: 50 units of 3280 tokens in 10 splits 167 us a call, in 7 158 us;
+    // 64 of 2500 175 / 171 us)
     split_rounds(n, want, 512, fine, p->U, p->waves == 8 ? 256 : 512, &p->S1, &p->chunk1);
+    if (p->S1 < kPrecombineSplits)
+      split_rounds(n, want, 512, false, p->U, p->waves == 8 ? 256 : 512, &p->S1, &p->chunk1);
     if (p->fast_merge) {
       // (from 16 splits on, more of them cost the combine more than the pass
       // gains: 2048 retained keys in 32 splits 164 us a call, in 16 162 us; 512
       // in 8 124 us, in 4 129 us)
-      const int64_t want_ret = ceil_div(target_ret, p->U);
-      split_rounds(budget, std::min(want_ret, std::max<int64_t>(16, ceil_div(budget, 128))), 128,
-                   fine, p->U, 256, &p->S2, &p->chunk2);
+      // (here too: 50 units with 434 retained keys in 5 splits 169 us, in 4 167 us)
+      const int64_t want_ret = std::min(ceil_div(target_ret, p->U),
+                                        std::max<int64_t>(16, ceil_div(budget, 128)));
+      split_rounds(budget, want_ret, 128, fine, p->U, 256, &p->S2, &p->chunk2);
+      if (p->S2 < kPrecombineRetSplits)
+        split_rounds(budget, want_ret, 128, false, p->U, 256, &p->S2, &p->chunk2);
       if (p->chunk2 > 4096) split_range(budget, ceil_div(budget, 4096), 128, &p->S2, &p->chunk2);
     } else if (p->dtype == GRKV_F32) {
       // The fp32 kernels hold one to eight waves per block and little else, and
