@@ -819,9 +819,10 @@ __global__ __launch_bounds__(1024) void key_cg_kernel(
 // many splits kCgBlocks blocks per unit each sum a range of rows, leave Ap in
 // place of split 0's partial (their own rows of it) and their share of p . Ap
 // in cgpart; the block that finishes last (cgcount, which it sets back to zero)
-// makes the update.  No block waits for another, and each block releases its
-// part with one thread's fence (one by every wave, each a write-back of the
-// XCD's L2, costs what the split saves).
+// makes the update.  No block waits for another.  Every wave drains its own
+// stores of Ap before the block's barrier, and one thread releases them for the
+// block after it (a release by every wave, each a write-back of the XCD's L2,
+// costs what the split saves).
 constexpr int kCgTh = 1024;
 constexpr int kCgLoads = 8;    // split partials a thread loads together
 
@@ -894,14 +895,19 @@ __global__ __launch_bounds__(kCgTh) void key_cg_split_kernel(
     v.z += lam_k * pe.z - h * f.z;
     v.w += lam_k * pe.w - h * f.w;
     op4[e0] = v;   // Ap (the block has read split 0's partial of these elements)
+    // the store has left this wave before the barriers below: a workgroup
+    // barrier does not wait for global stores, and thread 0's release waits
+    // for its own wave's only
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     pap = (double)dot4(pe, v);
   }
   pap = block_sum(pap, red);
   // publish Ap and the share of p . Ap, then count in; the last block sees
   // every other block's
-  // (one thread releases for the block, after the barrier: a release at device
-  // scope writes the compute die's dirty cache lines back, and one by each wave
-  // of the block costs more than the sums)
+  // (one thread releases for the block, after the barrier before which every
+  // storing wave has drained: a release at device scope writes the compute
+  // die's dirty cache lines back, and one by each wave of the block costs more
+  // than the sums)
   __syncthreads();
   if (tid == 0) {
     cgpart[(size_t)u * kCgBlocks + blk] = pap;
