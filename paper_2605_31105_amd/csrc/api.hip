@@ -219,11 +219,21 @@ static void layout_plan(Plan* p, size_t slots, size_t splits2, size_t splits3, s
 
 // Workspace of the key step, after the compress workspace.  A key-pass block
 // holds all m rows of a unit and a split of its retained keys.
-static void make_key_plan(const Plan& p, int steps, KeyPlan* kp) {
-  // about 256 blocks (one per compute unit) while every unit is iterating;
-  // about 2048 later, when a unit's iteration spanning several compute units
-  // keeps it short once only a few units are still converging
-  split_range(p.c, 256 / p.U, 64, &kp->S_full, &kp->chunk_full);
+void make_key_plan(const Plan& p, int steps, KeyPlan* kp) {
+  // While every unit is iterating: about one block per compute unit, the count
+  // rounded down where a block fills one (128 rows: 48 units of 2000 keys in 5
+  // splits 1.95 ms a call, in 6 2.19) and up where two fit (32 rows; 64 with more
+  // than 64 units: 155 units of 3000 keys in one split 5.6 ms, in two 4.0; with
+  // 48 units 5 splits 1.55 ms, 6 1.65).  Past 128 units of 128 rows one split
+  // leaves compute units idle and two take a second round, which shrinks as units
+  // converge: long units take two (one split / two: 129 units of 3500 keys 5.4 /
+  // 4.5 ms, of 2000 3.94 / 3.70, of 1000 3.40 / 3.47; 220 of 3500 6.7 / 6.4, of
+  // 2000 4.94 / 5.03).
+  // Later: about 2048 blocks, when a unit's iteration spanning several compute
+  // units keeps it short once only a few units are still converging
+  const bool up = p.mp == 32 || (p.mp == 64 && p.U > 64) ||
+                  (p.mp == 128 && p.U > 128 && p.c >= (p.U <= 144 ? 1792 : 2304));
+  split_range(p.c, up ? ceil_div(256, p.U) : 256 / p.U, 64, &kp->S_full, &kp->chunk_full);
   split_range(p.c, ceil_div(2048, p.U), 64, &kp->S4, &kp->chunk4);
   // the ring passes' later iterations: about 1024 blocks (fewer partials for
   // the separate CG update to combine, measured faster than 2048), at most 16

@@ -228,6 +228,9 @@ struct KeyPlan {
   size_t total;
 };
 
+// The splits and workspace of `steps` alternating steps of plan p.
+void make_key_plan(const Plan& p, int steps, KeyPlan* kp);
+
 struct KeyArgs {
   const uint16_t* q;        // [U][m][d] window queries
   const uint16_t* k0;       // [U][c][d] retained keys K0
