@@ -122,7 +122,34 @@ int make_plan(const grkv_problem* prob, int64_t n, int32_t window, int32_t budge
   p->csplit = 1;
   if ((p->fast_merge || solve_big_supported(*p)) && (size_t)p->U * (p->d / 16) <= 256)
     p->csplit = p->d / 16;
-  auto splits = [&](bool fine) {
+  // fine: the finer splits of small calls; in fp32 the blocks that they make (0
+  // and -1: the coarse splits)
+  auto splits = [&](int fine) {
+    if (p->dtype == GRKV_F32) {
+      // The fp32 kernels hold one to eight waves per block and little else, and
+      // their key tiles are a serial chain, so a call with few units is split
+      // down to two tiles per block, to `fine` blocks over the units at most
+      // (2 units of 1024 tokens, 32 rows: with the blocked solve 287 -> 95 us),
+      // and never into fewer splits than the coarse ones, whose blocks keep the
+      // compute units busy in calls with many units (131 units of 10976 tokens,
+      // 32 rows: 3 splits 2.40 ms, 8 splits 1.98)
+      auto finest = [&](int64_t len, int64_t want_c, int64_t min_c, int* S, int* chunk) {
+        split_range(len, want_c, min_c, S, chunk);
+        int Sf, ch;
+        split_range(len, std::max(fine, 1) / p->U, 64, &Sf, &ch);
+        if (Sf > *S) {
+          *S = Sf;
+          *chunk = ch;
+        }
+      };
+      finest(n, want, 512, &p->S1, &p->chunk1);
+      finest(budget, fine < 0 ? ceil_div(256, p->U) : want, fine < 0 ? 256 : 128, &p->S2,
+             &p->chunk2);
+      if (p->chunk2 > 8192) split_range(budget, ceil_div(budget, 8192), 128, &p->S2, &p->chunk2);
+      finest(budget, ceil_div(256, p->U), 256, &p->S3, &p->chunk3);
+      layout_plan(p, (size_t)p->U * budget, (size_t)p->U * p->S2, (size_t)p->U * p->S3, 0);
+      return;
+    }
     // blocks that run at a time: pass B holds two blocks of up to four waves per
     // compute unit or one of eight, the retained pass one
     // (shorter ranges only from where the partials are combined by a launch of
@@ -142,33 +169,30 @@ int make_plan(const grkv_problem* prob, int64_t n, int32_t window, int32_t budge
       if (p->S2 < kPrecombineRetSplits)
         split_rounds(budget, want_ret, 128, false, p->U, 256, &p->S2, &p->chunk2);
       if (p->chunk2 > 4096) split_range(budget, ceil_div(budget, 4096), 128, &p->S2, &p->chunk2);
-    } else if (p->dtype == GRKV_F32) {
-      // The fp32 kernels hold one to eight waves per block and little else, and
-      // their key tiles are a serial chain, so a call with few units is split
-      // down to two tiles per block: at most 512 blocks
-      // (2 units of 1024 tokens, 32 rows: with the blocked solve 287 -> 95 us)
-      const int64_t want32 = std::max<int64_t>(512 / p->U, 1);
-      split_range(n, fine ? want32 : want, fine ? 64 : 512, &p->S1, &p->chunk1);
-      split_range(budget, fine ? want32 : ceil_div(256, p->U), fine ? 64 : 256, &p->S2, &p->chunk2);
-    } else {
-      split_range(budget, want, 128, &p->S2, &p->chunk2);
-      if (p->chunk2 > 8192) split_range(budget, ceil_div(budget, 8192), 128, &p->S2, &p->chunk2);
-    }
-    if (p->fast_merge || solve_supported(*p)) {   // (one split count for both in the solve)
       p->S3 = p->S2;
       p->chunk3 = p->chunk2;
     } else {
-      split_range(budget, ceil_div(256, p->U), fine && p->dtype == GRKV_BF16 ? 128 : 256, &p->S3,
-                  &p->chunk3);
+      split_range(budget, want, 128, &p->S2, &p->chunk2);
+      if (p->chunk2 > 8192) split_range(budget, ceil_div(budget, 8192), 128, &p->S2, &p->chunk2);
+      split_range(budget, ceil_div(256, p->U), fine ? 128 : 256, &p->S3, &p->chunk3);
     }
     layout_plan(p, (size_t)p->U * budget, (size_t)p->U * p->S2, (size_t)p->U * p->S3, 0);
   };
-  // the finer splits of small calls, unless only their partials take the call
-  // past the fixed scratch of the non-allocating entry point
-  splits(true);
-  if (p->total > GRKV_NOALLOC_SCRATCH_BYTES) {
-    splits(false);
-    if (p->total > GRKV_NOALLOC_SCRATCH_BYTES && p->dtype == GRKV_BF16) splits(true);
+  // The finer splits, in fp32 the finest, that keep the call inside the fixed
+  // scratch of the non-allocating entry point; a call that no splits keep inside
+  // it takes the finest.  fp32: 512 blocks of up to four waves, 256 of eight (8
+  // units of 8192 tokens, 128 rows, 2048 retained: coarse 363 us, 256 blocks 267,
+  // 512 265; 124 units of 580 tokens, 256 rows: coarse 525 us, 256 blocks 523, 512
+  // 618; 16 units of 4096 544, 392, 429)
+  const int finest = p->dtype == GRKV_BF16 ? 1 : p->waves == 8 ? 256 : 512;
+  const int coarsest = p->dtype == GRKV_BF16 ? 0 : -1;
+  for (int fine = finest;; fine = fine > 0 ? fine * 3 / 4 : fine - 1) {
+    splits(fine);
+    if (p->total <= GRKV_NOALLOC_SCRATCH_BYTES) break;
+    if (fine == coarsest) {
+      splits(finest);
+      break;
+    }
   }
   return GRKV_OK;
 }
@@ -331,22 +355,25 @@ int check_pointers(const void* q_obs, const void* K, const void* V, const grkv_p
 }
 
 // The solve of up to 128 rows outside the fast path: Y combined already, X V0
-// and Gram partials of S2 splits of the normalised X (no masses to divide by).
+// and Gram partials of the normalised X (no masses to divide by).  Several
+// splits, or different counts of the two, are summed by one launch over all
+// units into resid and gram, which the solve then reads element by element
+// before it writes them.
+bool generic_sums(const Plan& p) { return p.S2 > 2 || p.S3 != p.S2; }
+
 hipError_t generic_solve(const Plan& p, char* ws, float* y, float* stats, hipStream_t s) {
   auto F = [&](size_t o) { return (float*)(ws + o); };
   Plan q = p;
   q.csplit = 1;
   q.rag = nullptr;
-  // several splits: summed by one launch over all units into resid and gram,
-  // which the solve reads element by element before it writes them
   const float* xv = F(p.xvpart);
   const float* np = F(p.npart);
   int S = p.S2;
-  if (S > 2) {
+  if (generic_sums(p)) {
     const float* part[kCombineSegs] = {xv, np, nullptr, nullptr};
     float* const outs[kCombineSegs] = {F(p.resid), F(p.gram), nullptr, nullptr};
     const size_t per[kCombineSegs] = {(size_t)p.mp * p.d, (size_t)p.mp * p.mp, 0, 0};
-    const int Sc[kCombineSegs] = {S, S, 0, 0};
+    const int Sc[kCombineSegs] = {p.S2, p.S3, 0, 0};
     const hipError_t e = launch_combine_parts(p.U, Sc, part, outs, per, s);
     if (e != hipSuccess) return e;
     xv = F(p.resid);

@@ -329,6 +329,9 @@ def test_retained_mass_far_below_full_cache(fix_window, kv_heads):
     ("m-256", dict(group=8, window=32, n=1500, budget=300)),
     ("window-1", dict(group=1, window=1, n=999, budget=65)),
     ("many-units", dict(layers=150, n=300, budget=70)),
+    # two and three splits of X V0 partials beside one of Gram partials
+    ("many-units-2-and-1-splits", dict(layers=150, n=400, budget=200)),
+    ("many-units-3-and-1-splits", dict(layers=150, n=400, budget=300)),
 ], ids=lambda v: v if isinstance(v, str) else "")
 def test_fp32_shapes(label, over):
     # the fp32 split counts, and the solve on one, two and many summed partials

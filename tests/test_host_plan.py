@@ -51,3 +51,33 @@ def test_key_step_splits(plan, rows, units, keys, splits):
         p = plan(units, rows // 16, d, G.GRKV_BF16, 4 * keys, 16, keys)
         assert p.mp == rows and p.S_full == splits
         assert p.S_full <= p.S4r <= p.S4
+
+
+@pytest.mark.parametrize("rows,units,d,n,budget", [
+    (32, 131, 128, 10976, 4962), (32, 93, 64, 14335, 6199), (64, 64, 128, 4096, 512),
+    (128, 40, 128, 9000, 3000), (256, 124, 128, 580, 253), (256, 59, 128, 8028, 3698),
+    (32, 400, 64, 20000, 9000), (128, 8, 128, 8192, 2048), (256, 8, 128, 8192, 1024),
+])
+def test_fp32_splits(plan, rows, units, d, n, budget):
+    # never fewer splits than one block's share of 1024 (256 for the Gram sums)
+    # gives: calls with many units keep the compute units busy
+    p = plan(units, rows // 16, d, G.GRKV_F32, n, 16, budget)
+    ceil = lambda a, b: -(-a // b)
+    def count(length, want, least):
+        want = max(1, min(want, ceil(length, least)))
+        return ceil(length, ceil(ceil(length, want), 32) * 32)
+    assert p.S1 >= count(n, ceil(1024, units), 512)
+    assert p.S2 >= count(budget, ceil(1024, units), 128) and p.chunk2 <= 8192
+    assert p.S3 >= count(budget, ceil(256, units), 256)
+
+
+def test_fp32_splits_fit_the_fixed_scratch(plan):
+    # the finest splits that fit, not all or nothing: 2048 retained keys take
+    # fewer of them than 512, and neither falls back to the coarse ones
+    small = plan(8, 8, 128, G.GRKV_F32, 8192, 16, 512)
+    large = plan(8, 8, 128, G.GRKV_F32, 8192, 16, 2048)
+    assert max(small.total, large.total) <= G.NOALLOC_SCRATCH_BYTES
+    assert small.S1 == 64 and large.S1 > 16 and large.S2 > 16
+    # a call that no splits keep inside it takes the finest
+    big = plan(31, 16, 64, G.GRKV_F32, 16227, 16, 6612)
+    assert big.total > G.NOALLOC_SCRATCH_BYTES and big.S1 >= 32
