@@ -113,7 +113,10 @@ typedef struct {
  * that a given call does not run leaves its two events unrecorded: the bf16
  * path (head_dim 64/128, G*w <= 128) folds FULL_Y, RESID and GRAM into
  * neighbouring stages, reads the retained rows inside RET_PROB (no GATHER) and
- * forms the retained softmax from the full-cache log-sum-exp (no RET_LSE). */
+ * forms the retained softmax from the full-cache log-sum-exp (no RET_LSE).  fp32
+ * calls of up to 128 rows record every stage but KEY; their RESID follows GRAM
+ * and holds the sums of the X V0 and N partials (nothing in calls of one or two
+ * of them each), R itself is formed in SOLVE. */
 enum {
   GRKV_STAGE_FULL_LSE = 0,     /* full-cache pass A: reference / sum-exp per split */
   GRKV_STAGE_FULL_LSE_COMBINE, /* -> log-sum-exp of every window row */
@@ -125,7 +128,7 @@ enum {
   GRKV_STAGE_RET_LSE_COMBINE,
   GRKV_STAGE_RET_PROB,         /* retained-cache pass B: X V0 (and on the bf16 path
                                   K0 -> k_out, Gram and retained-mass partials) */
-  GRKV_STAGE_RESID,            /* R = Y - X V0 */
+  GRKV_STAGE_RESID,            /* R = Y - X V0, or the sums it is formed from */
   GRKV_STAGE_GRAM,             /* N partials */
   GRKV_STAGE_SOLVE,            /* (Y, R, N combines,) Cholesky, Z, stats */
   GRKV_STAGE_UPDATE,           /* V* = V0 + X_G^T Z */

@@ -356,31 +356,29 @@ int check_pointers(const void* q_obs, const void* K, const void* V, const grkv_p
 
 // The solve of up to 128 rows outside the fast path: Y combined already, X V0
 // and Gram partials of the normalised X (no masses to divide by).  Several
-// splits, or different counts of the two, are summed by one launch over all
-// units into resid and gram, which the solve then reads element by element
-// before it writes them.
-bool generic_sums(const Plan& p) { return p.S2 > 2 || p.S3 != p.S2; }
+// splits, or different counts of the two, are summed first by one launch over
+// all units (generic_sums) into resid and gram, which the solve then reads
+// element by element before it writes them.
+bool generic_presum(const Plan& p) { return p.S2 > 2 || p.S3 != p.S2; }
+
+hipError_t generic_sums(const Plan& p, char* ws, hipStream_t s) {
+  if (!generic_presum(p)) return hipSuccess;
+  auto F = [&](size_t o) { return (float*)(ws + o); };
+  const float* part[kCombineSegs] = {F(p.xvpart), F(p.npart), nullptr, nullptr};
+  float* const outs[kCombineSegs] = {F(p.resid), F(p.gram), nullptr, nullptr};
+  const size_t per[kCombineSegs] = {(size_t)p.mp * p.d, (size_t)p.mp * p.mp, 0, 0};
+  const int S[kCombineSegs] = {p.S2, p.S3, 0, 0};
+  return launch_combine_parts(p.U, S, part, outs, per, s);
+}
 
 hipError_t generic_solve(const Plan& p, char* ws, float* y, float* stats, hipStream_t s) {
   auto F = [&](size_t o) { return (float*)(ws + o); };
   Plan q = p;
   q.csplit = 1;
   q.rag = nullptr;
-  const float* xv = F(p.xvpart);
-  const float* np = F(p.npart);
-  int S = p.S2;
-  if (generic_sums(p)) {
-    const float* part[kCombineSegs] = {xv, np, nullptr, nullptr};
-    float* const outs[kCombineSegs] = {F(p.resid), F(p.gram), nullptr, nullptr};
-    const size_t per[kCombineSegs] = {(size_t)p.mp * p.d, (size_t)p.mp * p.mp, 0, 0};
-    const int Sc[kCombineSegs] = {p.S2, p.S3, 0, 0};
-    const hipError_t e = launch_combine_parts(p.U, Sc, part, outs, per, s);
-    if (e != hipSuccess) return e;
-    xv = F(p.resid);
-    np = F(p.gram);
-    S = 1;
-  }
-  return launch_solve(q, y, 1, S, xv, np, nullptr, nullptr, 0.f, nullptr, y, F(p.resid),
+  const bool pre = generic_presum(p);
+  return launch_solve(q, y, 1, pre ? 1 : p.S2, pre ? F(p.resid) : F(p.xvpart),
+                      pre ? F(p.gram) : F(p.npart), nullptr, nullptr, 0.f, nullptr, y, F(p.resid),
                       F(p.gram), F(p.z), (uint16_t*)(ws + p.zhi), (uint16_t*)(ws + p.zlo),
                       F(p.stats_ws), stats, (double*)(ws + p.zpart), nullptr, nullptr, nullptr,
                       nullptr, nullptr, s);
@@ -468,8 +466,7 @@ int run_compress(const Plan& p, const void* q_obs, const void* K, const void* V,
   // the generic value step needs X itself, which only the generic pass writes
   GRKV_STAGE(GRKV_STAGE_RET_PROB,
              fast_merge ? launch_stream(p, ret, 2, s) : launch_prob_pass(p, ret, s));
-  const bool small_solve = !fast_merge && solve_supported(p);
-  if (!fast_merge && !small_solve)
+  if (!fast_merge && solve_big_supported(p))
     GRKV_STAGE(GRKV_STAGE_RESID,
                launch_combine_rows(p, F(p.xvpart), p.S2, F(p.y), F(p.resid), s));
   // 4. value step: N, Cholesky solve for Z, V* = V0 + X_G^T Z
@@ -505,10 +502,9 @@ int run_compress(const Plan& p, const void* q_obs, const void* K, const void* V,
       GRKV_STAGE(GRKV_STAGE_SOLVE,
                  launch_solve_big(p, F(p.npart), p.S3, F(p.y), F(p.resid), F(p.gram), F(p.z),
                                   F(p.stats_ws), out->stats, Dd(p.zpart), s));
-    } else if (small_solve) {
-      GRKV_STAGE(GRKV_STAGE_SOLVE, generic_solve(p, ws, F(p.y), out->stats, s));
     } else {
-      return GRKV_ERR_HIP;   // (every plan has one of the solves)
+      GRKV_STAGE(GRKV_STAGE_RESID, generic_sums(p, ws, s));
+      GRKV_STAGE(GRKV_STAGE_SOLVE, generic_solve(p, ws, F(p.y), out->stats, s));
     }
     GRKV_STAGE(GRKV_STAGE_UPDATE,
                launch_update_gen(p, F(p.x), fixed, F(p.z), F(p.stats_ws), ws + p.v0c,
@@ -685,6 +681,7 @@ int grkv_compress_kv(const void* q_obs, const void* K, const void* V, int64_t n,
                              s) != hipSuccess ||
           launch_prob_pass(p32, r, s) != hipSuccess ||
           launch_gram(p32, x, fixed, F(p.npart), s) != hipSuccess ||
+          generic_sums(p32, ws, s) != hipSuccess ||
           generic_solve(p32, ws, F(p.y), out->stats, s) != hipSuccess ||
           hipMemcpyAsync(out->v_out, v0f, vbytes, hipMemcpyDeviceToDevice, s) != hipSuccess ||
           launch_update_add(p32, x, fixed, F(p.z), F(p.stats_ws), out->v_out, s) != hipSuccess)

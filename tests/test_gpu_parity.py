@@ -11,7 +11,7 @@ import pytest
 
 import workloads as W
 from oracle import grkv_oracle as O
-from tests.parity import check_unit, run_gpu
+from tests.parity import check_unit, run_gpu, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -336,6 +336,36 @@ def test_retained_mass_far_below_full_cache(fix_window, kv_heads):
 def test_fp32_shapes(label, over):
     # the fp32 split counts, and the solve on one, two and many summed partials
     _full_check(W.config(1, **over), "fp32-" + label)
+
+
+@pytest.mark.parametrize("over", [dict(), dict(layers=150, n=400, budget=200),
+                                  dict(group=4, window=32, n=3000, budget=500),
+                                  dict(group=8, window=32, n=1500, budget=300)],
+                         ids=["two-splits", "2-and-1-splits", "many-splits", "m-256"])
+def test_fp32_records_every_stage(over):
+    # the generic path runs every stage but the key step, whatever the splits
+    import ctypes
+    import paper_2605_31105_amd as G
+    cfg = W.config(1, **over)
+    q, K, V = (to_device(a, cfg.dtype) for a in _batch(cfg))
+    hip = ctypes.CDLL("libamdhip64.so")
+    names = [s for s in G.STAGES if s != "key"]
+    evs = (ctypes.c_void_p * (2 * G.NUM_STAGES))()
+    for s in names:
+        for k in range(2):
+            e = ctypes.c_void_p()
+            assert hip.hipEventCreate(ctypes.byref(e)) == 0
+            evs[2 * G.STAGES.index(s) + k] = e.value
+    G.compress(q, K, V, cfg.window, cfg.budget, cfg.pool_kernel, cfg.lam, stage_events=evs)
+    torch.cuda.synchronize()
+    for s in names:
+        i, ms = G.STAGES.index(s), ctypes.c_float()
+        st = hip.hipEventElapsedTime(ctypes.byref(ms), ctypes.c_void_p(evs[2 * i]),
+                                     ctypes.c_void_p(evs[2 * i + 1]))
+        assert st == 0 and ms.value >= 0, "stage %s not recorded (%d)" % (s, st)
+    for e in evs:
+        if e:
+            hip.hipEventDestroy(ctypes.c_void_p(e))
 
 
 def test_fp32_singular():
