@@ -70,7 +70,7 @@ static void split_rounds(int64_t len, int64_t want, int64_t min_len, bool fine, 
 static void layout_plan(Plan* p, size_t slots, size_t splits2, size_t splits3, size_t tab);
 
 int make_plan(const grkv_problem* prob, int64_t n, int32_t window, int32_t budget,
-              int32_t pool_kernel, float lambda, const grkv_options* opt, Plan* p) {
+              int32_t pool_kernel, float lambda, const grkv_options* opt, Plan* p, bool ragged) {
   if (!prob) return GRKV_ERR_INVALID;
   if (prob->units < 1 || prob->group < 1) return GRKV_ERR_INVALID;
   if (prob->dtype != GRKV_BF16 && prob->dtype != GRKV_F32) return GRKV_ERR_INVALID;
@@ -162,10 +162,13 @@ int make_plan(const grkv_problem* prob, int64_t n, int32_t window, int32_t budge
       // (from 16 splits on, more of them cost the combine more than the pass
       // gains: 2048 retained keys in 32 splits 164 us a call, in 16 162 us; 512
       // in 8 124 us, in 4 129 us)
-      // (here too: 50 units with 434 retained keys in 5 splits 169 us, in 4 167 us)
+      // (here too: 50 units with 434 retained keys in 5 splits 169 us, in 4 167 us;
+      // a ragged call has no such launch, its solve sums the partials: 8 units of
+      // 1024 retained keys on average in 16 splits 150 us, in 8 141; 23 of 655 in 10
+      // 153, in 6 144)
       const int64_t want_ret = std::min(ceil_div(target_ret, p->U),
                                         std::max<int64_t>(16, ceil_div(budget, 128)));
-      split_rounds(budget, want_ret, 128, fine, p->U, 256, &p->S2, &p->chunk2);
+      split_rounds(budget, want_ret, 128, fine && !ragged, p->U, 256, &p->S2, &p->chunk2);
       if (p->S2 < kPrecombineRetSplits)
         split_rounds(budget, want_ret, 128, false, p->U, 256, &p->S2, &p->chunk2);
       if (p->chunk2 > 4096) split_range(budget, ceil_div(budget, 4096), 128, &p->S2, &p->chunk2);
@@ -772,7 +775,7 @@ static int make_ragged_plan(const grkv_problem* prob, int64_t n, int32_t window,
   int cmean = (int)((sum + U / 2) / U);
   if (cmean < window) cmean = window;
   if (cmean > n) cmean = (int)n;
-  const int st = make_plan(prob, n, window, cmean, pool_kernel, lambda, opt, p);
+  const int st = make_plan(prob, n, window, cmean, pool_kernel, lambda, opt, p, true);
   if (st != GRKV_OK) return st;
   if (!(stream_supported(*p) && p->fast_merge)) return GRKV_OK;
   // slots per retained-pass split and per update block: the mean budget's, or up

@@ -79,10 +79,11 @@ struct Plan {
 
 constexpr int kZParts = 16;   // solve blocks per unit at most, plus ||Y||^2 (entry 15)
 
-// Fills `plan`; returns GRKV_OK or the error the call must report.
+// Fills `plan`; returns GRKV_OK or the error the call must report.  ragged: the
+// plan is of the mean budget of a ragged call.
 int make_plan(const grkv_problem* prob, int64_t n, int32_t window,
               int32_t budget, int32_t pool_kernel, float lambda,
-              const grkv_options* opt, Plan* plan);
+              const grkv_options* opt, Plan* plan, bool ragged = false);
 
 // One streamed attention pass over nk keys per unit.
 struct AttnPass {

@@ -27,12 +27,13 @@ def plan(tmp_path_factory):
                     "-I" + os.path.join(PKG, "csrc"), os.path.join(ROOT, "tests", "plan_probe.cpp"),
                     G.lib_path(), "-Wl,-rpath," + PKG, "-o", so], check=True)
     fn = ctypes.CDLL(so).plan_probe
-    fn.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.c_void_p]
+    fn.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32,
+                   ctypes.c_void_p]
 
-    def probe(units, group, d, dtype, n, window, budget):
+    def probe(units, group, d, dtype, n, window, budget, ragged=0):
         prob = G.Problem(units, group, d, dtype)
         out = (ctypes.c_int64 * len(FIELDS))()
-        st = fn(ctypes.byref(prob), n, window, budget, out)
+        st = fn(ctypes.byref(prob), n, window, budget, ragged, out)
         return SimpleNamespace(**dict(zip(FIELDS, out))) if st == G.GRKV_OK else None
 
     return probe
@@ -81,3 +82,14 @@ def test_fp32_splits_fit_the_fixed_scratch(plan):
     # a call that no splits keep inside it takes the finest
     big = plan(31, 16, 64, G.GRKV_F32, 16227, 16, 6612)
     assert big.total > G.NOALLOC_SCRATCH_BYTES and big.S1 >= 32
+
+
+@pytest.mark.parametrize("units,group,n,budget,uniform,ragged", [
+    (8, 4, 8192, 1024, 16, 8), (23, 8, 1422, 655, 11, 6), (11, 4, 2891, 565, 9, 5),
+    (64, 4, 24001, 2000, 4, 4),
+])
+def test_ragged_retained_splits(plan, units, group, n, budget, uniform, ragged):
+    # the shorter ranges of small calls pay where a launch sums their partials,
+    # which a ragged call does not have
+    assert plan(units, group, 128, G.GRKV_BF16, n, 16, budget).S2 == uniform
+    assert plan(units, group, 128, G.GRKV_BF16, n, 16, budget, 1).S2 == ragged
