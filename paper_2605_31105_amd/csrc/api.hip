@@ -249,17 +249,20 @@ static void layout_plan(Plan* p, size_t slots, size_t splits2, size_t splits3, s
 void make_key_plan(const Plan& p, int steps, KeyPlan* kp) {
   // While every unit is iterating: about one block per compute unit, the count
   // rounded down where a block fills one (128 rows: 48 units of 2000 keys in 5
-  // splits 1.95 ms a call, in 6 2.19) and up where two fit (32 rows; 64 with more
-  // than 64 units: 155 units of 3000 keys in one split 5.6 ms, in two 4.0; with
-  // 48 units 5 splits 1.55 ms, 6 1.65).  Past 128 units of 128 rows one split
-  // leaves compute units idle and two take a second round, which shrinks as units
-  // converge: long units take two (one split / two: 129 units of 3500 keys 5.4 /
-  // 4.5 ms, of 2000 3.94 / 3.70, of 1000 3.40 / 3.47; 220 of 3500 6.7 / 6.4, of
-  // 2000 4.94 / 5.03).
+  // splits 1.95 ms a call, in 6 2.19) and up where two fit: 32 rows; 64 with more
+  // than 64 units (155 units of 3000 keys in one split 5.6 ms, in two 4.0), and
+  // long units in fewer (52 of 5000 keys in 4 splits 2.40 ms, in 5 2.17; of 3000
+  // 1.74 / 1.70; 60 of 2500 1.62 / 1.64, 40 of 2000 1.40 / 1.43).
+  // Past 128 units of 128 rows one split leaves compute units idle, and two take
+  // a second round of 2 U - 256 blocks, which is gone once U - 128 units have
+  // converged: long units take two, from a length that rises with the units (one
+  // split / two: 130 units of 1000 keys 3.27 / 3.15 ms; 150 of 1500 4.06 / 4.09, of
+  // 1900 4.22 / 4.11; 170 of 1900 4.09 / 4.16, of 2100 3.96 / 3.88; 210 of 2100 4.63
+  // / 4.64, of 3000 5.73 / 5.53; 250 of 1900 5.67 / 5.75, of 3000 6.22 / 6.00).
   // Later: about 2048 blocks, when a unit's iteration spanning several compute
   // units keeps it short once only a few units are still converging
-  const bool up = p.mp == 32 || (p.mp == 64 && p.U > 64) ||
-                  (p.mp == 128 && p.U > 128 && p.c >= (p.U <= 144 ? 1792 : 2304));
+  const bool up = p.mp == 32 || (p.mp == 64 && (p.U > 64 || p.c >= 2816)) ||
+                  (p.mp == 128 && p.U > 128 && p.c >= std::min(2432, 1024 + 24 * (p.U - 130)));
   split_range(p.c, up ? ceil_div(256, p.U) : 256 / p.U, 64, &kp->S_full, &kp->chunk_full);
   split_range(p.c, ceil_div(2048, p.U), 64, &kp->S4, &kp->chunk4);
   // the ring passes' later iterations: about 1024 blocks (fewer partials for

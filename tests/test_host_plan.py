@@ -43,9 +43,11 @@ def plan(tmp_path_factory):
     # two blocks of up to 64 rows share a compute unit: one split per unit would
     # leave half of it idle
     (32, 90, 2500, 3), (32, 155, 3370, 2), (64, 130, 2500, 2), (64, 255, 2000, 2), (64, 48, 2000, 5),
+    (64, 52, 5000, 5), (64, 60, 7900, 5), (64, 60, 2500, 4),
     # a block of 128 rows fills one: whole rounds, but long units past 128 of them
     (128, 48, 2000, 5), (128, 104, 500, 2), (128, 200, 1000, 1), (128, 129, 3500, 2),
-    (128, 220, 3500, 2), (128, 256, 4000, 1),
+    (128, 220, 3500, 2), (128, 256, 4000, 1), (128, 130, 1100, 2), (128, 170, 2087, 2),
+    (128, 170, 1900, 1), (128, 210, 2100, 1),
 ])
 def test_key_step_splits(plan, rows, units, keys, splits):
     for d in (64, 128):
