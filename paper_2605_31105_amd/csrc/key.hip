@@ -825,6 +825,7 @@ __global__ __launch_bounds__(1024) void key_cg_kernel(
 // costs what the split saves).
 constexpr int kCgTh = 1024;
 constexpr int kCgLoads = 8;    // split partials a thread loads together
+constexpr int kCgSplitUnits = 12;
 
 template <int MP, int D>
 __global__ __launch_bounds__(kCgTh) void key_cg_split_kernel(
@@ -1003,11 +1004,12 @@ __global__ __launch_bounds__(kCgTh) void key_cg_split_kernel(
 template <int MP, int D>
 hipError_t launch_cg(const Plan& p, const KeyArgs& a, int S, hipStream_t s) {
   // The blocks of one unit cost a fence each: they pay from a megabyte of
-  // partials per unit and with at most 8 units.  Whole calls, one block per unit
-  // against kCgBlocks: 8 units of 3277 keys (26 splits) 1355 / 1067 us, of 1024
-  // (16) 1543 / 1409, of 512 (8) 1546 / 1631; 16 of 1024 (16) 1423 / 1455, 32 of
-  // 1024 2237 / 2602, 128 of 496 3198 / 8771.
-  if (2 * p.U <= kCgBlocks && (size_t)S * MP * D * sizeof(float) >= (size_t)1 << 20)
+  // partials per unit and with at most kCgSplitUnits units, whose single blocks
+  // would leave most of the chip idle.  Whole calls, one block per unit against
+  // kCgBlocks: 8 units of 3277 keys (26 splits) 1011 / 851 us, of 1100 1496 / 1307,
+  // of 512 (8 splits) 1546 / 1631; 12 units of 2000 1825 / 1552, 15 of 2000 1217 /
+  // 1228, 16 of 1100 1465 / 1486, 32 of 1024 2237 / 2602, 128 of 496 3198 / 8771.
+  if (p.U <= kCgSplitUnits && (size_t)S * MP * D * sizeof(float) >= (size_t)1 << 20)
     hipLaunchKernelGGL((key_cg_split_kernel<MP, D>), dim3(kCgBlocks, p.U), dim3(kCgTh), 0, s,
                        a.opart, a.hpart, S, a.Fm, a.alpha, a.r, a.p, a.sdot, a.cg, a.cgpart,
                        a.cgcount, a.lam_k, a.tol, a.max_iter);

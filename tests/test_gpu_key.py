@@ -158,6 +158,41 @@ def test_key_value_outputs_match_compress():
     assert torch.equal(a.v_out, b.v_out) and torch.equal(a.stats, b.stats)
 
 
+SPLIT_CG = [
+    # label, units, group, head dim, n, budget, steps; calls of few units with a
+    # megabyte of split partials each (splits of 64 keys), in every row count and
+    # head dimension, counts that are not multiples of the loads together.
+    # (The 2^-12 relative rounding of Y bounds the relative error of the right-hand
+    # side E at 2^-12 / sqrt(D_after): n is chosen so that every D_after is above
+    # 0.02, 1.7e-3.  At n = 2100 and 1700 retained keys D_after is 2.4e-3, the bound
+    # 5e-3, and the split and the one-block update alike are 4.5e-3 off.)
+    ("m-128-d-128", 2, 4, 128, 8192, 1700, 1),
+    ("m-128-d-64", 2, 4, 64, 8192, 2100, 1),
+    ("m-96-d-128-9-units", 9, 3, 128, 12000, 2100, 1),
+    ("m-64-d-128", 2, 2, 128, 8192, 2100, 1),
+    ("m-64-d-64", 1, 2, 64, 16384, 4200, 1),
+    ("m-32-d-128", 1, 1, 128, 20000, 4200, 1),
+    ("m-32-d-64", 1, 1, 64, 32768, 8230, 1),
+    ("m-128-d-128-two-steps", 2, 4, 128, 8192, 1100, 2),
+]
+
+
+@pytest.mark.parametrize("label,units,group,d,n,budget,steps", SPLIT_CG, ids=[c[0] for c in SPLIT_CG])
+def test_key_split_update(label, units, group, d, n, budget, steps):
+    cfg = W.config(2, layers=1, kv_heads=units, group=group, head_dim=d, n=n, budget=budget)
+    print("case split update", label, flush=True)
+    q, K, V = W.make_batch(cfg)
+    gpu = _run(cfg, q, K, V, steps=steps, max_iter=200)
+    for u in range(units):
+        if steps == 1:
+            print(_check(cfg, q, K, V, gpu, u), flush=True)
+        else:
+            print(_alt_check(cfg, q, K, V, gpu, u, steps), flush=True)
+    again = _run(cfg, q, K, V, steps=steps, max_iter=200)
+    for k in ("kstar", "info"):
+        assert np.array_equal(gpu[k], again[k]), k
+
+
 def test_key_deterministic():
     cfg = W.config(2)
     q, K, V = W.make_batch(cfg)
