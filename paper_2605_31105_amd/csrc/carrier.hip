@@ -4,12 +4,12 @@
 // cosine similarity with its own (the key-similarity matching of D2O/KVMerger),
 // and the loads a_i of the retained slots are summarised per unit.
 //
-// match_kernel: a block takes 256 consecutive cache positions of one unit (two
-// 16-row tiles per wave in registers) and streams the unit's retained keys
-// through LDS in tiles of 64, gathered through idx; the inverse norm of each
+// match_kernel: a block takes 128 or 256 consecutive cache positions of one unit
+// (one or two 16-row tiles per wave in registers) and streams the unit's retained
+// keys through LDS in tiles of 64, gathered through idx; the inverse norm of each
 // retained key is formed while the tile is staged (NaN past the last slot, so
 // that those never compare larger).  S = K_q K_ret^T runs on the bf16 MFMA
-// (exact products, fp32 sums); a lane keeps, for each of its 8 rows, the best
+// (exact products, fp32 sums); a lane keeps, for each of its 4 or 8 rows, the best
 // (S / ||k_i||, slot) over the keys it sees, in increasing slot order, and the
 // 16 lanes that share a row settle the row at the end (equal values go to the
 // lower slot).  Scaling by 1 / ||k_j|| is left out: it does not change the
@@ -19,15 +19,17 @@
 // key costs every block the same.  The products of the next 16 keys are issued
 // among the compares of the current ones, with one barrier per tile; the norm
 // is a corrected hardware estimate, and row addresses are looked up
-// a tile ahead.  64 units of 32k tokens and 2048 keys: 1606 -> 1345 us (four row
-// tiles per wave, at one block per compute unit, 1570 us).
+// a tile ahead.  Whole calls, 64 units of 32k tokens and 2048 keys: 1677 -> 1320 us
+// (four row tiles per wave, at one block per compute unit, about 1600).
 // stats_kernel: one block per unit; loads by LDS atomics, then b, b_eff, A_max,
 // the Gini coefficient (exact integer sum of |a_i - a_j| over all pairs: with
 // F(v) the number of loads <= v it is 2 sum_v F(v) (c - F(v)), from a histogram
-// of the loads and one scan; over the pairs themselves when a load reaches the
-// histogram's size), and the boundary-carrier figures.  With 64 units of 32k
+// of the loads and one scan; over the pairs themselves with few slots and when a
+// load reaches the histogram's size), and the boundary-carrier figures.  With 64 units of 32k
 // tokens and 2048 slots: 147 -> 14 us.
 #include <math.h>
+
+#include <type_traits>
 
 #include "grkv_device.h"
 #include "grkv_internal.h"
@@ -155,9 +157,11 @@ __global__ __launch_bounds__(kMatchWaves * 64) void match_kernel(
   for (int t = 0; t < ntiles; ++t) {
     const int buf = t & 1;
     __syncthreads();   // tile t is in LDS, and every wave is done with tile t - 1
-    store(t + 1);      // (past the last tile: never read)
-    load();
-    rows(t + 3);
+    if (t + 1 < ntiles) {   // (the loads run up to two tiles past the last: never stored)
+      store(t + 1);
+      load();
+      rows(t + 3);
+    }
     // acc[rt]: rows r0 + 16rt + 4g + i, key 16kt + l16
     auto products = [&](int kt, f32x4 (&acc)[RT], float& inv) {
       const int key = 16 * kt + l16;
@@ -229,6 +233,7 @@ __global__ __launch_bounds__(kMatchWaves * 64) void match_kernel(
 
 constexpr int kStatsThreads = 1024;
 constexpr int kMaxCarrierSlots = 8192;
+constexpr int kPairSlots = 256;
 
 // metrics [U][8] = {b, b_eff, A_max, Gini, boundary fraction, boundary share,
 // enrichment, boundary / interior mean load}
@@ -244,15 +249,24 @@ __global__ __launch_bounds__(kStatsThreads) void stats_kernel(
   const int32_t* iu = idx + (size_t)u * c;
   for (int i = tid; i < c; i += kStatsThreads) cnt[i] = 0;
   __syncthreads();
-  for (int64_t j0 = tid; j0 < n; j0 += 16 * kStatsThreads) {   // sixteen loads in flight
-    int a[16];
+  auto count = [&](auto batch_tag) {   // `batch` loads in flight
+    constexpr int B = decltype(batch_tag)::value;
+    for (int64_t j0 = tid; j0 < n; j0 += B * kStatsThreads) {
+      int a[B];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) a[k] = assign[(size_t)u * n + min(j0 + k * kStatsThreads, n - 1)];
+      for (int k = 0; k < B; ++k) a[k] = assign[(size_t)u * n + min(j0 + k * kStatsThreads, n - 1)];
 #pragma unroll
-    for (int k = 0; k < 16; ++k)
-      if (j0 + k * kStatsThreads < n && a[k] >= 0 && a[k] < c) atomicAdd(&cnt[a[k]], 1);
-  }
-  for (int i = tid; i < kMaxCarrierSlots; i += kStatsThreads) hist[i] = 0u;
+      for (int k = 0; k < B; ++k)
+        if (j0 + k * kStatsThreads < n && a[k] >= 0 && a[k] < c) atomicAdd(&cnt[a[k]], 1);
+    }
+  };
+  if (n <= 2 * kStatsThreads) count(std::integral_constant<int, 2>{});
+  else count(std::integral_constant<int, 16>{});
+  // few slots: every pair directly (100 slots: a call 1.3 us shorter than with the
+  // histogram; 256 the same, 512 5 us longer)
+  const bool direct = c <= kPairSlots;
+  if (!direct)
+    for (int i = tid; i < kMaxCarrierSlots; i += kStatsThreads) hist[i] = 0u;
   if (tid == 0) large = 0;
   __syncthreads();
   // per thread: sum a, sum a^2, max a, active, boundary slots, boundary load,
@@ -271,11 +285,12 @@ __global__ __launch_bounds__(kStatsThreads) void stats_kernel(
       sb += a;
     }
     if (counts) counts[(size_t)u * c + i] = (int32_t)a;
+    if (direct) continue;
     if (a < (unsigned long long)kMaxCarrierSlots) atomicAdd(&hist[a], 1u);
     else large = 1;
   }
   __syncthreads();
-  if (!large) {   // (block-uniform)
+  if (!direct && !large) {   // (block-uniform)
     constexpr int PER = kMaxCarrierSlots / kStatsThreads;
     uint32_t h[PER], sum = 0;
 #pragma unroll
@@ -378,10 +393,18 @@ bool carrier_supported(int dtype, int d, int c) {
 hipError_t launch_carrier(const void* K, const int32_t* idx, int U, int64_t n, int c, int d,
                           const float* stats, int32_t* assign, int32_t* counts, float* metrics,
                           float* l_common, hipStream_t s) {
-  // two row tiles per wave when that still gives two blocks per compute unit
-  // (which run side by side at 109 registers), else one
+  // Two row tiles per wave (113 registers, two blocks per compute unit at d = 128)
+  // read each key half as often, one starts sooner and fills the chip with fewer
+  // positions.  One / two tiles, whole calls at d = 128 and 64: 64 units of 8192
+  // positions with 384 slots 122 / 128 and 87 / 89 us, with 512 145 / 141 and 99 / 97,
+  // with 1100 262 / 219 and 168 / 148; 40 units of 3400 positions (560 blocks of two
+  // tiles) with 1100 slots 98 / 101 and 69 / 74; 8 of 8192 with 512 38 / 42 and 31 /
+  // 36.  Where two tiles take one round at d = 128 and one tile a second past its
+  // three blocks per compute unit: 132 of 706 with 255 41.8 / 39.3, 100 of 1000 with
+  // 900 78.8 / 68.0, but 180 of 500 with 400 (720 blocks of one tile) 44.1 / 48.4.
   auto blocks = [&](int tiles) { return (n + 16 * tiles * kMatchWaves - 1) / (16 * tiles * kMatchWaves); };
-  const int rt = U * blocks(2) >= 512 ? 2 : 1;
+  const int64_t b1 = U * blocks(1), b2 = U * blocks(2);
+  const int rt = (b2 >= 1024 && c >= 512) || (d == 128 && b2 <= 512 && b1 > 768) ? 2 : 1;
   const dim3 grid((unsigned)blocks(rt), U);
 #define GRKV_MATCH(DV, RTV)                                                                  \
   hipLaunchKernelGGL((match_kernel<DV, RTV>), grid, dim3(kMatchWaves * 64), 0, s,            \

@@ -119,9 +119,17 @@ def test_carrier_config4_sampled():
 
 
 @pytest.mark.parametrize("units,n,c,d,kind", [
-    (256, 1000, 200, 128, "normal"),    # two row tiles per wave, a part-filled last key tile
+    (256, 1000, 200, 128, "normal"),    # one row tile per wave, a part-filled last key tile
     (128, 1030, 64, 64, "normal"),      # the same at head dim 64, one whole key tile
-    (2, 20000, 130, 64, "one-carrier"), # a load past the histogram of loads
+    (256, 1000, 512, 128, "normal"),    # two row tiles per wave
+    (205, 1111, 525, 64, "normal"),     # the same at head dim 64, a part-filled last key tile
+    (100, 1000, 100, 128, "normal"),    # two row tiles, since one would take a second round
+    (3, 2048, 300, 128, "normal"),      # the assignments counted two at a time
+    (3, 2049, 300, 128, "normal"),      # and sixteen
+    (4, 900, 256, 128, "normal"),       # the most slots whose pairs are summed directly
+    (4, 900, 257, 64, "normal"),        # the fewest that go through the histogram
+    (2, 20000, 130, 64, "one-carrier"), # one load of all tokens, pairs directly
+    (2, 20000, 300, 64, "one-carrier"), # a load past the histogram of loads
     (2, 3000, 100, 128, "duplicates"),  # equal cosines go to the lower slot
 ])
 def test_carrier_tiles_and_loads(units, n, c, d, kind):
