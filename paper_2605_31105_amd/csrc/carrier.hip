@@ -49,9 +49,9 @@ __device__ __forceinline__ float row_sum(float v) {
 }
 
 // 1 / sqrt(ss) with the square root and then the reciprocal rounded to nearest
-// (Markstein's residual corrections of the hardware estimates; over all
-// mantissas and estimates an ulp off either way, the result differs from the
-// IEEE operations' in 1 of 10^7), 0 for ss = 0 or infinite; ss is scaled by a
+// (Markstein's residual corrections of the hardware estimates; with estimates an
+// ulp off either way, the result is within an ulp of the IEEE operations' and
+// differs from it in about 1 of 10^7), 0 for ss = 0 or infinite; ss is scaled by a
 // power of four where the estimate would leave its normal range.
 __device__ __forceinline__ float inv_norm(float ss) {
   const bool tiny = ss < 0x1p-100f;
