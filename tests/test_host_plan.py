@@ -95,3 +95,10 @@ def test_ragged_retained_splits(plan, units, group, n, budget, uniform, ragged):
     # which a ragged call does not have
     assert plan(units, group, 128, G.GRKV_BF16, n, 16, budget).S2 == uniform
     assert plan(units, group, 128, G.GRKV_BF16, n, 16, budget, 1).S2 == ragged
+
+
+@pytest.mark.parametrize("group,dtype", [(4, G.GRKV_BF16), (8, G.GRKV_BF16), (4, G.GRKV_F32)])
+def test_equal_budgets_are_the_plain_call(plan, group, dtype):
+    for window in (16, 32):
+        one = G.workspace_bytes(8, group, 128, dtype, 8192, window, 512)
+        assert G.workspace_bytes_ragged(8, group, 128, dtype, 8192, window, [512] * 8) == one > 0
