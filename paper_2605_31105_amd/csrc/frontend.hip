@@ -17,12 +17,14 @@
 //    atomic per wave and 32 keys per lane;
 //  * radix rounds on those candidates find T, and they complete the per-head
 //    counts of keys above T and equal to T (shared out in head order).
-// A layer is 1 MB at 8 heads of 32k and one compute unit reads it at about
-// 100 GB/s, so the sweeps are what it costs: four of them (a histogram sweep
-// per radix digit of the whole key, then the counts) took 95 us for 32 layers
-// of 8 x 32k scores, the sample and one sweep take 59 us.
+// What it costs is one compute unit's passes over the layer (1 MB at 8 heads of
+// 32k): four sweeps, a histogram sweep per radix digit of the whole key and then
+// the counts, took 95 us for 32 layers of 8 x 32k scores; the sample, its bisection
+// and one sweep take 60.  The sample and the bisection are about 17 of them (by as
+// much a call of tied scores, which stops after them, is longer than the radix).
 // The bracket is used only when the exact counts confirm that it holds T and
-// the candidates fit; otherwise (heavily tied scores, an unlucky sample) the
+// the candidates fit; otherwise (an unlucky sample, or heavily tied scores, which
+// the sample itself shows) the
 // radix select over the full keys runs: three digits of 11, 11 and 9 bits, one
 // LDS histogram sweep per digit, then a counting sweep.
 #include "grkv_device.h"
@@ -77,8 +79,12 @@ __device__ __forceinline__ uint32_t wave_sum_dpp(uint32_t v) {
 constexpr int kAdaWaves = kAdaThreads / 64;
 constexpr int kAdaSamplePer = 8;
 constexpr int kAdaSample = kAdaSamplePer * kAdaThreads;
-constexpr uint32_t kAdaCand = 12288;   // candidates held in LDS
-constexpr int64_t kAdaInside = 10240;  // ranks a bracket may span (its ends are rounded outwards)
+constexpr uint32_t kAdaCand = 24576;   // candidates held in LDS
+constexpr int64_t kAdaWhole = 12288;   // layers of up to this many keys: every key is one
+// Ranks a bracket may span: its ends are rounded outwards, and the keys between
+// two sampled ranks vary by their root times the sampling stride (1300 where four
+// standard deviations of a rank just fit).
+constexpr int64_t kAdaInside = 18432;
 constexpr uint32_t kAdaTop = 0x7F800001u;
 constexpr uint32_t kAdaSlack = 32768u;
 constexpr int64_t kAdaSparse = 65536;  // four samples span at least 32 keys (one line) from here
@@ -114,29 +120,35 @@ __device__ bool bracket_search(const uint32_t* __restrict__ key, int64_t N, int 
     t1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)t1);
     parity ^= 1;
   };
-  // 1. the bracket [lo, hi): the samples about four standard deviations + 16
-  // ranks either side of rank r = k / stride (fewer where they would hold more
+  // 1. the bracket [lo, hi): the samples about four or five standard deviations
+  // + 8 ranks either side of rank r = k / stride (fewer where they would hold more
   // keys than fit), each bisected down to kAdaSlack units in the
   // last place (2^-8 relative: far less than the ranks' width) and kept on its
-  // safe side
+  // safe side.  (Five, of independent samples, where four samples share a line:
+  // scores of neighbouring positions go together.  With four and half the room
+  // for candidates, 1 to 7% of such layers with scores in runs of 32 alike missed T
+  // or did not fit, and calls of 32 of them took 141 us at 8 x 32k scores and 345 at
+  // 8 x 93k, where the radix takes 95 and 250; now 66 and 123, and independent
+  // scores 60.2 where they took 58.2.)
   uint32_t lo = 0u, hi = kAdaTop;
-  if (N > (int64_t)kAdaCand) {
-    // (one or two heads of a layer that one batch of loads covers: the radix's
+  const bool whole = N <= kAdaWhole;   // every key is inside
+  if (!whole) {
+    // (one or two heads of fewer keys than that pattern is for: the radix's
     // sweeps are as short as the bisection; 30000 keys of one head 21.9 us
-    // against 25.1, four heads of 3200 28.2 against 24.6)
-    if (H <= 2 && N <= (int64_t)kAdaThreads * kAdaUnroll) return false;
+    // against 25.1, 63366 31.5 / 32.7, four heads of 3200 28.2 against 24.6)
+    if (H <= 2 && N < kAdaSparse) return false;
     // sample i is key i * stride, or (layers of at least kAdaSparse keys) key
     // (i / 4) * 4 stride + 8 (i % 4): of four neighbouring samples' span, the
     // first 25 keys
     const int64_t stride = (N + kAdaSample - 1) / kAdaSample;
     const int ns = (int)((N + stride - 1) / stride);
     const bool sparse = N >= kAdaSparse;
-    // (three standard deviations of a sampled rank at least: with fewer the
+    // (four standard deviations of a sampled rank at least: with fewer the
     // bracket often misses T, and the sweep is lost)
     const int r = (int)((int64_t)kk / stride);
     const float sd = sqrtf((float)r * (1.f - fminf((float)r / ns, 1.f)));
-    const int delta = min(4 * (int)sd + 16, (int)(kAdaInside / (2 * stride)));
-    if (delta < 3.f * sd + 1.f) return false;
+    const int delta = min((sparse ? 5 : 4) * (int)sd + 8, (int)(kAdaInside / (2 * stride)));
+    if (delta < 4.f * sd + 1.f) return false;
     uint32_t sv[kAdaSamplePer];
 #pragma unroll
     for (int m = 0; m < kAdaSamplePer; ++m) {
@@ -148,6 +160,7 @@ __device__ bool bracket_search(const uint32_t* __restrict__ key, int64_t N, int 
     const bool act[2] = {r - delta >= 0, r + delta < ns};
     const uint32_t J[2] = {(uint32_t)(r - delta), (uint32_t)(r + delta)};
     uint32_t L[2] = {0u, 0u}, U[2] = {kAdaTop, kAdaTop};
+    uint32_t cl = (uint32_t)ns, ch = 0u;   // samples at or above the lower, the upper bound
 #pragma unroll 1
     for (int it = 0; it < 32; ++it) {
       const bool go0 = act[0] && U[0] - L[0] > kAdaSlack, go1 = act[1] && U[1] - L[1] > kAdaSlack;
@@ -160,12 +173,16 @@ __device__ bool bracket_search(const uint32_t* __restrict__ key, int64_t N, int 
         c1 += sv[m] >= m1;
       }
       totals(c0, c1, t0, t1);
-      if (go0) { if (t0 > J[0]) L[0] = m0; else U[0] = m0; }
-      if (go1) { if (t1 > J[1]) L[1] = m1; else U[1] = m1; }
+      if (go0) { if (t0 > J[0]) L[0] = m0; else { U[0] = m0; ch = t0; } }
+      if (go1) { if (t1 > J[1]) { L[1] = m1; cl = t1; } else U[1] = m1; }
     }
     if (act[0]) hi = U[0];
     if (act[1]) lo = L[1];
     if (!(lo < hi)) return false;
+    // far more samples between the bounds than the ranks chosen: tied scores,
+    // which would not fit (32 layers of 8 x 32k scores of two values 115 us, with the
+    // sweep first 151)
+    if ((int64_t)(cl - ch) * stride > 3 * (int64_t)kAdaCand / 2) return false;
   }
   // 2. one sweep: keys at or above hi counted, keys in [lo, hi) appended.  A
   // wave takes a segment of one head at a time (up to kAdaUnroll keys a lane;
@@ -177,7 +194,6 @@ __device__ bool bracket_search(const uint32_t* __restrict__ key, int64_t N, int 
   __syncthreads();
   const uint32_t width = hi - lo;
   uint32_t above = 0;   // (this wave's share)
-  const bool whole = N <= (int64_t)kAdaCand;   // every key is inside
   const int want = max((P + 64 * kAdaUnroll - 1) / (64 * kAdaUnroll), max(1, kAdaWaves / H));
   const int len = ((P + want - 1) / want + 63) / 64 * 64, nseg = (P + len - 1) / len;
   for (int q = wave; q < H * nseg; q += kAdaWaves) {

@@ -148,6 +148,36 @@ def test_ragged_generic_path(label, cfg_id, over, budgets):
     _ragged_check(cfg, q, K, V, budgets)
 
 
+def _shift_sampled_ranks(flat, kk, above):
+    """Exchanges sampled and other keys so that the search's samples place the
+    kk-th largest key one and a half bracket half-widths off: above (or below) its
+    bracket of sampled ranks."""
+    N = flat.shape[1]
+    stride = -(-N // 8192)
+    ns = -(-N // stride)
+    i = np.arange(ns)
+    pos = (i >> 2) * 4 * stride + 8 * (i & 3) if N >= 65536 else i * stride
+    pos = pos[pos < N]
+    r = kk // stride
+    delta = min((5 if N >= 65536 else 4) * int(np.sqrt(r * (1 - min(r / ns, 1)))) + 8,
+                18432 // (2 * stride))
+    want = r - 3 * delta // 2 if above else r + 3 * delta // 2
+    assert 0 < want < ns
+    free = np.setdiff1d(np.arange(N), pos)
+    for x in flat:
+        T = np.partition(x, N - kk)[N - kk]
+        have = np.count_nonzero(x[pos] >= T)
+        if above:     # fewer samples at or above T
+            a, b = pos[x[pos] >= T], free[x[free] < T]
+        else:
+            a, b = pos[x[pos] < T], free[x[free] >= T]
+        k = abs(have - want)
+        assert (have > want) == above and k <= min(a.size, b.size)
+        a, b = a[:k].copy(), b[:k].copy()
+        x[a], x[b] = x[b], x[a]
+        assert np.count_nonzero(x[pos] >= T) == want
+
+
 @pytest.mark.parametrize("layers,heads,P,budget,dist", [
     (3, 1, 500, 60, "normal"),          # every key fits the candidate area
     (2, 3, 4096, 300, "normal"),        # 12288 keys: the most that fit
@@ -160,11 +190,21 @@ def test_ragged_generic_path(label, cfg_id, over, budgets):
     (2, 4, 6000, 32, "normal"),         # none taken
     (2, 1, 20000, 900, "normal"),       # few heads, one batch of loads: radix
     (2, 1, 40000, 900, "normal"),
+    (2, 1, 66000, 900, "normal"),       # a batch of loads and four samples per cache line
+    (2, 2, 40000, 900, "normal"),
     (3, 17, 997, 90, "normal"),         # more heads than waves, short segments
     (2, 128, 130, 40, "normal"),
     (1, 3, 70001, 30000, "normal"),     # a high rank: the bracket's width is capped
     (1, 8, 65537, 4096, "normal"),
-    (1, 8, 131000, 8192, "normal"),     # too many keys per sample: radix
+    (1, 8, 131000, 8192, "normal"),     # the bracket's width is capped
+    (1, 16, 131000, 8192, "normal"),    # too many keys per sample: radix
+    (2, 8, 20000, 1500, "rank-above"),  # T just above the bracket: full radix
+    (2, 8, 20000, 1500, "rank-below"),  # and just below
+    (2, 5, 8000, 700, "rank-above"),    # the same with one sample per cache line
+    (2, 5, 8000, 700, "rank-below"),
+    (2, 8, 40000, 3000, "runs"),        # neighbouring scores alike
+    (2, 8, 40000, 20000, "zeros"),      # ties at zero
+    (2, 8, 4000, 3900, "zeros"),
 ])
 def test_adaptive_budgets_search_paths(layers, heads, P, budget, dist):
     import paper_2605_31105_amd as G
@@ -183,6 +223,13 @@ def test_adaptive_budgets_search_paths(layers, heads, P, budget, dist):
         if flat.shape[1] >= 65536:
             for k in range(4):
                 flat[:, 8 * k::4 * stride] *= np.float32(1e-3)
+    if dist == "runs":
+        p = (np.repeat(p[:, ::32], 32, axis=1)[:, :P]
+             * np.exp(0.1 * rng.standard_normal((U, P)))).astype(np.float32)
+    if dist == "zeros":
+        p = np.maximum(p - 3.0, 0.0).astype(np.float32)
+    if dist.startswith("rank-"):
+        _shift_sampled_ranks(p.reshape(layers, -1), heads * (budget - 32), dist == "rank-above")
     print("case", layers, heads, P, budget, dist, flush=True)
     got = G.adaptive_budgets(torch.from_numpy(p).cuda(), layers, heads, budget, 32)
     torch.cuda.synchronize()
