@@ -190,6 +190,22 @@ constexpr int kSample = 2 * kLargeCand;
 constexpr int kSamplePer = kSample / kSelectThreads;
 constexpr uint32_t kSampleSlack = 4096;   // 2^-11 relative: far inside the ranks' width
 
+__device__ __forceinline__ int sample_delta(int r) { return 4 * (int)sqrtf((float)r) + 16; }
+
+// Whether the keys between the sampled bounds of both searches can be expected
+// to fit the candidate area (three deviations of their number allowed).
+__device__ bool sample_fits(int P, const Search (&b)[2]) {
+  const int stride = (P + kSample - 1) / kSample, ns = (P + stride - 1) / stride;
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    if (!b[t].wide()) continue;
+    const int r = (int)(b[t].k / (uint32_t)stride), delta = sample_delta(r);
+    const float width = (float)(min(r + delta, ns) - max(r - delta, 0));
+    if ((width + 3.f * sqrtf(width)) * (float)stride > (float)kLargeCand) return false;
+  }
+  return true;
+}
+
 __device__ void sample_bounds(const float* p, int P, const Search (&b)[2], KthWork& wk,
                               uint32_t (&lo)[2], uint32_t (&hi)[2], bool (&try_)[2]) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -214,7 +230,7 @@ __device__ void sample_bounds(const float* p, int P, const Search (&b)[2], KthWo
     hi[t] = b[t].hi;
     const bool w = b[t].wide();
     const int r = w ? (int)(b[t].k / (uint32_t)stride) : 0;
-    const int delta = 4 * (int)sqrtf((float)r) + 16;
+    const int delta = sample_delta(r);
     J[2 * t] = r - delta;
     J[2 * t + 1] = r + delta;
     act[2 * t] = w && r - delta >= 0;
@@ -663,7 +679,10 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelK a) {
   const Search b0[2] = {b[0], b[1]};
   if (tid == 0) { wk.kmin = kmin; wk.kmax = kmax; }
   __syncthreads();   // (also: pooling's stage, on bits, is no longer read)
-  const bool single = P <= kSegBits && one_sweep(p, P, b, wk, band, bits, cnt_sh);
+  // (a threshold so deep that the keys in its bracket would not fit would lose the
+  // sweep: 8 units of 131072 given scores and 16000 retained 671 us a call, 600 without)
+  const bool single = P <= kSegBits && sample_fits(P, b) &&
+                      one_sweep(p, P, b, wk, band, bits, cnt_sh);
   if (!single) {
     __syncthreads();
     b[0] = b0[0];

@@ -152,6 +152,9 @@ EDGE = [
     # memory): a prefix past 32768, a pool of 33, a pool wider than its
     # LDS staging (summed straight from global memory)
     ("prefix-40k", dict(n=40000, budget=1024)),
+    # thresholds just shallow enough for the one sweep, and too deep for it
+    ("prefix-100k", dict(n=100000, budget=8000, kv_heads=1, group=1)),
+    ("prefix-100k-deep", dict(n=100000, budget=24000, kv_heads=1, group=1)),
     ("pool-33", dict(pool_kernel=33)),
     ("pool-8001", dict(n=10000, budget=512, pool_kernel=8001)),
 ]
