@@ -12,10 +12,9 @@ import subprocess
 
 import pytest
 
+from paper_2605_31105_amd.build import CSRC, SOURCES
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-CSRC = os.path.join(ROOT, "paper_2605_31105_amd", "csrc")
-SOURCES = ["attention", "stream", "selection", "merge", "merge_generic", "key", "carrier",
-           "frontend", "api"]
 
 
 @pytest.mark.skipif(os.environ.get("GRKV_HOST_ASAN") != "1", reason="opt-in: GRKV_HOST_ASAN=1")
@@ -31,7 +30,7 @@ def test_host_planning_under_asan(tmp_path):
                         "-Xarch_host", "-fsanitize=address",
                         "-Xarch_host", "-fno-omit-frame-pointer",
                         "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
-                        "-c", os.path.join(CSRC, src + ".hip"), "-o", obj], check=True)
+                        "-c", os.path.join(CSRC, src), "-o", obj], check=True)
         objs.append(obj)
     drv = str(tmp_path / "drv.o")
     exe = str(tmp_path / "host_planning_check")

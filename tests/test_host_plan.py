@@ -1,6 +1,8 @@
 """The host plans (split counts, workspace) of the built library, CPU only."""
 import ctypes
+import math
 import os
+import random
 import shutil
 import subprocess
 from types import SimpleNamespace
@@ -102,3 +104,61 @@ def test_equal_budgets_are_the_plain_call(plan, group, dtype):
     for window in (16, 32):
         one = G.workspace_bytes(8, group, 128, dtype, 8192, window, 512)
         assert G.workspace_bytes_ragged(8, group, 128, dtype, 8192, window, [512] * 8) == one > 0
+
+
+def _plain_total(units, rows, d, bf16, n, window, budget):
+    """Workspace with the split counts of even ranges alone (no finer ones, no
+    rounds of blocks): what any plan of the call may fall back to."""
+    ceil = lambda a, b: -(-a // b)
+    def count(length, want, least):
+        want = max(1, min(want, ceil(length, least)))
+        return ceil(length, ceil(ceil(length, want), 32) * 32)
+    mp = 32
+    while mp < rows:
+        mp *= 2
+    fast = bf16 and mp <= 128
+    want = ceil(1024, units)
+    S1 = count(n, want, 512)
+    if fast:
+        S2 = max(count(budget, ceil(256, units), 128), ceil(budget, 4096))
+        S3 = S2
+    else:
+        S2 = max(count(budget, want if bf16 else ceil(256, units), 128 if bf16 else 256),
+                 ceil(budget, 8192))
+        S3 = count(budget, ceil(256, units), 256)
+    U, esz, P = units, 2 if bf16 else 4, max(n - window, 1)
+    comb = U if fast and S2 >= 8 else 0
+    parts = [U * S1 * mp * 4, U * S1 * mp * 8, U * mp * 8, U * mp * 4, U * S1 * mp * d * 4,
+             U * mp * d * 4, U * P * 4, U * P * 4, U * budget, 0 if fast else U * budget * d * esz,
+             U * S2 * mp * 4, U * S2 * mp * 8, U * mp * 8, U * mp * 4, U * S2 * mp * d * 4,
+             0 if fast else mp * U * budget * 4, U * mp * d * 4, U * S3 * mp * mp * 4,
+             U * S2 * mp * 4 if fast else 0, comb * mp * d * 4, comb * mp * mp * 4, comb * mp * 4,
+             U * mp * mp * 4, U * d * mp * 4, U * d * mp * 2, U * d * mp * 2, U * 16, U * 128]
+    return sum(ceil(b, 256) * 256 for b in parts)
+
+
+def test_plans_cover_their_ranges_and_fit(plan):
+    # random shapes: the splits cover each range without an empty one, in whole
+    # key tiles and inside the kernels' slot limits, and a call that even ranges
+    # keep inside the fixed scratch is planned inside it
+    rng = random.Random(5)
+    log = lambda a, b: int(math.exp(rng.uniform(math.log(a), math.log(b))))
+    fit = 0
+    for _ in range(20000):
+        units, group = log(1, 600), rng.randint(1, 8)
+        window = rng.randint(1, 256 // group)
+        n = window + log(1, 60000) - 1
+        budget = min(n, window + log(1, 20000) - 1)
+        d, bf16 = rng.choice((64, 128)), rng.random() < 0.6
+        shape = (units, group, d, n, window, budget, bf16)
+        p = plan(units, group, d, G.GRKV_BF16 if bf16 else G.GRKV_F32, n, window, budget,
+                 int(bf16 and rng.random() < 0.3))
+        for S, chunk, length in ((p.S1, p.chunk1, n), (p.S2, p.chunk2, budget),
+                                 (p.S3, p.chunk3, budget)):
+            assert S >= 1 and chunk % 32 == 0 and S * chunk >= length > (S - 1) * chunk, shape
+        assert p.chunk2 <= (4096 if bf16 and p.mp <= 128 else 8192), shape
+        assert p.update_slots % 32 == 0 and 32 <= p.update_slots <= 4096, shape
+        if _plain_total(units, group * window, d, bf16, n, window, budget) <= G.NOALLOC_SCRATCH_BYTES:
+            fit += 1
+            assert p.total <= G.NOALLOC_SCRATCH_BYTES, shape
+    assert fit > 3000
