@@ -154,7 +154,7 @@ hipError_t launch_gram(const Plan& p, const float* x, const uint8_t* fixed,
 bool solve_supported(const Plan& p);
 // Fast value step (bf16, mp <= 128): the solve combines the Y, X V0 and Gram
 // partials (writing y, resid and gram) and solves by blocked Cholesky; then
-// v_out = V0 + X_G^T Z is written in one pass from the compact V0 copy.
+// v_out = V0 + X_G^T Z is written in one pass, V0 rows read through idx.
 bool merge_fast_supported(const Plan& p);
 // mpart: row sums of the retained P partials [U][S2][mp] when P was formed
 // against the full-cache LSE lse1_log2 scaled by 2^lse_bias (X = P / row sum;
@@ -184,13 +184,13 @@ hipError_t launch_update(const Plan& p, const void* q, const void* k0,
                          const float* stats_ws, const void* V, const int32_t* idx,
                          float* v_out, const double* zpart, float* stats_user, hipStream_t s);
 
-// Generic value step (any dtype, mp up to 256): Cholesky in LDS; the update
-// adds X_G^T Z into v_out, which the gather filled with V0.
-// Writes the per-unit stats to stats_ws (always) and stats_user (if not null).
-// The same solve for mp = 256 (G * w in (128, 256]) with d 64 or 128: blocked
-// MFMA factorisation of N held block-packed in LDS, one 8-wave block per unit.
-// npart holds S3 Gram partials per unit; it may be gram itself when S3 is 1
-// (each element is read before the same thread overwrites it with N).
+// The solve for mp = 256 (G * w in (128, 256]) with d 64 or 128, from combined Y
+// and R = Y - X V0 and S3 Gram partials per unit: one launch sums the partials and
+// completes N into gram (npart and gram distinct), one factors N, held
+// block-packed in LDS, in p.csplit blocks of 16 waves per unit, each of which
+// solves for its share of the columns of Z.  Writes gram, Z^T and the per-unit
+// stats to stats_ws (always) and stats_user (if not null); with p.csplit > 1 the
+// blocks' ||Z||^2 and ||Y||^2 go to zpart and D after is left to the update.
 bool solve_big_supported(const Plan& p);
 hipError_t launch_solve_big(const Plan& p, const float* npart, int S3, const float* y,
                             const float* resid, float* gram, float* z, float* stats_ws,
@@ -203,6 +203,7 @@ hipError_t launch_solve_big(const Plan& p, const float* npart, int S3, const flo
 hipError_t launch_update_gen(const Plan& p, const float* x, const uint8_t* fixed, const float* z,
                              float* stats_ws, const void* v0c, float* v_out, const double* zpart,
                              float* stats_user, hipStream_t s);
+// v_out += X_G^T Z, where v_out holds V0 (later alternating steps of the key step).
 hipError_t launch_update_add(const Plan& p, const float* x, const uint8_t* fixed,
                              const float* z, const float* stats_ws, float* v_out,
                              hipStream_t s);

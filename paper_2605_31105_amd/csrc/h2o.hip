@@ -371,7 +371,14 @@ __global__ __launch_bounds__(kH2oTh) void h2o_colsum_kernel(
 
 // Stationary 16-wide tiles per wave of a pass with `items` rows (or keys) per
 // unit: four when that still gives two blocks per compute unit, else fewer
-// (shorter blocks over more compute units).
+// (shorter blocks over more compute units).  Whole calls of 8 units of 4 heads, d =
+// 128, one / two / four tiles, the rule's marked: the row pass at 8192 tokens 838 /
+// 752 / 753* us, at 16384 2705 / 2350 / 2321*, one unit of 8192 473* / 510 / 607; the
+// column sums at 8192 748* / 837 / 1227, at 16384 2523 / 2314* / 2935.  With 2 heads
+// the four-tile column sums spill 7 registers and are still the fastest (16 units of
+// 16384 2424 / 2248 / 2200*).  At d = 64 one tile less would be 6% faster at the line
+// itself (8 units of 16384 1620 / 1727* / 2099) and 4% slower past it (2 heads, 24000
+// 1720 / 1651* / 1840).
 int h2o_tiles(int U, int64_t items) {
   for (int t = 4; t > 1; t /= 2)
     if (U * ((items + 128 * t - 1) / (128 * t)) >= 512) return t;

@@ -29,7 +29,7 @@
 // 1602 us.
 //
 // Inputs: the full N (gram), and Y and R = Y - X V0 combined [U][mp][D].
-// Outputs: Z^T (z [U][D][mp]) and the stats, as the generic solve (with
+// Outputs: Z^T (z [U][D][mp]) and the stats, as the solve of up to 128 rows (with
 // csplit > 1 D after is formed by the update from the blocks' ||Z||^2).
 #include "grkv_device.h"
 #include "grkv_internal.h"
