@@ -86,7 +86,7 @@ constexpr int64_t kAdaWhole = 12288;   // layers of up to this many keys: every 
 // standard deviations of a rank just fit).
 constexpr int64_t kAdaInside = 18432;
 constexpr uint32_t kAdaTop = 0x7F800001u;
-constexpr uint32_t kAdaSlack = 32768u;
+constexpr uint32_t kAdaSlack = 256u;
 constexpr int64_t kAdaSparse = 65536;  // four samples span at least 32 keys (one line) from here
 
 // LDS of the one-sweep search, over the histogram area of the full radix.
@@ -122,21 +122,21 @@ __device__ bool bracket_search(const uint32_t* __restrict__ key, int64_t N, int 
   };
   // 1. the bracket [lo, hi): the samples about four or five standard deviations
   // + 8 ranks either side of rank r = k / stride (fewer where they would hold more
-  // keys than fit), each bisected down to kAdaSlack units in the
-  // last place (2^-8 relative: far less than the ranks' width) and kept on its
-  // safe side.  (Five, of independent samples, where four samples share a line:
+  // keys than fit), each bisected until few samples lie between its
+  // ends (or kAdaSlack units in the last place) and kept on its safe side.  (Five, of independent samples, where four samples share a line:
   // scores of neighbouring positions go together.  With four and half the room
   // for candidates, 1 to 7% of such layers with scores in runs of 32 alike missed T
   // or did not fit, and calls of 32 of them took 141 us at 8 x 32k scores and 345 at
-  // 8 x 93k, where the radix takes 95 and 250; now 66 and 123, and independent
-  // scores 60.2 where they took 58.2.)
+  // 8 x 93k, where the radix takes 95 and 250; now 67 and 123, and independent
+  // scores 59.9 where they took 58.4.  Bisected to a fixed 2^-8 relative, scores
+  // within a few percent of each other did not fit either: 142 us, now 64.)
   uint32_t lo = 0u, hi = kAdaTop;
   const bool whole = N <= kAdaWhole;   // every key is inside
   if (!whole) {
-    // (one or two heads of fewer keys than that pattern is for: the radix's
-    // sweeps are as short as the bisection; 30000 keys of one head 21.9 us
-    // against 25.1, 63366 31.5 / 32.7, four heads of 3200 28.2 against 24.6)
-    if (H <= 2 && N < kAdaSparse) return false;
+    // (few heads of fewer keys than that pattern is for: the radix's sweeps are as
+    // short as the bisection; 30000 keys of one head 21.9 us against 25.1, 63366 31.5 /
+    // 32.7, three heads of 10655 27 / 29, four of 5000 29 / 27)
+    if (N < kAdaSparse && H <= (N <= (int64_t)kAdaThreads * kAdaUnroll ? 3 : 2)) return false;
     // sample i is key i * stride, or (layers of at least kAdaSparse keys) key
     // (i / 4) * 4 stride + 8 (i % 4): of four neighbouring samples' span, the
     // first 25 keys
@@ -160,10 +160,13 @@ __device__ bool bracket_search(const uint32_t* __restrict__ key, int64_t N, int 
     const bool act[2] = {r - delta >= 0, r + delta < ns};
     const uint32_t J[2] = {(uint32_t)(r - delta), (uint32_t)(r + delta)};
     uint32_t L[2] = {0u, 0u}, U[2] = {kAdaTop, kAdaTop};
-    uint32_t cl = (uint32_t)ns, ch = 0u;   // samples at or above the lower, the upper bound
+    // (samples at or above L and U: a bound is near enough once few lie between)
+    uint32_t cL[2] = {(uint32_t)ns, (uint32_t)ns}, cU[2] = {0u, 0u};
+    const uint32_t near = (uint32_t)(4 + delta / 32);
 #pragma unroll 1
     for (int it = 0; it < 32; ++it) {
-      const bool go0 = act[0] && U[0] - L[0] > kAdaSlack, go1 = act[1] && U[1] - L[1] > kAdaSlack;
+      const bool go0 = act[0] && cL[0] - cU[0] > near && U[0] - L[0] > kAdaSlack;
+      const bool go1 = act[1] && cL[1] - cU[1] > near && U[1] - L[1] > kAdaSlack;
       if (!go0 && !go1) break;
       const uint32_t m0 = L[0] + (U[0] - L[0]) / 2, m1 = L[1] + (U[1] - L[1]) / 2;
       uint32_t c0 = 0, c1 = 0, t0, t1;
@@ -173,8 +176,8 @@ __device__ bool bracket_search(const uint32_t* __restrict__ key, int64_t N, int 
         c1 += sv[m] >= m1;
       }
       totals(c0, c1, t0, t1);
-      if (go0) { if (t0 > J[0]) L[0] = m0; else { U[0] = m0; ch = t0; } }
-      if (go1) { if (t1 > J[1]) { L[1] = m1; cl = t1; } else U[1] = m1; }
+      if (go0) { if (t0 > J[0]) { L[0] = m0; cL[0] = t0; } else { U[0] = m0; cU[0] = t0; } }
+      if (go1) { if (t1 > J[1]) { L[1] = m1; cL[1] = t1; } else { U[1] = m1; cU[1] = t1; } }
     }
     if (act[0]) hi = U[0];
     if (act[1]) lo = L[1];
@@ -182,7 +185,7 @@ __device__ bool bracket_search(const uint32_t* __restrict__ key, int64_t N, int 
     // far more samples between the bounds than the ranks chosen: tied scores,
     // which would not fit (32 layers of 8 x 32k scores of two values 115 us, with the
     // sweep first 151)
-    if ((int64_t)(cl - ch) * stride > 3 * (int64_t)kAdaCand / 2) return false;
+    if ((int64_t)(cL[1] - cU[0]) * stride > 3 * (int64_t)kAdaCand / 2) return false;
   }
   // 2. one sweep: keys at or above hi counted, keys in [lo, hi) appended.  A
   // wave takes a segment of one head at a time (up to kAdaUnroll keys a lane;

@@ -181,7 +181,8 @@ def _shift_sampled_ranks(flat, kk, above):
 @pytest.mark.parametrize("layers,heads,P,budget,dist", [
     (3, 1, 500, 60, "normal"),          # every key fits the candidate area
     (2, 3, 4096, 300, "normal"),        # 12288 keys: the most that fit
-    (2, 3, 4097, 300, "normal"),        # one head more than fits: sampled
+    (2, 3, 4097, 300, "normal"),        # more than fit: three heads take the radix
+    (2, 4, 3073, 300, "normal"),        # and four are sampled
     (4, 8, 20011, 1500, "normal"),
     (2, 8, 9000, 700, "two-values"),    # ties too many for the bracket: full radix
     (2, 5, 8000, 700, "sampled-low"),   # samples miss the top: the bracket fails its check
@@ -205,6 +206,8 @@ def _shift_sampled_ranks(flat, kk, above):
     (2, 8, 40000, 3000, "runs"),        # neighbouring scores alike
     (2, 8, 40000, 20000, "zeros"),      # ties at zero
     (2, 8, 4000, 3900, "zeros"),
+    (2, 8, 40000, 3000, "narrow"),      # scores within a percent of each other
+    (2, 4, 6000, 700, "narrow"),
 ])
 def test_adaptive_budgets_search_paths(layers, heads, P, budget, dist):
     import paper_2605_31105_amd as G
@@ -226,6 +229,8 @@ def test_adaptive_budgets_search_paths(layers, heads, P, budget, dist):
     if dist == "runs":
         p = (np.repeat(p[:, ::32], 32, axis=1)[:, :P]
              * np.exp(0.1 * rng.standard_normal((U, P)))).astype(np.float32)
+    if dist == "narrow":
+        p = np.exp(0.005 * rng.standard_normal((U, P))).astype(np.float32)
     if dist == "zeros":
         p = np.maximum(p - 3.0, 0.0).astype(np.float32)
     if dist.startswith("rank-"):
