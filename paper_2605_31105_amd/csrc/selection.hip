@@ -188,7 +188,13 @@ __device__ void radix_finish(Search& b, const uint32_t* cand, uint32_t L, KthWor
 // searches start from the full range.
 constexpr int kSample = 2 * kLargeCand;
 constexpr int kSamplePer = kSample / kSelectThreads;
-constexpr uint32_t kSampleSlack = 4096;   // 2^-11 relative: far inside the ranks' width
+// A bound is near enough once at most kSampleNear samples lie between its ends (or
+// kSampleSlack units in the last place).  (Bisected to 2^-11 relative, scores within
+// 0.3% of each other put more keys than fit between the bounds: 8 units of 131072
+// given scores, 8000 retained, 514 us a call before the single sweep, 613 with it,
+// now 430.)
+constexpr uint32_t kSampleNear = 4;
+constexpr uint32_t kSampleSlack = 16;
 
 __device__ __forceinline__ int sample_delta(int r) { return 4 * (int)sqrtf((float)r) + 16; }
 
@@ -200,7 +206,7 @@ __device__ bool sample_fits(int P, const Search (&b)[2]) {
   for (int t = 0; t < 2; ++t) {
     if (!b[t].wide()) continue;
     const int r = (int)(b[t].k / (uint32_t)stride), delta = sample_delta(r);
-    const float width = (float)(min(r + delta, ns) - max(r - delta, 0));
+    const float width = (float)(min(r + delta, ns) - max(r - delta, 0) + (int)kSampleNear);
     if ((width + 3.f * sqrtf(width)) * (float)stride > (float)kLargeCand) return false;
   }
   return true;
@@ -238,17 +244,25 @@ __device__ void sample_bounds(const float* p, int P, const Search (&b)[2], KthWo
     try_[t] = act[2 * t] || act[2 * t + 1];
   }
   // the J-th largest sample (0-based) is the largest x with count(>= x) > J:
-  // L keeps count(>= L) > J, H count(>= H) <= J, from the key range down to
-  // kSampleSlack units in the last place (each bound kept on its safe side)
-  uint32_t L[4], H[4];
+  // L keeps count(>= L) = cL > J, H count(>= H) = cH <= J, from the key range
+  // until near (each bound kept on its safe side)
+  uint32_t L[4], H[4], cL[4], cH[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) { L[i] = b[i >> 1].lo; H[i] = b[i >> 1].hi; }
+  for (int i = 0; i < 4; ++i) {
+    L[i] = b[i >> 1].lo;
+    H[i] = b[i >> 1].hi;
+    cL[i] = (uint32_t)ns;
+    cH[i] = 0u;
+  }
+  auto open = [&](int i) {
+    return act[i] && cL[i] - cH[i] > kSampleNear && H[i] - L[i] > kSampleSlack;
+  };
   int parity = 0;
 #pragma unroll 1
   for (int it = 0; it < 32; ++it) {
     bool more = false;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) more |= act[i] && H[i] - L[i] > kSampleSlack;
+    for (int i = 0; i < 4; ++i) more |= open(i);
     if (!more) break;   // uniform
     uint32_t mid[4];
 #pragma unroll
@@ -270,9 +284,10 @@ __device__ void sample_bounds(const float* p, int P, const Search (&b)[2], KthWo
     const uint32_t cnt[4] = {t01 & 0xFFFFu, t01 >> 16, t23 & 0xFFFFu, t23 >> 16};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      if (!(act[i] && H[i] - L[i] > kSampleSlack)) continue;
-      if (cnt[i] > (uint32_t)J[i]) L[i] = mid[i];
-      else H[i] = mid[i];
+      if (!open(i)) continue;
+      const uint32_t c = (uint32_t)__builtin_amdgcn_readfirstlane((int)cnt[i]);
+      if (c > (uint32_t)J[i]) { L[i] = mid[i]; cL[i] = c; }
+      else { H[i] = mid[i]; cH[i] = c; }
     }
   }
 #pragma unroll

@@ -108,6 +108,26 @@ def test_h2o_end_to_end_against_oracle(pool):
         assert v_err <= 2e-3
 
 
+@pytest.mark.parametrize("n,budget,spread", [(100000, 4096, 0.003), (100000, 8000, 0.003),
+                                             (40000, 2048, 0.0005), (40000, 2048, 0.05)])
+def test_compress_scored_long_prefix_scores_close_together(n, budget, spread):
+    # scores within a fraction of a percent of each other: the sampled bounds are
+    # bisected by counts until their keys fit the candidate area; equal scores and
+    # the bands of nearly equal ones go to the lower positions as the oracle's do
+    import paper_2605_31105_amd as G
+    cfg = W.config(2, layers=1, kv_heads=1, group=1, n=n, budget=budget, pool_kernel=1)
+    q, K, V = W.make_batch(cfg)
+    s = np.exp(spread * np.random.default_rng(n + budget).standard_normal(
+        (cfg.units, n - cfg.window))).astype(np.float32)
+    qd, Kd, Vd = (to_device(a, cfg.dtype) for a in (q, K, V))
+    print("case scored close scores", n, budget, spread, flush=True)
+    res = G.compress_scored(qd, Kd, Vd, cfg.window, cfg.budget, 1, cfg.lam,
+                            torch.from_numpy(s).cuda())
+    torch.cuda.synchronize()
+    order = np.argsort(-s[0].astype(np.float64), kind="stable")[: budget - cfg.window]
+    assert np.array_equal(res.idx[0].cpu().numpy()[: budget - cfg.window], np.sort(order))
+
+
 def test_compress_scored_long_prefix_sample_misses_the_top():
     # a prefix past 32768 positions takes the long-prefix selection, whose
     # first brackets come from every 5th score (stride = ceil(P / 8192)); here
