@@ -190,15 +190,16 @@ def _shift_sampled_ranks(flat, kk, above):
     (2, 4, 6000, 6032, "normal"),       # every token of the layer taken
     (2, 4, 6000, 32, "normal"),         # none taken
     (2, 1, 20000, 900, "normal"),       # few heads, one batch of loads: radix
-    (2, 1, 40000, 900, "normal"),
-    (2, 1, 66000, 900, "normal"),       # a batch of loads and four samples per cache line
+    (2, 1, 40000, 900, "normal"),       # and two batches
+    (2, 1, 66000, 900, "normal"),       # one head, sampled four per cache line
     (2, 2, 40000, 900, "normal"),
     (3, 17, 997, 90, "normal"),         # more heads than waves, short segments
     (2, 128, 130, 40, "normal"),
-    (1, 3, 70001, 30000, "normal"),     # a high rank: the bracket's width is capped
+    (1, 3, 70001, 30000, "normal"),     # a high rank
+    (1, 8, 80000, 6352, "normal"),      # the bracket's width is capped
     (1, 8, 65537, 4096, "normal"),
-    (1, 8, 131000, 8192, "normal"),     # the bracket's width is capped
-    (1, 16, 131000, 8192, "normal"),    # too many keys per sample: radix
+    (1, 8, 131000, 8192, "normal"),     # too many keys per sample: radix
+    (1, 16, 131000, 8192, "normal"),
     (2, 8, 20000, 1500, "rank-above"),  # T just above the bracket: full radix
     (2, 8, 20000, 1500, "rank-below"),  # and just below
     (2, 5, 8000, 700, "rank-above"),    # the same with one sample per cache line
