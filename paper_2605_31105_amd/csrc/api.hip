@@ -123,7 +123,8 @@ int make_plan(const grkv_problem* prob, int64_t n, int32_t window, int32_t budge
   if ((p->fast_merge || solve_big_supported(*p)) && (size_t)p->U * (p->d / 16) <= 256)
     p->csplit = p->d / 16;
   // fine: the finer splits of small calls; in fp32 the blocks that they make (0
-  // and -1: the coarse splits)
+  // and -1: the coarse splits; -2: 512 blocks, fewer than the coarse ones with
+  // many units)
   auto splits = [&](int fine) {
     if (p->dtype == GRKV_F32) {
       // The fp32 kernels hold one to eight waves per block and little else, and
@@ -142,11 +143,16 @@ int make_plan(const grkv_problem* prob, int64_t n, int32_t window, int32_t budge
           *chunk = ch;
         }
       };
-      finest(n, want, 512, &p->S1, &p->chunk1);
-      finest(budget, fine < 0 ? ceil_div(256, p->U) : want, fine < 0 ? 256 : 128, &p->S2,
-             &p->chunk2);
+      finest(n, fine < -1 ? 512 / p->U : want, fine < -1 ? 64 : 512, &p->S1, &p->chunk1);
+      finest(budget, fine < -1 ? 512 / p->U : fine < 0 ? ceil_div(256, p->U) : want,
+             fine < -1 ? 64 : fine < 0 ? 256 : 128, &p->S2, &p->chunk2);
       if (p->chunk2 > 8192) split_range(budget, ceil_div(budget, 8192), 128, &p->S2, &p->chunk2);
-      finest(budget, ceil_div(256, p->U), 256, &p->S3, &p->chunk3);
+      if (fine < -1 && solve_supported(*p)) {
+        p->S3 = p->S2;
+        p->chunk3 = p->chunk2;
+      } else {
+        finest(budget, ceil_div(256, p->U), 256, &p->S3, &p->chunk3);
+      }
       layout_plan(p, (size_t)p->U * budget, (size_t)p->U * p->S2, (size_t)p->U * p->S3, 0);
       return;
     }
@@ -188,7 +194,7 @@ int make_plan(const grkv_problem* prob, int64_t n, int32_t window, int32_t budge
   // 512 265; 124 units of 580 tokens, 256 rows: coarse 525 us, 256 blocks 523, 512
   // 618; 16 units of 4096 544, 392, 429)
   const int finest = p->dtype == GRKV_BF16 ? 1 : p->waves == 8 ? 256 : 512;
-  const int coarsest = p->dtype == GRKV_BF16 ? 0 : -1;
+  const int coarsest = p->dtype == GRKV_BF16 ? 0 : -2;
   for (int fine = finest;; fine = fine > 0 ? fine * 3 / 4 : fine - 1) {
     splits(fine);
     if (p->total <= GRKV_NOALLOC_SCRATCH_BYTES) break;

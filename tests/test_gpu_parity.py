@@ -335,6 +335,9 @@ def test_retained_mass_far_below_full_cache(fix_window, kv_heads):
     # two and three splits of X V0 partials beside one of Gram partials
     ("many-units-2-and-1-splits", dict(layers=150, n=400, budget=200)),
     ("many-units-3-and-1-splits", dict(layers=150, n=400, budget=300)),
+    # as few splits as keep the call inside the fixed scratch
+    ("many-units-fewest-splits", dict(layers=61, kv_heads=3, group=5, head_dim=128, window=9,
+                                      n=4210, budget=10)),
 ], ids=lambda v: v if isinstance(v, str) else "")
 def test_fp32_shapes(label, over):
     # the fp32 split counts, and the solve on one, two and many summed partials

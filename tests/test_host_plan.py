@@ -83,6 +83,11 @@ def test_fp32_splits_fit_the_fixed_scratch(plan):
     large = plan(8, 8, 128, G.GRKV_F32, 8192, 16, 2048)
     assert max(small.total, large.total) <= G.NOALLOC_SCRATCH_BYTES
     assert small.S1 == 64 and large.S1 > 16 and large.S2 > 16
+    # many units of few splits each: in as few as it takes
+    for units, group, d, n, window, budget in ((26, 5, 128, 49788, 18, 39), (183, 5, 128, 4210, 9, 10),
+                                               (113, 8, 64, 11847, 9, 31),
+                                               (18, 4, 64, 51980, 50, 217)):
+        assert plan(units, group, d, G.GRKV_F32, n, window, budget).total <= G.NOALLOC_SCRATCH_BYTES
     # a call that no splits keep inside it takes the finest
     big = plan(31, 16, 64, G.GRKV_F32, 16227, 16, 6612)
     assert big.total > G.NOALLOC_SCRATCH_BYTES and big.S1 >= 32
